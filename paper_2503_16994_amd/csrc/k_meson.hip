@@ -13,96 +13,86 @@
 // Gamma is named by a 4-bit mask m: Gamma_m = g_t^{m3} g_x^{m0} g_y^{m1} g_z^{m2}
 // (ordered product, t first, so m = 15 is g5 = g_t g_x g_y g_z).
 //
-// Kernel 1 (k_meson_partial): workgroup (b, t) stages 16 sites at a time of
-// its 256-site chunk of slice t in LDS (12 x 12 complex each, read coalesced
-// from the canonical columns); thread (site lane, al, al') accumulates the
-// 16 (be, be') entries; the 16 site lanes of a pair are summed by a wave
-// butterfly and the waves in order, giving one partial G per chunk.
+// As a matrix product, G_t = Z Z^H with Z[(al, be)][(x, a, c)] the 16 x 9 V3
+// matrix of slice t, so it runs on the FP64 matrix cores: with Z = Zr + i Zi,
+//   Re G = Zr Zr^T + Zi Zi^T,   Im G = X - X^T,   X = Zi Zr^T,
+// three real 16x16 products instead of the four of a general complex one
+// (G is Hermitian).
+//
+// Kernel 1 (k_meson_partial): workgroup (b, t) takes one chunk of slice t,
+// each of its four waves every fourth group of four sites.  In
+// v_mfma_f64_16x16x4 lane l holds row l % 16 and inner index l / 16 of both
+// operands, so the lane that loads component (al, a) of column (be, c) at
+// site l / 16 of the group holds one entry of the left and of the right
+// operand at once: nine 16-byte loads and 27 matrix instructions per four
+// sites, no LDS and no barrier inside the loop, and the next group's loads in
+// flight meanwhile.  The waves' sums are added in wave order.
 // Kernel 2 (k_meson_reduce): workgroup t sums the chunk partials of every
-// entry in chunk order and contracts with the requested Gamma pairs (a fixed-
-// order block sum).  FP64 throughout; deterministic, no atomics.  The work
-// is a stream of 2304 B per site (HBM bound at FP64: ~9 flop/B).
+// entry in chunk order, forms G and contracts with the requested Gamma pairs
+// (a fixed-order block sum).  FP64 throughout; deterministic, no atomics.
+//
+// Bound: HBM, 2304 B per site read once.  At 32^3x64 the call takes 870 us
+// (5.6 TB/s, against 6.0 TB/s of a plain read-only sum on the same card);
+// staged in LDS 16 sites at a time and accumulated with vector FMAs, 168
+// registers and two barriers per 16 sites, it took 1578 us.
 #include "lqcd_kernels.h"
 
 namespace lqcd {
 
 constexpr int kMesonBlock = 256;
-constexpr int kMesonPass = 16;    // sites staged per pass
-constexpr int kMesonChunk = 256;  // sites per workgroup
+constexpr int kMesonGroup = 4;       // sites of one wave's step (the inner dimension of the matrix instruction)
+constexpr int kMesonMaxChunk = 1024; // sites per workgroup, halved until the grid fills the GPU
+constexpr int kMesonMinChunk = 64;
+constexpr long kMesonGrid = 2048;    // workgroups wanted: eight per CU, two rounds of four
 
 using cd = cpx<double>;
+typedef double d4 __attribute__((ext_vector_type(4)));
 
 __global__ __launch_bounds__(kMesonBlock) void k_meson_partial(const double2* __restrict__ psi, long V, long V3,
-                                                               int nchunk, double2* partials) {
-  __shared__ double2 S[kMesonPass][12][12];  // [site][row al a][col be c]
+                                                               int chunk, int nchunk, double2* partials) {
   const int t = blockIdx.y, b = blockIdx.x, tid = threadIdx.x;
-  const long s0 = (long)t * V3 + (long)b * kMesonChunk;
-  const long s_end = min((long)(t + 1) * V3, s0 + kMesonChunk);
-  const int sl = tid >> 4, pr = tid & 15, al = pr >> 2, al2 = pr & 3;
-  cd acc[4][4];
+  const int w = tid >> 6, l = tid & 63, row = l & 15, al = row >> 2, be = row & 3;
+  const long s_end = min((long)(t + 1) * V3, (long)t * V3 + (long)(b + 1) * chunk);
+  constexpr int kStep = kMesonGroup * (kMesonBlock / 64);
+  long x = (long)t * V3 + (long)b * chunk + kMesonGroup * w + (l >> 4);  // this lane's site
+  // element (c, a) of this lane's (al, be): column 3 be + c, component 3 al + a
+  const double2* p = psi + ((size_t)(3 * be) * V + x) * 12 + 3 * al;
+  double2 z[9], zn[9];
+  auto load = [&](double2 (&v)[9]) {
+    const bool in = x < s_end;
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+    for (int c = 0; c < 3; ++c)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = {0.0, 0.0};
-  for (long base = s0; base < s_end; base += kMesonPass) {
-    // e = (column j, site, component k): consecutive e are consecutive in
-    // memory within a column (16 sites x 12 components)
-    for (int e = tid; e < kMesonPass * 144; e += kMesonBlock) {
-      const int j = e / (kMesonPass * 12), r = e % (kMesonPass * 12);
-      const int site = r / 12, k = r % 12;
-      const long x = base + site;
-      double2 v = make_double2(0.0, 0.0);
-      if (x < s_end) v = psi[((size_t)j * V + x) * 12 + k];
-      S[site][k][j] = v;
+      for (int a = 0; a < 3; ++a) v[3 * c + a] = in ? p[(size_t)c * V * 12 + a] : make_double2(0.0, 0.0);
+    x += kStep;
+    p += kStep * 12;
+  };
+  d4 rr = {0.0, 0.0, 0.0, 0.0}, ii = rr, xx = rr;
+  const int steps = (int)((s_end - ((long)t * V3 + (long)b * chunk) + kStep - 1) / kStep);  // uniform
+  load(z);
+  for (int k = 0; k < steps; ++k) {
+    load(zn);  // past the chunk: zeros, nothing read
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      rr = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].x, z[e].x, rr, 0, 0, 0);
+      ii = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].y, z[e].y, ii, 0, 0, 0);
+      xx = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].y, z[e].x, xx, 0, 0, 0);
     }
-    __syncthreads();
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      cd r1[12], r2[12];
-#pragma unroll
-      for (int q = 0; q < 12; ++q) {
-        const double2 u = S[sl][3 * al + a][q], w = S[sl][3 * al2 + a][q];
-        r1[q] = {u.x, u.y};
-        r2[q] = {w.x, w.y};
-      }
-#pragma unroll
-      for (int c = 0; c < 3; ++c)
-#pragma unroll
-        for (int be = 0; be < 4; ++be)
-#pragma unroll
-          for (int be2 = 0; be2 < 4; ++be2)
-            acc[be][be2] = cmacc(acc[be][be2], r2[3 * be2 + c], r1[3 * be + c]);  // += r1 conj(r2), four FMAs
-    }
-    __syncthreads();
+    for (int e = 0; e < 9; ++e) z[e] = zn[e];
   }
-  // sum the 16 site lanes of every (al, al') pair: lanes pr + 16 k of a wave,
-  // then the four waves in order
-  __shared__ double2 red[kMesonBlock / 64][16][16];
-  const int w = tid >> 6, l = tid & 63;
+  // result element r of lane l: row l / 16 + 4 r, column l % 16
+  __shared__ double2 red[kMesonBlock / 64][256];
 #pragma unroll
-  for (int be = 0; be < 4; ++be)
-#pragma unroll
-    for (int be2 = 0; be2 < 4; ++be2) {
-      cd v = acc[be][be2];
-#pragma unroll
-      for (int off = 16; off < 64; off <<= 1) {
-        v.re += __shfl_xor(v.re, off, 64);
-        v.im += __shfl_xor(v.im, off, 64);
-      }
-      if (l < 16) red[w][pr][4 * be + be2] = make_double2(v.re, v.im);
-    }
+  for (int r = 0; r < 4; ++r) red[w][((l >> 4) + 4 * r) * 16 + row] = make_double2(rr[r] + ii[r], xx[r]);
   __syncthreads();
-  // output entry i = ((al be) al' be'): pair (al, al'), component (be, be')
-  const int i = tid;
-  const int oal = i >> 6, obe = (i >> 4) & 3, oal2 = (i >> 2) & 3, obe2 = i & 3;
   double2 s = make_double2(0.0, 0.0);
 #pragma unroll
   for (int ww = 0; ww < kMesonBlock / 64; ++ww) {
-    const double2 v = red[ww][4 * oal + oal2][4 * obe + obe2];
-    s.x += v.x;
-    s.y += v.y;
+    s.x += red[ww][tid].x;
+    s.y += red[ww][tid].y;
   }
-  partials[((size_t)t * nchunk + b) * 256 + i] = s;
+  partials[((size_t)t * nchunk + b) * 256 + tid] = s;  // (Re G, X) of entry (tid / 16, tid % 16)
 }
 
 // chiral-basis gamma matrices g_x, g_y, g_z, g_t (mu = 0..3): each has one
@@ -157,13 +147,18 @@ struct MesonPairs {
 __global__ __launch_bounds__(256) void k_meson_reduce(const double2* __restrict__ partials, int nchunk, double2* G,
                                                       MesonPairs pairs) {
   __shared__ double red[2][4];
+  __shared__ double xs[256];
   const int t = blockIdx.x, i = threadIdx.x;
   double2 g = make_double2(0.0, 0.0);
+#pragma unroll 8
   for (int b = 0; b < nchunk; ++b) {
     const double2 v = partials[((size_t)t * nchunk + b) * 256 + i];
     g.x += v.x;
     g.y += v.y;
   }
+  xs[i] = g.y;
+  __syncthreads();
+  g.y -= xs[(i & 15) * 16 + (i >> 4)];  // Im G = X - X^T
   if (G) G[(size_t)t * 256 + i] = g;
   // entry i = G[al][be][de][ga]
   const int al = i >> 6, be = (i >> 4) & 3, de = (i >> 2) & 3, ga = i & 3;
@@ -196,13 +191,27 @@ __global__ __launch_bounds__(256) void k_meson_reduce(const double2* __restrict_
   }
 }
 
-int meson_nchunk(long V3) { return (int)((V3 + kMesonChunk - 1) / kMesonChunk); }
+// Sites per workgroup: as many as leave kMesonGrid workgroups (fewer partials
+// to write and sum again), down to one group of 16 sites a wave where the
+// lattice is too small to fill the GPU (there the loop's length is the time).
+static int meson_chunk(long V3, int T) {
+  int c = kMesonMaxChunk;
+  while (c > kMesonMinChunk && T * ((V3 + c - 1) / c) < kMesonGrid) c >>= 1;
+  return c;
+}
+// A chunk below 256 sites means that twice its length left fewer than
+// kMesonGrid workgroups, so there are never more than
+// max(T ceil(V3 / 256), 2 kMesonGrid) partials (4 KiB each, 16 MiB).
+int meson_nchunk(long V3, int T) {
+  const int c = meson_chunk(V3, T);
+  return (int)((V3 + c - 1) / c);
+}
 
 hipError_t launch_meson(const KGeom& g, const double2* psi, int npairs, const int* masks, double2* const* outs,
                         double scale, double2* G, double2* scratch, hipStream_t st) {
   if (npairs < 0 || npairs > kMaxMesonPairs) return hipErrorInvalidValue;
   const long V3 = (long)g.L[0] * g.L[1] * g.L[2], V = V3 * g.L[3];
-  const int nchunk = meson_nchunk(V3);
+  const int chunk = meson_chunk(V3, g.L[3]), nchunk = meson_nchunk(V3, g.L[3]);
   MesonPairs pairs;
   pairs.n = npairs;
   pairs.scale = scale;
@@ -211,7 +220,7 @@ hipError_t launch_meson(const KGeom& g, const double2* psi, int npairs, const in
     pairs.m[p][1] = p < npairs ? masks[2 * p + 1] : 0;
     pairs.out[p] = p < npairs ? outs[p] : nullptr;
   }
-  k_meson_partial<<<dim3(nchunk, g.L[3]), kMesonBlock, 0, st>>>(psi, V, V3, nchunk, scratch);
+  k_meson_partial<<<dim3(nchunk, g.L[3]), kMesonBlock, 0, st>>>(psi, V, V3, chunk, nchunk, scratch);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_meson_reduce<<<g.L[3], 256, 0, st>>>(scratch, nchunk, G, pairs);

@@ -559,7 +559,7 @@ int meson_check(const char* who, const lqcd_geom_t* g, const void* psi, int npai
 
 size_t meson_scratch_bytes(const lqcd_geom_t* g) {
   const long V3 = (long)g->desc.L[0] * g->desc.L[1] * g->desc.L[2];
-  return (size_t)g->desc.L[3] * meson_nchunk(V3) * 256 * sizeof(double2);
+  return (size_t)g->desc.L[3] * meson_nchunk(V3, g->desc.L[3]) * 256 * sizeof(double2);
 }
 }  // namespace lqcd
 

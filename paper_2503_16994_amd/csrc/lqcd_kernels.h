@@ -107,10 +107,10 @@ hipError_t launch_import_gauge(const KGeom& g, const double2* Ucanon, double2* U
 // Meson two-point functions (k_meson.hip): colour-traced spin tensor G per
 // time slice of a 12-column canonical propagator (G may be null) and the
 // correlators of up to kMaxMesonPairs (Gamma, Gamma') mask pairs, times
-// `scale`, into outs[p][t]; scratch holds T x meson_nchunk(V3) x 256
-// complex partials.
+// `scale`, into outs[p][t]; scratch holds T x meson_nchunk(V3, T) x
+// 256 complex partials, never more than max(T x ceil(V3 / 256), 4096) x 256.
 constexpr int kMaxMesonPairs = 32;
-int meson_nchunk(long V3);
+int meson_nchunk(long V3, int T);
 hipError_t launch_meson(const KGeom& g, const double2* psi, int npairs, const int* masks, double2* const* outs,
                         double scale, double2* G, double2* scratch, hipStream_t st);
 // SF boundary source (k_sf.hip): writes the slice y0 = 1 of the 12-column

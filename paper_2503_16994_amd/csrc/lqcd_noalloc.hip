@@ -55,7 +55,9 @@ extern "C" int lqcd_meson_noalloc(const lqcd_geom_t* g, const void* psi, int npa
                                   void* G, void* stream) {
   const int rc = meson_check("lqcd_meson_noalloc", g, psi, npairs, pairs, C, G);
   if (rc) return rc;
-  const size_t need = meson_scratch_bytes(g);
+  // the documented bound; the launch itself never needs more than this or 16 MiB
+  const size_t V3 = (size_t)g->desc.L[0] * g->desc.L[1] * g->desc.L[2];
+  const size_t need = (size_t)g->desc.L[3] * ((V3 + 255) / 256) * 256 * sizeof(double2);
   if (need > (size_t)LQCD_NOALLOC_SCRATCH_BYTES)
     return fail(LQCD_EINVAL, "lqcd_meson_noalloc: lattice needs %zu scratch bytes, above the fixed %zu", need,
                 (size_t)LQCD_NOALLOC_SCRATCH_BYTES);

@@ -51,6 +51,24 @@ def test_meson_matches_oracle_on_random_columns(L):
     assert none is None and np.array_equal(G2.cpu().numpy(), G.cpu().numpy())
 
 
+# 2x2x2x4: half of one 16-site step of a workgroup; 6x2x2x4: V3 = 24, a ragged
+# second step; 10x6x2x4: V3 = 120, a ragged second 64-site chunk; 2x2x2x2046
+# and 2x2x2x2048: both sides of the line where the chunk grows to 1024 sites.
+# Sums of at most 9 V3 products of O(1) numbers: 1e-12 as above.
+@pytest.mark.parametrize("L", [(2, 2, 2, 4), (6, 2, 2, 4), (10, 6, 2, 4), (2, 2, 2, 2046), (2, 2, 2, 2048)],
+                         ids=lambda L: "x".join(map(str, L)))
+def test_meson_chunk_edges(L):
+    print(f"\n[gpu case] meson {L}", flush=True)
+    psi = random_columns(L, seed=sum(L))
+    lat = lqcd.Lattice(L, lqcd.BC_PERIODIC, (1, 1, 1, -1))
+    ws = lqcd.Workspace(lat, lqcd.PM_F64, 1)
+    C, G = lqcd.meson(lat, torch.from_numpy(psi).cuda(), PAIRS, ws)
+    G_ref = orc.meson_G(L, psi)
+    assert rel_max(G.cpu().numpy(), G_ref) < 1e-12
+    for p, (m1, m2) in enumerate(PAIRS):
+        assert rel_max(C[p].cpu().numpy(), orc.meson_correlator(G_ref, m1, m2)) < 1e-12, (m1, m2)
+
+
 def test_meson_of_a_solved_propagator():
     """12 point sources solved by lqcd_solve (8^3x16, FP64 eo-CG, two-row
     links), contracted on the GPU: equal to the oracle's contraction of the
