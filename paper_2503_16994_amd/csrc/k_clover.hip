@@ -14,12 +14,25 @@
 // as the fallback for an indefinite block with a tiny LDL^H pivot
 // (clover_inv.h); a block that is singular to working precision is reported
 // as a numerical error.
+//
+// Work decomposition: a workgroup of six waves owns the 64 sites of one
+// layout tile.  Wave p computes the field strength of plane p (a lane per
+// site) and leaves its nine independent reals in LDS; then wave b < 2
+// assembles, stores and inverts the blocks of chirality b.  One thread per
+// site doing all of it keeps six 3x3 matrices, four leaves and two 6x6 blocks
+// alive: that needed 9 KB of scratch per lane and took 9.2 ms at 32^3x64 (3.26
+// ms at 24^3x48, three precisions stored); this takes 1.88 ms (0.69 ms).
+// Bound: the links through L2 (twelve per plane and site) and FP64 issue.
+// Three waves per SIMD (two workgroups per CU) at the price of 28 spilled
+// registers measure 687 us at 24^3x48, two waves without spills 711 us.
 #include "clover_inv.h"
 #include "lqcd_kernels.h"
 
 namespace lqcd {
 
 using cd = cpx<double>;
+
+constexpr int kCloverPlanes = 6;  // xy, xz, xt, yz, yt, zt: one wave each
 
 struct M3 {
   cd m[9];
@@ -32,9 +45,8 @@ __device__ inline M3 m3_mul(const M3& a, const M3& b) {
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       cd v = cmul(a.m[3 * i], b.m[j]);
-      v = cadd(v, cmul(a.m[3 * i + 1], b.m[3 + j]));
-      v = cadd(v, cmul(a.m[3 * i + 2], b.m[6 + j]));
-      r.m[3 * i + j] = v;
+      v = cmac(v, a.m[3 * i + 1], b.m[3 + j]);
+      r.m[3 * i + j] = cmac(v, a.m[3 * i + 2], b.m[6 + j]);
     }
   return r;
 }
@@ -46,13 +58,9 @@ __device__ inline M3 m3_mul_nd(const M3& a, const M3& b) {
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      cd v = {0.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        const cd bb = b.m[3 * j + k];
-        v = cadd(v, cmul(a.m[3 * i + k], cd{bb.re, -bb.im}));
-      }
-      r.m[3 * i + j] = v;
+      cd v = cmulc(b.m[3 * j], a.m[3 * i]);
+      v = cmacc(v, b.m[3 * j + 1], a.m[3 * i + 1]);
+      r.m[3 * i + j] = cmacc(v, b.m[3 * j + 2], a.m[3 * i + 2]);
     }
   return r;
 }
@@ -64,104 +72,143 @@ __device__ inline M3 m3_mul_dn(const M3& a, const M3& b) {
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      cd v = {0.0, 0.0};
-#pragma unroll
-      for (int k = 0; k < 3; ++k) v = cadd(v, cmulc(a.m[3 * k + i], b.m[3 * k + j]));
-      r.m[3 * i + j] = v;
+      cd v = cmulc(a.m[i], b.m[j]);
+      v = cmacc(v, a.m[3 + i], b.m[3 + j]);
+      r.m[3 * i + j] = cmacc(v, a.m[6 + i], b.m[6 + j]);
     }
   return r;
 }
 
-__device__ inline M3 load_link(const KGeom& g, const double2* U, bool two_row, int x, int y, int z,
-                               int t, int mu) {
-  x = (x + g.L[0]) % g.L[0];
-  y = (y + g.L[1]) % g.L[1];
-  z = (z + g.L[2]) % g.L[2];
-  t = (t + g.L[3]) % g.L[3];
-  const long lex = x + (long)g.L[0] * (y + (long)g.L[1] * (z + (long)g.L[2] * t));
-  const int p = (x + y + z + t) & 1;
-  const size_t s = (size_t)(lex >> 1);
-  const int ne = two_row ? 6 : 9;  // stored complex per link
-  const double2* u = U + (size_t)p * 4 * ne * g.V2p + tix(s, 4 * ne) + mu * ne * kTile;
+// a - b^+
+__device__ inline M3 m3_sub_dag(const M3& a, const M3& b) {
   M3 r;
 #pragma unroll
-  for (int e = 0; e < 6; ++e) {
+  for (int i = 0; i < 3; ++i)
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+      r.m[3 * i + j] = {a.m[3 * i + j].re - b.m[3 * j + i].re, a.m[3 * i + j].im + b.m[3 * j + i].im};
+  return r;
+}
+
+// link U_mu of the site with lexical index lex and parity p
+template <bool TWO_ROW>
+__device__ inline M3 load_link(const KGeom& g, const double2* U, int lex, int p, int mu) {
+  constexpr int ne = TWO_ROW ? 6 : 9;  // stored complex per link
+  const double2* u = U + (size_t)p * 4 * ne * g.V2p + tix((size_t)(lex >> 1), 4 * ne) + mu * ne * kTile;
+  M3 r;
+#pragma unroll
+  for (int e = 0; e < ne; ++e) {
     double2 v = u[e * kTile];
     r.m[e] = {v.x, v.y};
   }
-  if (two_row) {
-    su3_third_row(r.m);
-  } else {
-#pragma unroll
-    for (int e = 6; e < 9; ++e) {
-      double2 v = u[e * kTile];
-      r.m[e] = {v.x, v.y};
-    }
-  }
+  if constexpr (TWO_ROW) su3_third_row(r.m);
   return r;
 }
 
-// traceless anti-Hermitian part of (Q - Q^+)/8 for the (mu, nu) plane at x
-__device__ inline M3 field_strength(const KGeom& g, const double2* U, bool two_row, const int (&x)[4],
-                                    int mu, int nu) {
-  int dm[4] = {0, 0, 0, 0}, dn[4] = {0, 0, 0, 0};
-  dm[mu] = 1;
-  dn[nu] = 1;
-#define LNK(ox, oy, oz, ot, d) load_link(g, U, two_row, x[0] + (ox), x[1] + (oy), x[2] + (oz), x[3] + (ot), d)
-  const M3 Um_x = LNK(0, 0, 0, 0, mu);
-  const M3 Un_x = LNK(0, 0, 0, 0, nu);
-  const M3 Un_xpm = LNK(dm[0], dm[1], dm[2], dm[3], nu);
-  const M3 Um_xpn = LNK(dn[0], dn[1], dn[2], dn[3], mu);
-  const M3 Um_xmm = LNK(-dm[0], -dm[1], -dm[2], -dm[3], mu);
-  const M3 Un_xmm = LNK(-dm[0], -dm[1], -dm[2], -dm[3], nu);
-  const M3 Um_xmmpn = LNK(dn[0] - dm[0], dn[1] - dm[1], dn[2] - dm[2], dn[3] - dm[3], mu);
-  const M3 Um_xmmmn = LNK(-dm[0] - dn[0], -dm[1] - dn[1], -dm[2] - dn[2], -dm[3] - dn[3], mu);
-  const M3 Un_xmmmn = LNK(-dm[0] - dn[0], -dm[1] - dn[1], -dm[2] - dn[2], -dm[3] - dn[3], nu);
-  const M3 Um_xmn = LNK(-dn[0], -dn[1], -dn[2], -dn[3], mu);
-  const M3 Un_xmn = LNK(-dn[0], -dn[1], -dn[2], -dn[3], nu);
-  const M3 Un_xpmmn = LNK(dm[0] - dn[0], dm[1] - dn[1], dm[2] - dn[2], dm[3] - dn[3], nu);
+// Traceless anti-Hermitian part of (Q - Q^+)/8 for the (mu, nu) plane at a
+// site, Q the sum of the four counter-clockwise leaves.  Leaves 1 and 4 start
+// and end with U_mu(x), leaves 2 and 3 with U_mu(x - mu), and only Q - Q^+
+// counts, so
+//   l1 - l4^+ = U_mu(x) (A - B^+),  l2 - l3^+ = (C - D) U_mu(x - mu)
+// take ten products instead of twelve.
+template <bool TWO_ROW>
+__device__ inline M3 field_strength(const KGeom& g, const double2* U, const Coord& c, int lex, int p, int mu, int nu) {
+  // steps of the lexical index to the neighbours, wrapped
+  auto step = [&](int d, int dir) {
+    int stride = 1;
+    for (int k = 0; k < d; ++k) stride *= g.L[k];
+    const int x = coord_of(c, d), last = g.L[d] - 1;
+    if (dir > 0) return x == last ? -last * stride : stride;
+    return x == 0 ? last * stride : -stride;
+  };
+  const int fm = step(mu, 1), bm = step(mu, -1), fn = step(nu, 1), bn = step(nu, -1);
+  // The fence keeps the scheduler from hoisting every load to the front: all
+  // twelve links would be live at once and spill.
+#define LNK(off, par, d) load_link<TWO_ROW>(g, U, lex + (off), (par), (d))
+#define FENCE __builtin_amdgcn_sched_barrier(0)
+  const M3 Un_x = LNK(0, p, nu);
+  M3 A = m3_mul_nd(LNK(fm, 1 - p, nu), LNK(fn, 1 - p, mu));
+  FENCE;
+  A = m3_mul_nd(A, Un_x);
+  M3 B = m3_mul_dn(LNK(bn, 1 - p, nu), LNK(bn, 1 - p, mu));
+  FENCE;
+  B = m3_mul(B, LNK(fm + bn, p, nu));
+  FENCE;
+  A = m3_mul(LNK(0, p, mu), m3_sub_dag(A, B));
+  FENCE;
+  B = m3_mul_nd(Un_x, LNK(bm + fn, p, mu));
+  FENCE;
+  M3 C = m3_mul_nd(B, LNK(bm, 1 - p, nu));
+  FENCE;
+  B = m3_mul(LNK(bm + bn, p, mu), LNK(bn, 1 - p, nu));
+  FENCE;
+  B = m3_mul_dn(B, LNK(bm + bn, p, nu));
+#pragma unroll
+  for (int e = 0; e < 9; ++e) C.m[e] = csub(C.m[e], B.m[e]);
+  FENCE;
+  C = m3_mul(C, LNK(bm, 1 - p, mu));
+#undef FENCE
 #undef LNK
-  // four counter-clockwise leaves starting and ending at x
-  M3 l1 = m3_mul_nd(m3_mul_nd(m3_mul(Um_x, Un_xpm), Um_xpn), Un_x);
-  M3 l2 = m3_mul(m3_mul_nd(m3_mul_nd(Un_x, Um_xmmpn), Un_xmm), Um_xmm);
-  // Um(x-m)^+ Un(x-m-n)^+ = (Un(x-m-n) Um(x-m))^+, then * Um(x-m-n) * Un(x-n)
-  M3 l3 = m3_mul(m3_mul_dn(m3_mul(Un_xmmmn, Um_xmm), Um_xmmmn), Un_xmn);
-  M3 l4 = m3_mul_nd(m3_mul(m3_mul_dn(Un_xmn, Um_xmn), Un_xpmmn), Um_x);
   M3 F;
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
-      cd q = cadd(cadd(l1.m[3 * i + j], l2.m[3 * i + j]), cadd(l3.m[3 * i + j], l4.m[3 * i + j]));
-      cd qt = cadd(cadd(l1.m[3 * j + i], l2.m[3 * j + i]), cadd(l3.m[3 * j + i], l4.m[3 * j + i]));
+      const cd q = cadd(A.m[3 * i + j], C.m[3 * i + j]), qt = cadd(A.m[3 * j + i], C.m[3 * j + i]);
       F.m[3 * i + j] = {(q.re - qt.re) * 0.125, (q.im + qt.im) * 0.125};
     }
   const double tr_im = (F.m[0].im + F.m[4].im + F.m[8].im) / 3.0;
   F.m[0].im -= tr_im;
   F.m[4].im -= tr_im;
   F.m[8].im -= tr_im;
-  F.m[0].re = F.m[4].re = F.m[8].re = 0.0;
   return F;
+}
+
+// The nine independent reals of an anti-Hermitian 3x3 matrix: the imaginary
+// diagonal, then the entries (1,0), (2,0), (2,1).
+struct AH3 {
+  double d[3];
+  cd o[3];
+};
+// a * X + b * Y
+__device__ inline AH3 ah3_comb(double a, const AH3& x, double b, const AH3& y) {
+  AH3 r;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    r.d[i] = a * x.d[i] + b * y.d[i];
+    r.o[i] = {a * x.o[i].re + b * y.o[i].re, a * x.o[i].im + b * y.o[i].im};
+  }
+  return r;
+}
+__device__ inline cd ah3_at(const AH3& x, int i, int j) {
+  if (i == j) return {0.0, x.d[i]};
+  if (i > j) return x.o[i + j - 1];
+  const cd v = x.o[i + j - 1];
+  return {-v.re, v.im};  // -conj
 }
 
 __device__ inline cd times_i(cd a) { return {-a.im, a.re}; }
 
-// Hermitian 6x6 block from E1, E2, E3 (anti-Hermitian 3x3), full storage
-__device__ inline void make_block(const M3& E1, const M3& E2, const M3& E3, double c, double d,
-                                  cd (&B)[6][6]) {
+// Hermitian 6x6 block from E1, E2, E3 (anti-Hermitian 3x3): the lower
+// triangle is computed, the upper one is its adjoint
+__device__ inline void make_block(const AH3& E1, const AH3& E2, const AH3& E3, double c, double d, cd (&B)[6][6]) {
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
-      const cd e1 = E1.m[3 * a + b], e2 = E2.m[3 * a + b], e3 = E3.m[3 * a + b];
-      const cd ie3 = times_i(e3), ie1 = times_i(e1);
-      B[a][b] = cscale(c, ie3);
-      B[3 + a][3 + b] = cscale(-c, ie3);
-      B[a][3 + b] = cscale(c, cadd(ie1, e2));
-      B[3 + a][b] = cscale(c, csub(ie1, e2));
+      if (a >= b) {
+        const cd v = cscale(c, times_i(ah3_at(E3, a, b)));
+        B[a][b] = v;
+        B[3 + a][3 + b] = {-v.re, -v.im};
+      }
+      B[3 + a][b] = cscale(c, csub(times_i(ah3_at(E1, a, b)), ah3_at(E2, a, b)));
     }
 #pragma unroll
-  for (int i = 0; i < 6; ++i) B[i][i].re += d;
+  for (int i = 0; i < 6; ++i) {
+    B[i][i] = {B[i][i].re + d, 0.0};
+#pragma unroll
+    for (int j = i + 1; j < 6; ++j) B[i][j] = {B[j][i].re, -B[j][i].im};
+  }
 }
 
 // block B into components c0 .. c0+17 of site s of a tiled 36-component field
@@ -177,79 +224,121 @@ __device__ inline void store_packed(S* field, size_t s, int c0, const cd (&B)[6]
     for (int j = 0; j < i; ++j) st(base + tri_index(i, j) * kTile, B[i][j]);
 }
 
-__global__ __launch_bounds__(128) void k_clover(const CloverLaunch c) {
+template <bool TWO_ROW>
+__global__ __launch_bounds__(64 * kCloverPlanes, 3) void k_clover(const CloverLaunch c) {
+  __shared__ double sh[kCloverPlanes][9][kTile];
   const KGeom& g = c.g;
-  const int p = blockIdx.y;
-  const int s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= g.V2) return;
-  const Coord co = site_coord(g, s, p);
-  const int x[4] = {co.x, co.y, co.z, co.t};
-  const size_t par = (size_t)p * 36 * g.V2p;  // parity p of the clover field
-
-  // planes: 0 xy, 1 xz, 2 xt, 3 yz, 4 yt, 5 zt
-  const M3 Fxy = field_strength(g, c.U64, c.two_row != 0, x, 0, 1);
-  const M3 Fxz = field_strength(g, c.U64, c.two_row != 0, x, 0, 2);
-  const M3 Fxt = field_strength(g, c.U64, c.two_row != 0, x, 0, 3);
-  const M3 Fyz = field_strength(g, c.U64, c.two_row != 0, x, 1, 2);
-  const M3 Fyt = field_strength(g, c.U64, c.two_row != 0, x, 1, 3);
-  const M3 Fzt = field_strength(g, c.U64, c.two_row != 0, x, 2, 3);
-
+  // the two parities of a tile side by side, each XCD a contiguous range
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int p = blk & 1, l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int s = (blk >> 1) * kTile + l;
+  const Coord co = site_coord(g, s < g.V2 ? s : 0, p);
+  if (s < g.V2) {
+    const int mu = w < 3 ? 0 : (w < 5 ? 1 : 2);
+    const int nu = w < 3 ? w + 1 : (w < 5 ? w - 1 : 3);
+    const M3 F = field_strength<TWO_ROW>(g, c.U64, co, 2 * s + (co.x & 1), p, mu, nu);
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      sh[w][i][l] = F.m[4 * i].im;
+      const cd v = F.m[i == 0 ? 3 : 5 + i];  // (1,0), (2,0), (2,1)
+      sh[w][3 + 2 * i][l] = v.re;
+      sh[w][4 + 2 * i][l] = v.im;
+    }
+  }
+  __syncthreads();
+  if (w >= 2 || s >= g.V2) return;
+  const int b = w;  // chirality
+  auto plane = [&](int q) {
+    AH3 r;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      r.d[i] = sh[q][i][l];
+      r.o[i] = {sh[q][3 + 2 * i][l], sh[q][4 + 2 * i][l]};
+    }
+    return r;
+  };
   const int T = g.L[3];
   bool bnd = false;
   if (g.bc == BC_SF) bnd = (co.t == 1) || (co.t == T - 1);
   if (g.bc == BC_OPEN) bnd = (co.t == 0) || (co.t == T - 1);
   const double d = 4.0 + c.m0 + (bnd ? (c.cF - 1.0) : 0.0);
   const double cc = 0.5 * c.csw;
+  const size_t par = (size_t)p * 36 * g.V2p;  // parity p of the clover field
 
+  // E_k = sg F_{tk} - B_k with F_{tk} = -F_{kt}; planes 0 xy, 1 xz, 2 xt, 3 yz, 4 yt, 5 zt
+  const double sg = (b == 0) ? 1.0 : -1.0;
+  auto block = [&](cd(&B)[6][6]) {
+    make_block(ah3_comb(-sg, plane(2), -1.0, plane(3)), ah3_comb(-sg, plane(4), 1.0, plane(1)),
+               ah3_comb(-sg, plane(5), -1.0, plane(0)), cc, d, B);
+  };
+  // the matrix to invert: the block, or with a twisted mass (the block of
+  // chirality b is B + i sg mu) Q = B^2 + mu^2: B is Hermitian, so
+  // (B + i m)^{-1} = Q^{-1} (B - i m) for m = +-mu (and the adjoint is the same
+  // with -m); the odd sites store the Hermitian positive definite Q^{-1}, the
+  // hop kernels apply B and the i m term themselves
+  auto to_invert = [&](cd(&B)[6][6]) {
+    if (c.mu == 0.0) return;
+    cd Q[6][6];
 #pragma unroll
-  for (int b = 0; b < 2; ++b) {
-    const double sg = (b == 0) ? 1.0 : -1.0;
-    // E_k = sg F_{tk} - B_k with F_{tk} = -F_{kt}
-    M3 E1, E2, E3;
+    for (int i = 0; i < 6; ++i)
 #pragma unroll
-    for (int e = 0; e < 9; ++e) {
-      E1.m[e] = csub(cscale(-sg, Fxt.m[e]), Fyz.m[e]);
-      E2.m[e] = cadd(cscale(-sg, Fyt.m[e]), Fxz.m[e]);
-      E3.m[e] = csub(cscale(-sg, Fzt.m[e]), Fxy.m[e]);
+      for (int j = 0; j <= i; ++j) {
+        cd v = {i == j ? c.mu * c.mu : 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < 6; ++k) v = cmac(v, B[i][k], B[k][j]);
+        Q[i][j] = v;
+      }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+      B[i][i] = {Q[i][i].re, 0.0};
+#pragma unroll
+      for (int j = 0; j < i; ++j) {
+        B[i][j] = Q[i][j];
+        B[j][i] = {Q[i][j].re, -Q[i][j].im};
+      }
     }
-    cd B[6][6];
-    make_block(E1, E2, E3, cc, d, B);
-    store_packed(c.C64 + par, s, 18 * b, B);
-    if (c.C32) store_packed(c.C32 + par, s, 18 * b, B);
-    if (c.C16) store_packed(c.C16 + par, s, 18 * b, B);
-    if (p == 1 && c.mu == 0.0) {
-      cd R[6][6];
-      if (blk6::herm_inverse(B, R) == blk6::INV_SINGULAR) atomicOr(c.err_flag, 1);
-      store_packed(c.Ci64, s, 18 * b, R);
-      if (c.Ci32) store_packed(c.Ci32, s, 18 * b, R);
-      if (c.Ci16) store_packed(c.Ci16, s, 18 * b, R);
-    } else if (p == 1) {
-      // twisted mass: the block of chirality b is B + i sg mu (g5 = sg on
-      // it).  B is Hermitian, so (B + i m)^{-1} = (B^2 + mu^2)^{-1} (B - i m)
-      // for m = +-mu (and the adjoint is the same with -m): the odd sites
-      // store the Hermitian positive definite Q^{-1} = (B^2 + mu^2)^{-1}
-      // (LDL^H), the hop kernels apply B and the i m term themselves
-      cd Q[6][6], Qi[6][6];
-#pragma unroll
-      for (int i = 0; i < 6; ++i)
-#pragma unroll
-        for (int j = 0; j < 6; ++j) {
-          cd v = {i == j ? c.mu * c.mu : 0.0, 0.0};
-#pragma unroll
-          for (int k = 0; k < 6; ++k) v = cadd(v, cmul(B[i][k], B[k][j]));
-          Q[i][j] = v;
-        }
-      if (blk6::herm_inverse(Q, Qi) == blk6::INV_SINGULAR) atomicOr(c.err_flag, 1);
-      store_packed(c.Ci64, s, 18 * b, Qi);
-      if (c.Ci32) store_packed(c.Ci32, s, 18 * b, Qi);
-      if (c.Ci16) store_packed(c.Ci16, s, 18 * b, Qi);
-    }
+  };
+  cd B[6][6];
+  block(B);
+  store_packed(c.C64 + par, s, 18 * b, B);
+  if (c.C32) store_packed(c.C32 + par, s, 18 * b, B);
+  if (c.C16) store_packed(c.C16 + par, s, 18 * b, B);
+  if (p == 0) return;
+  to_invert(B);
+  const double bound = blk6::norm_inf_bound(B);
+  blk6::NormBound rb;
+  const size_t base = tix((size_t)s, 36) + 18 * b * kTile;
+  auto put = [&](int e, cd v) {
+    st(c.Ci64 + base + e * kTile, v);
+    if (c.Ci32) st(c.Ci32 + base + e * kTile, v);
+    if (c.Ci16) st(c.Ci16 + base + e * kTile, v);
+  };
+  double diag[6];
+  const bool ldl = blk6::inverse_ldl_each(B, [&](int i, int j, cd v) {
+    rb.add(i, j, v);
+    if (i != j) return put(tri_index(i, j), v);
+    diag[i] = v.re;
+    if (i & 1) put(i >> 1, cd{diag[i - 1], diag[i]});
+  });
+  if (!(ldl && blk6::accepted(bound, rb.max()))) {  // rare: the norms decide, or the pivoted route
+    cd A[6][6], R[6][6];
+    block(A);
+    to_invert(A);
+    blk6::inverse_ldl(A, R);
+    if (blk6::herm_inverse_careful(A, R, ldl) == blk6::INV_SINGULAR) atomicOr(c.err_flag, 1);
+    store_packed(c.Ci64, s, 18 * b, R);
+    if (c.Ci32) store_packed(c.Ci32, s, 18 * b, R);
+    if (c.Ci16) store_packed(c.Ci16, s, 18 * b, R);
   }
 }
 
 hipError_t launch_clover(const CloverLaunch& c, hipStream_t st) {
-  dim3 grid((c.g.V2 + 127) / 128, 2);
-  k_clover<<<grid, 128, 0, st>>>(c);
+  const unsigned grid = 2u * (unsigned)((c.g.V2 + kTile - 1) / kTile);
+  if (c.two_row)
+    k_clover<true><<<grid, 64 * kCloverPlanes, 0, st>>>(c);
+  else
+    k_clover<false><<<grid, 64 * kCloverPlanes, 0, st>>>(c);
   return hipGetLastError();
 }
 
