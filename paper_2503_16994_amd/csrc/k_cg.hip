@@ -46,10 +46,11 @@ __device__ inline double bsum(double v, double* sh) {
   return s;
 }
 
-// fixed-order sum of n partials, result broadcast to the block
+// fixed-order sum of the partials of one rhs (n as in parts_count), result
+// broadcast to the block
 __device__ inline double psum(const double* p, int n, double* sh) {
   double acc = 0.0;
-  for (int i = threadIdx.x; i < n; i += kB) acc += p[i];
+  for (int i = threadIdx.x; i < parts_count(n); i += kB) acc += parts_at(p, n, i);
   double s = bsum(acc, sh);
   __shared__ double out;
   if (threadIdx.x == 0) out = s;
@@ -97,19 +98,6 @@ __global__ void k_cg_setup(CGState* s, const double* b2, const double* eta2, CGS
   if (zero) c.rho2 = 0.0;
 }
 
-__global__ void k_cg_alpha(CGState* s, const double* partials, int nparts) {
-  __shared__ double sh[4];
-  const int r = blockIdx.x;
-  if (s[r].done) return;
-  const double v = psum(partials + (size_t)r * nparts, nparts, sh);
-  if (threadIdx.x == 0) {
-    CGState& c = s[r];
-    c.pAp = v;
-    c.alpha = (v > 0.0) ? c.rr / v : 0.0;
-    c.rr_prev = c.rr;
-  }
-}
-
 // beta and the iteration control from the new |r|^2 = v; the denominator is
 // rr_prev, the |r|^2 the alpha step of this iteration divided by (alpha sets
 // it), so the fused beta/p kernel below can replace rr while its other
@@ -144,7 +132,7 @@ __global__ void k_cg_beta(CGState* s, const double* partials, int nparts) {
   __shared__ double sh[4];
   const int r = blockIdx.x;
   if (s[r].done) return;
-  const double v = psum(partials + (size_t)r * nparts, nparts, sh);
+  const double v = psum(partials + (size_t)r * parts_stride(nparts), nparts, sh);
   if (threadIdx.x == 0) beta_step(s[r], v);
 }
 
@@ -255,7 +243,7 @@ __global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n
   const int q = blockIdx.y;
   CGState& c = cs[q];
   if (c.done) return;
-  const double v = psum(partials + (size_t)q * nparts, nparts, sh);
+  const double v = psum(partials + (size_t)q * parts_stride(nparts), nparts, sh);
   const double rr0 = c.rr_prev;
   if (blockIdx.x == 0 && threadIdx.x == 0) beta_step(c, v);
   if (!finite(v)) return;
@@ -382,7 +370,7 @@ __global__ void k_ru_finish(CGState* s, const double* part_res, int n_res, const
   const int r = blockIdx.x;
   if (ru_skip(s[r])) return;
   const double res2 = psum(part_res + (size_t)r * n_res, n_res, sh);
-  const double rr = psum(part_r + (size_t)r * n_r, n_r, sh);
+  const double rr = psum(part_r + (size_t)r * parts_stride(n_r), n_r, sh);
   if (threadIdx.x != 0) return;
   CGState& c = s[r];
   c.rupd += 1;
@@ -469,10 +457,6 @@ hipError_t launch_cg_escalate(CGState* s, int nrhs, hipStream_t st) {
 hipError_t launch_cg_setup(CGState* s, const double* b2, const double* eta2, const CGSetup& cfg,
                            hipStream_t st) {
   k_cg_setup<<<(cfg.nrhs + 63) / 64, 64, 0, st>>>(s, b2, eta2, cfg);
-  return hipGetLastError();
-}
-hipError_t launch_cg_alpha(CGState* s, const double* partials, int nparts, int nrhs, hipStream_t st) {
-  k_cg_alpha<<<nrhs, kB, 0, st>>>(s, partials, nparts);
   return hipGetLastError();
 }
 hipError_t launch_cg_beta(CGState* s, const double* partials, int nparts, int nrhs, hipStream_t st) {

@@ -103,13 +103,8 @@ __device__ inline void hop_fetch(HopOperands<NR, SG, SI>& f, const HopLaunch& a,
   }
 }
 
-template <int MU, int DIR, int NR, typename A, typename SG, typename SI>
-__device__ inline void hop_apply(cpx<A> (&acc)[NR][4][3], const HopOperands<NR, SG, SI>& f, const HopLaunch& a,
-                                 const Coord& c) {
-  bool edge;
-  A pr, pi;
-  if (!hop_phase<MU, DIR, A>(a.g, c, edge, pr, pi)) return;
-  cpx<A> U[9];
+template <int NR, typename A, typename SG, typename SI>
+__device__ inline void hop_link(cpx<A> (&U)[9], const HopOperands<NR, SG, SI>& f, const HopLaunch& a) {
 #pragma unroll
   for (int e = 0; e < 6; ++e) U[e] = widen<A>(f.u[e]);
   if (a.two_row) {
@@ -118,22 +113,39 @@ __device__ inline void hop_apply(cpx<A> (&acc)[NR][4][3], const HopOperands<NR, 
 #pragma unroll
     for (int e = 6; e < 9; ++e) U[e] = widen<A>(f.u[e]);
   }
+}
+
+// w = ph U h (forward) or ph U^+ h (backward), h the projected half spinor of y
+template <int MU, int DIR, typename A, typename SI>
+__device__ inline void hop_half(const cpx<A> (&U)[9], const SI (&y)[12], bool edge, A pr, A pi, cpx<A> (&w)[2][3]) {
+  cpx<A> psi[4][3];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = widen<A>(y[k]);
+  cpx<A> h[2][3];
+  spin_project<MU, DIR>(psi, h);
+  if (DIR > 0) su3_mul(U, h, w);
+  else su3_dag_mul(U, h, w);
+  if (edge) {
+    const cpx<A> ph = {pr, pi};
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+      for (int a2 = 0; a2 < 3; ++a2) w[q][a2] = cmul(ph, w[q][a2]);
+  }
+}
+
+template <int MU, int DIR, int NR, typename A, typename SG, typename SI>
+__device__ inline void hop_apply(cpx<A> (&acc)[NR][4][3], const HopOperands<NR, SG, SI>& f, const HopLaunch& a,
+                                 const Coord& c) {
+  bool edge;
+  A pr, pi;
+  if (!hop_phase<MU, DIR, A>(a.g, c, edge, pr, pi)) return;
+  cpx<A> U[9];
+  hop_link(U, f, a);
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    cpx<A> psi[4][3];
-#pragma unroll
-    for (int k = 0; k < 12; ++k) psi[k / 3][k % 3] = widen<A>(f.y[r][k]);
-    cpx<A> h[2][3], w[2][3];
-    spin_project<MU, DIR>(psi, h);
-    if (DIR > 0) su3_mul(U, h, w);
-    else su3_dag_mul(U, h, w);
-    if (edge) {
-      const cpx<A> ph = {pr, pi};
-#pragma unroll
-      for (int q = 0; q < 2; ++q)
-#pragma unroll
-        for (int a2 = 0; a2 < 3; ++a2) w[q][a2] = cmul(ph, w[q][a2]);
-    }
+    cpx<A> w[2][3];
+    hop_half<MU, DIR>(U, f.y[r], edge, pr, pi, w);
     spin_accumulate<MU, DIR>(acc[r], w);
   }
 }
@@ -551,9 +563,9 @@ __device__ inline void fused_alpha(const HopLaunch& a, double* sh) {
       if (a.alpha_slot >= 0 && threadIdx.x == 0) c.alpha_w[a.alpha_slot] = 0.0;
       continue;
     }
-    const double* p = a.alpha_parts + (size_t)r * a.alpha_nparts;
+    const double* p = a.alpha_parts + (size_t)r * parts_stride(a.alpha_nparts);
     double acc = 0.0;
-    for (int i = threadIdx.x; i < a.alpha_nparts; i += kHopBlock) acc += p[i];
+    for (int i = threadIdx.x; i < parts_count(a.alpha_nparts); i += kHopBlock) acc += parts_at(p, a.alpha_nparts, i);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     __syncthreads();
@@ -600,8 +612,7 @@ __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
       }
       if (a.partials) {
 #pragma unroll
-        for (int k = 0; k < NC; ++k)
-          nrm += (double)v[r][k].re * (double)v[r][k].re + (double)v[r][k].im * (double)v[r][k].im;
+        for (int k = 0; k < NC; ++k) nrm += cnorm2(v[r][k]);
       }
     }
     if (a.partials) {
@@ -657,12 +668,314 @@ __global__ __launch_bounds__(kHopBlock) void k_hop_xr(const HopLaunch a) {
         rv.re -= alpha * (AV)v[r][k].re;
         rv.im -= alpha * (AV)v[r][k].im;
         st(rb + o + k * kTile, rv);
-        nrm += (double)rv.re * (double)rv.re + (double)rv.im * (double)rv.im;
+        nrm += cnorm2(rv);
       }
     }
     const double bs = block_sum_rl<RL>(nrm, red);
     if ((int)threadIdx.x < RL)
       a.partials[(size_t)(ts.rhs_tile0 + (int)threadIdx.x * NR + r) * a.nbs + ts.sb] = bs;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Small launches: one site and rhs spread over eight waves.
+//
+// With too few sites to hide latency, the time of a launch is the length of
+// one thread's chain: eight rounds of loads and SU(3) products, then the
+// clover blocks.  Here a workgroup of eight waves owns 64 sites and one rhs:
+// wave d computes hop d alone (one round of loads) and leaves its two-spin
+// result in LDS; then each of six waves owns two output components (colour
+// w % 3 of both spins of chirality w / 3), adds the eight hops in the order of
+// the one-thread chain and applies its two rows of the clover block, whose
+// loads were issued before the hops.  Every sum is formed by the same
+// operations in the same order as in k_hop, so results agree bit for bit: a
+// launch's size never shows in them (the |out|^2 partials, per 64 sites, are
+// paired by their readers, see parts_count).  Modes are run-time uniform: the
+// launch is bound by latency, not by issue.  alpha has workgroups of its own.
+// 8^4, one rhs: 10.1 -> 5.9 us per FP64 hop, 9.5 -> 5.5 FP32, 7.6 -> 4.7 BF16.
+constexpr int kSpreadSites = 64;
+constexpr int kSpreadBlock = 512;
+
+// entry q of the reconstructed half spinor: component (chirality B, spin q)
+// of the contribution of a hop whose two-spin result is w (one colour each)
+template <int MU, int DIR, typename A>
+__device__ inline cpx<A> spread_add(cpx<A> acc, int b, int q, const cpx<A>* w, int col, int l) {
+  // upper chirality: w_q itself; lower: +-1 or +-i times w_{1-q} (x, y) or w_q (z, t)
+  const int sp = (b == 1 && MU < 2) ? 1 - q : q;
+  const cpx<A> v = w[(3 * sp + col) * kSpreadSites + l];
+  if (b == 0) return cadd(acc, v);
+  // sign of the forward hop: x: -i, -i; y: -, +; z: -i, +i; t: +, +
+  const bool neg = (DIR > 0) == (MU == 0 || (MU < 3 && q == 0));
+  if (MU == 0 || MU == 2) return neg ? csub_i(acc, v) : cadd_i(acc, v);
+  return neg ? csub(acc, v) : cadd(acc, v);
+}
+
+template <int K, typename A, typename SG, typename SI>
+__device__ inline void spread_hop(const HopLaunch& a, const SI* yb, int p, int s, const Coord& c, int rhs, cpx<A>* w,
+                                  int l) {
+  constexpr int MU = K / 2, DIR = (K & 1) ? -1 : 1;
+  bool edge;
+  A pr, pi;
+  cpx<A> v[2][3];
+  if (hop_phase<MU, DIR, A>(a.g, c, edge, pr, pi)) {
+    HopOperands<1, SG, SI> f;
+    fetch_k<K>(f, a, yb, p, s, c, rhs);
+    cpx<A> U[9];
+    hop_link(U, f, a);
+    hop_half<MU, DIR>(U, f.y[0], edge, pr, pi, v);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 6; ++e) v[e / 3][e % 3] = {(A)0, (A)0};
+  }
+#pragma unroll
+  for (int e = 0; e < 6; ++e) w[(6 * K + e) * kSpreadSites + l] = v[e / 3][e % 3];
+}
+
+// row i of a packed Hermitian 6x6 block: the six elements of row i, the
+// stored lower-triangle entry for each column and the diagonal pair
+template <typename A, typename SG>
+__device__ inline void load_row(const SG* C, int blk, int i, int s, cpx<A> (&m)[6]) {
+  const SG* c = C + tix(s, 36) + blk * 18 * kTile;
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    const int e = j == i ? (i >> 1) : (j < i ? 3 + i * (i - 1) / 2 + j : 3 + j * (j - 1) / 2 + i);
+    const auto v = ld(c + e * kTile);
+    m[j] = {(A)v.re, (A)v.im};
+  }
+}
+// that row times v, in the order of herm6_mul
+template <typename A>
+__device__ inline cpx<A> row_mul(const cpx<A> (&m)[6], int i, const cpx<A> (&v)[6]) {
+  cpx<A> acc = {(A)0, (A)0};
+#pragma unroll
+  for (int j = 0; j < 6; ++j)
+    if (j == i) {
+      const A re = m[j].re, im = m[j].im;
+      acc = cscale((i & 1) ? im : re, v[j]);
+    }
+#pragma unroll
+  for (int j = 0; j < 6; ++j) {
+    if (j < i) acc = cmac(acc, m[j], v[j]);
+    if (j > i) acc = cmacc(acc, m[j], v[j]);
+  }
+  return acc;
+}
+
+template <typename SG, typename SI, typename SO, bool XR>
+__global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) {
+  using A = typename StoreTraits<SG>::acc;
+  __shared__ cpx<A> wls[8 * 6 * kSpreadSites];  // the hops; later the site vectors of the clover products
+  __shared__ double nls[12 * kSpreadSites];  // |component|^2 of the sites
+  const KGeom& g = a.g;
+  const int l = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int nwork = a.nbs * a.nrhs;
+  if ((int)blockIdx.x >= nwork) {  // the extra workgroups: alpha of one rhs each (see HopLaunch::alpha_cg)
+    const int r = blockIdx.x - nwork;
+    CGState& c = a.alpha_cg[r];
+    if (c.done) {
+      if (a.alpha_slot >= 0 && threadIdx.x == 0) c.alpha_w[a.alpha_slot] = 0.0;
+      return;
+    }
+    const double* pp = a.alpha_parts + (size_t)r * parts_stride(a.alpha_nparts);
+    double acc = 0.0;  // as in fused_alpha: the first kHopBlock threads
+    if (w < kHopBlock / 64)
+      for (int i = threadIdx.x; i < parts_count(a.alpha_nparts); i += kHopBlock) acc += parts_at(pp, a.alpha_nparts, i);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (l == 0 && w < kHopBlock / 64) nls[w] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      double v = 0.0;
+      for (int k = 0; k < kHopBlock / 64; ++k) v += nls[k];  // waves in order
+      c.pAp = v;
+      c.alpha = (v > 0.0) ? c.rr / v : 0.0;
+      c.rr_prev = c.rr;
+      if (a.alpha_slot >= 0) c.alpha_w[a.alpha_slot] = c.alpha;
+    }
+    return;
+  }
+  const int lb = xcd_remap(blockIdx.x, nwork);  // the rhs of a site block side by side on one XCD
+  const int rhs = lb % a.nrhs, sb = lb / a.nrhs;
+  if (a.done && a.done[rhs * (int)(sizeof(CGState) / sizeof(int))] != 0) return;
+  const int p = a.both ? (sb & 1) : a.p_out;
+  const int bx = a.both ? sb >> 1 : sb, s = bx * kSpreadSites + l;  // site block of the parity, site
+  const bool active = s < g.V2;
+  const SI* yb = static_cast<const SI*>(a.y);
+  const SI* zb = static_cast<const SI*>(a.z);
+  const SG* cpre = static_cast<const SG*>(a.Cpre);
+  if (a.both) {
+    yb += (1 - p) * a.par_stride;
+    if (zb) zb += p * a.par_stride;
+    if (cpre) cpre += p * a.cpre_par;
+  }
+  const Coord c = site_coord(g, active ? s : 0, p);
+  // this wave's output components: rows col and 3 + col of chirality b
+  const int b = w / 3, col = w % 3;
+  const bool owner = w < 6;
+  const bool tm = a.tm_post != 0 || a.tm_mu != 0.0;
+  // first clover product of the launch: A z before the hops, or the first matrix after them
+  const SG* first = a.pre == PRE_CLOV ? cpre
+                    : a.post == POST_CLOV ? static_cast<const SG*>(tm ? a.Ctm : a.Cpost) : nullptr;
+  cpx<A> m0[6], m1[6], z[6];
+  if (owner && active) {
+    if (first) {
+      load_row(first, b, col, s, m0);
+      load_row(first, b, 3 + col, s, m1);
+    }
+    if (a.pre != PRE_NONE) {
+      const SI* zp = zb + (size_t)rhs * a.z_rs + tix(s, 12) + 6 * b * kTile;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        const auto t = ld(zp + i * kTile);
+        z[i] = {(A)t.re, (A)t.im};
+      }
+    }
+  }
+  if (active) {
+    switch (w) {
+      case 0: spread_hop<0, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 1: spread_hop<1, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 2: spread_hop<2, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 3: spread_hop<3, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 4: spread_hop<4, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 5: spread_hop<5, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 6: spread_hop<6, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      default: spread_hop<7, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+    }
+  }
+  __syncthreads();
+  cpx<A> v[2] = {{(A)0, (A)0}, {(A)0, (A)0}};
+  if (owner && active) {
+    const A scale = (A)a.scale;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      cpx<A> t = {(A)0, (A)0};
+      t = spread_add<0, 1>(t, b, q, wls + 0 * 6 * kSpreadSites, col, l);
+      t = spread_add<0, -1>(t, b, q, wls + 1 * 6 * kSpreadSites, col, l);
+      t = spread_add<1, 1>(t, b, q, wls + 2 * 6 * kSpreadSites, col, l);
+      t = spread_add<1, -1>(t, b, q, wls + 3 * 6 * kSpreadSites, col, l);
+      t = spread_add<2, 1>(t, b, q, wls + 4 * 6 * kSpreadSites, col, l);
+      t = spread_add<2, -1>(t, b, q, wls + 5 * 6 * kSpreadSites, col, l);
+      t = spread_add<3, 1>(t, b, q, wls + 6 * 6 * kSpreadSites, col, l);
+      t = spread_add<3, -1>(t, b, q, wls + 7 * 6 * kSpreadSites, col, l);
+      v[q] = cscale(scale, t);
+    }
+    if (a.pre != PRE_NONE) {
+      const auto pick = [col](A x, A y, A t) { return col == 0 ? x : (col == 1 ? y : t); };
+      const cpx<A> z0 = {pick(z[0].re, z[1].re, z[2].re), pick(z[0].im, z[1].im, z[2].im)};
+      const cpx<A> z1 = {pick(z[3].re, z[4].re, z[5].re), pick(z[3].im, z[4].im, z[5].im)};
+      cpx<A> o0 = z0, o1 = z1;
+      if (a.pre == PRE_CLOV) {
+        o0 = row_mul(m0, col, z);
+        o1 = row_mul(m1, 3 + col, z);
+        if (tm) {
+          const A m = (A)(b == 0 ? a.tm_mu : -a.tm_mu);
+          o0 = {o0.re - m * z0.im, o0.im + m * z0.re};
+          o1 = {o1.re - m * z1.im, o1.im + m * z1.re};
+        }
+      }
+      v[0] = cadd(v[0], o0);
+      v[1] = cadd(v[1], o1);
+    }
+  }
+  if (a.post == POST_CLOV) {  // uniform over the launch
+    // one or (twisted mass) two products; each needs the six components of the
+    // chirality, which the other waves hold
+    for (int step = tm ? 0 : 1; step < 2; ++step) {
+      __syncthreads();  // wls is free
+      if (owner) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) wls[(6 * b + 3 * q + col) * kSpreadSites + l] = v[q];
+      }
+      __syncthreads();
+      if (owner && active) {
+        cpx<A> in6[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) in6[i] = wls[(6 * b + i) * kSpreadSites + l];
+        if (a.pre == PRE_CLOV || (tm && step == 1)) {
+          const SG* C = static_cast<const SG*>(step == 0 ? a.Ctm : a.Cpost);
+          load_row(C, b, col, s, m0);
+          load_row(C, b, 3 + col, s, m1);
+        }
+        const cpx<A> o0 = row_mul(m0, col, in6), o1 = row_mul(m1, 3 + col, in6);
+        if (step == 0) {  // (A + i m)^{-1} = Q^{-1} (A - i m), m = tm_mu g5
+          const A m = (A)(b == 0 ? -a.tm_mu : a.tm_mu);
+          const cpx<A> i0 = v[0], i1 = v[1];
+          v[0] = {o0.re - m * i0.im, o0.im + m * i0.re};
+          v[1] = {o1.re - m * i1.im, o1.im + m * i1.re};
+        } else {
+          v[0] = o0;
+          v[1] = o1;
+        }
+      }
+    }
+  }
+  double n2[2] = {0.0, 0.0};
+  if (owner) {
+    const bool masked = g.bc == BC_SF && c.t == 0;
+    if (a.g5 && b == 1) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) v[q] = {-v[q].re, -v[q].im};
+    }
+    if (masked) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) v[q] = {(A)0, (A)0};
+    }
+    const size_t site = tix(s, 12) + (6 * b + col) * kTile;
+    if constexpr (XR) {
+      using AV = typename StoreTraits<SO>::acc;
+      SO* xb = static_cast<SO*>(a.xr_x);
+      SO* rb = static_cast<SO*>(a.xr_r);
+      const SI* pb = static_cast<const SI*>(a.xr_p);
+      const CGState& cs = a.cg[rhs];
+      if (active && !cs.done) {
+        const AV alpha = (AV)cs.alpha;
+        const size_t o = (size_t)rhs * a.xr_rs + site, ox = (size_t)rhs * a.xr_xrs + site;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          if (xb) {
+            const auto pv = ld(pb + o + 3 * q * kTile);
+            auto xv = ld(xb + ox + 3 * q * kTile);
+            xv.re += alpha * pv.re;
+            xv.im += alpha * pv.im;
+            st(xb + ox + 3 * q * kTile, xv);
+          }
+          auto rv = ld(rb + o + 3 * q * kTile);
+          rv.re -= alpha * (AV)v[q].re;
+          rv.im -= alpha * (AV)v[q].im;
+          st(rb + o + 3 * q * kTile, rv);
+          n2[q] = cnorm2(rv);
+        }
+      }
+    } else if (s < g.V2p) {  // padding sites (v = 0) too
+      SO* op = static_cast<SO*>(a.out) + (a.both ? p * a.par_stride : 0) + (size_t)rhs * a.out_rs + site;
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        st(op + 3 * q * kTile, v[q]);
+        n2[q] = cnorm2(v[q]);
+      }
+    }
+  }
+  if (a.partials) {
+    if (owner) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) nls[(6 * b + 3 * q + col) * kSpreadSites + l] = n2[q];
+    }
+    __syncthreads();
+    if (w == 0) {  // the sum of one wave of k_hop
+      double nrm = 0.0;
+#pragma unroll
+      for (int k = 0; k < 12; ++k) nrm += nls[k * kSpreadSites + l];
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) nrm += __shfl_xor(nrm, off, 64);
+      if (l == 0) {
+        const int per = (a.nbs / (a.both ? 2 : 1) + 1) & ~1;  // slots per parity: whole pairs
+        double* pt = a.partials + (size_t)rhs * (a.both ? 2 * per : per) + p * (a.both ? per : 0);
+        pt[bx] = nrm;
+        if (bx == a.nbs / (a.both ? 2 : 1) - 1 && (bx & 1) == 0) pt[bx + 1] = 0.0;
+      }
+    }
   }
 }
 
@@ -674,6 +987,19 @@ static bool split_on(const HopLaunch& h) { return h.dir_split && h.nr_tile == 1 
 // twisted-mass kernels exist for one rhs per thread (the launch helpers of
 // the library set nr_tile = rhs_lanes = 1 whenever mu != 0)
 static bool tm_on(const HopLaunch& h) { return h.tm_post != 0 || h.tm_mu != 0.0; }
+
+// Launches of k_hop_spread: those with too few threads in flight otherwise (a
+// site and rhs is one thread of k_hop).  Measured with k_hop against
+// k_hop_spread, us per hop: V2 x rhs = 2048: FP64 10.1 / 5.9, FP32 9.5 / 5.5,
+// BF16 7.6 / 4.7; 16384: 14.4 / 9.4, 11.5 / 6.4, 7.6 / 4.8; 31104: 15.3 / 14.4,
+// 11.4 / 8.9, 8.1 / 6.7; 32768: 16.5 / 17.3, 12.7 / 9.9, 7.8 / 6.2; 41472:
+// 18.9 / 19.4, 13.2 / 12.3, 9.1 / 8.4; 65536: 24.4 / 30.9, 15.4 / 16.6, 10.2 /
+// 11.9.  FP64 has one workgroup per CU (183 registers), FP32 and BF16 two.
+// The caller's direction split sums in another order and keeps its own kernel.
+constexpr long kSpreadMax64 = 30 * 1024, kSpreadMax32 = 44 * 1024;
+static bool spread_on(const HopLaunch& h) {
+  return h.hop && !split_on(h) && (long)h.g.V2 * h.nrhs <= (h.prec == P_F64 ? kSpreadMax64 : kSpreadMax32);
+}
 
 // Unused dynamic LDS that caps the workgroups resident per CU (160 KiB of LDS
 // per CU, plus each workgroup's small static reduction array): level 1 -> 4,
@@ -692,7 +1018,7 @@ static unsigned lds_cap_bytes(int level) {
 // 4 rhs lanes (fewest sites per workgroup), or both parities split
 int hop_max_parts(long V2) {
   const long one = (V2 + sites_per_block(4) - 1) / sites_per_block(4);
-  const long both = 2 * ((V2 + sites_per_block(1, true) - 1) / sites_per_block(1, true));
+  const long both = 2 * ((V2 + sites_per_block(1, true) - 1) / sites_per_block(1, true) + 1);  // whole pairs
   return (int)(one > both ? one : both);
 }
 
@@ -702,10 +1028,30 @@ int hop_nblocks(const HopLaunch& h) {
   return h.both ? 2 * nb : nb;
 }
 
-// per-rhs partial sums a launch of the tiled shapes writes (its site blocks)
+static int spread_nblocks(const HopLaunch& h) {
+  return (h.both ? 2 : 1) * ((h.g.V2 + kSpreadSites - 1) / kSpreadSites);
+}
+// its partial sums per rhs, as a count of half sums (see parts_count): whole
+// pairs for each parity
+static int spread_nparts(const HopLaunch& h) {
+  const int per = (h.g.V2 + kSpreadSites - 1) / kSpreadSites;
+  return -(h.both ? 2 : 1) * ((per + 1) & ~1);
+}
+
+template <typename SG, typename SI, typename SO, bool XR>
+static hipError_t launch_spread(HopLaunch h, hipStream_t st) {
+  h.nbs = spread_nblocks(h);
+  const unsigned grid = (unsigned)h.nbs * (unsigned)h.nrhs + (h.alpha_cg ? (unsigned)h.nrhs : 0u);
+  k_hop_spread<SG, SI, SO, XR><<<grid, kSpreadBlock, 0, st>>>(h);
+  return hipGetLastError();
+}
+
+// per-rhs partial sums a launch of the tiled shapes writes (its site blocks;
+// negative: halves of them, see parts_count)
 int hop_nparts(const HopLaunch& h0) {
   HopLaunch h = h0;
   if (h.prec == P_F64) h.rhs_lanes = 1;
+  if (spread_on(h)) return spread_nparts(h);
   return hop_nblocks(h);
 }
 
@@ -766,6 +1112,7 @@ template <typename SG, typename SI, typename SO, int PRE, int POST, bool HOP>
 static hipError_t launch_tiled(const HopLaunch& h0, hipStream_t st) {
   HopLaunch h = h0;
   if (std::is_same<SG, double2>::value) h.rhs_lanes = 1;
+  if (spread_on(h)) return launch_spread<SG, SI, SO, false>(h, st);
   if (!prepare(h)) return hipErrorInvalidValue;
   if constexpr (std::is_same<SG, double2>::value) {
     return launch_rl<SG, SI, SO, PRE, POST, HOP, 1>(h, st);
@@ -817,7 +1164,9 @@ template <typename SG, typename SI, typename SV>
 static hipError_t launch_xr(const HopLaunch& h0, hipStream_t st) {
   HopLaunch h = h0;
   if (std::is_same<SG, double2>::value) h.rhs_lanes = 1;
-  if (!prepare(h) || h.both || !h.partials || !h.cg) return hipErrorInvalidValue;
+  if (h.both || !h.partials || !h.cg) return hipErrorInvalidValue;
+  if (spread_on(h)) return launch_spread<SG, SI, SV, true>(h, st);
+  if (!prepare(h)) return hipErrorInvalidValue;
   if constexpr (std::is_same<SG, double2>::value) {
     return launch_xr_rl<SG, SI, SV, 1>(h, st);
   } else {
@@ -850,6 +1199,7 @@ static hipError_t launch_single(const HopLaunch& h0, hipStream_t st) {
   h.nr_tile = 1;
   h.rhs_lanes = 1;
   h.dir_split = 0;
+  if (spread_on(h)) return launch_spread<SG, SI, SO, false>(h, st);
   if (!prepare(h)) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)h.nbs * (unsigned)h.nrhs;
   if (tm_on(h))

@@ -212,7 +212,7 @@ hipError_t launch_norm2(const void* x, int prec, long n, long rs, int nrhs, doub
 // fixed-order sum of nparts partials by one block per rhs
 __device__ inline double sum_partials(const double* p, int nparts, double* sh) {
   double acc = 0.0;
-  for (int i = threadIdx.x; i < nparts; i += kVecBlock) acc += p[i];
+  for (int i = threadIdx.x; i < parts_count(nparts); i += kVecBlock) acc += parts_at(p, nparts, i);
   double s = block_sum256(acc, sh);
   __shared__ double out;
   if (threadIdx.x == 0) out = s;
@@ -223,7 +223,7 @@ __device__ inline double sum_partials(const double* p, int nparts, double* sh) {
 __global__ void k_reduce(const double* partials, int nparts, double* dst) {
   __shared__ double sh[4];
   const int r = blockIdx.x;
-  double s = sum_partials(partials + (size_t)r * nparts, nparts, sh);
+  double s = sum_partials(partials + (size_t)r * parts_stride(nparts), nparts, sh);
   if (threadIdx.x == 0) dst[r] = s;
 }
 

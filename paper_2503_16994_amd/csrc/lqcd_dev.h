@@ -190,14 +190,17 @@ template <typename A>
 __device__ inline cpx<A> cadd(cpx<A> a, cpx<A> b) { return {a.re + b.re, a.im + b.im}; }
 template <typename A>
 __device__ inline cpx<A> csub(cpx<A> a, cpx<A> b) { return {a.re - b.re, a.im - b.im}; }
+// One product rounded, the other fused into it, spelled out: left to the
+// compiler, which of the two is fused differs between kernels, and kernels that
+// share these helpers would differ in last bits.
 template <typename A>
 __device__ inline cpx<A> cmul(cpx<A> a, cpx<A> b) {
-  return {a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
+  return {fma(a.re, b.re, -(a.im * b.im)), fma(a.re, b.im, a.im * b.re)};
 }
 // conj(a) * b
 template <typename A>
 __device__ inline cpx<A> cmulc(cpx<A> a, cpx<A> b) {
-  return {a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
+  return {fma(a.re, b.re, a.im * b.im), fma(a.re, b.im, -(a.im * b.re))};
 }
 // a + i b, a - i b
 template <typename A>
@@ -225,6 +228,21 @@ __device__ inline cpx<A> cmacc(cpx<A> acc, cpx<A> a, cpx<A> b) {
   acc.im = fma(-a.im, b.re, acc.im);
   return acc;
 }
+
+// |c|^2 in FP64 (one rounding of the product, one FMA), the term that every
+// kernel adds to a sum of squared components
+template <typename A>
+__device__ inline double cnorm2(cpx<A> c) {
+  return fma((double)c.re, (double)c.re, (double)c.im * (double)c.im);
+}
+
+// Partial sums of a hop launch, one per 128 sites: a count n > 0 means n
+// values; n < 0 means -n values of 64 sites each (a small launch), of which
+// 2 i and 2 i + 1 are the two waves whose sum is value i of the former.  The
+// sums over either are the same operations.
+__host__ __device__ inline int parts_stride(int n) { return n < 0 ? -n : n; }
+__device__ inline int parts_count(int n) { return n < 0 ? -n / 2 : n; }
+__device__ inline double parts_at(const double* p, int n, int i) { return n < 0 ? p[2 * i] + p[2 * i + 1] : p[i]; }
 
 // Third row of an SU(3) matrix (row major, m[3 a + b]) from its first two.
 // For a unitary matrix of determinant one the inverse is both the adjoint

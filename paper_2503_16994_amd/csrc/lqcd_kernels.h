@@ -84,7 +84,8 @@ struct HopLaunch {
   const struct CGState* cg;
   // CG alpha fused into a hop launch that does not need it (k_hop only):
   // alpha = rr / pAp with pAp the fixed-order sum of alpha_nparts partials per
-  // rhs; rhs r is handled by workgroup r mod grid, before its stencil work.
+  // rhs; rhs r is handled by workgroup r mod grid, before its stencil work (in a
+  // small launch by a workgroup of its own).
   struct CGState* alpha_cg;   // nullptr: no alpha step
   const double* alpha_parts;  // [nrhs][alpha_nparts]
   int alpha_nparts;
@@ -93,7 +94,7 @@ struct HopLaunch {
 
 int hop_nblocks(const HopLaunch& h);
 int hop_max_parts(long V2);  // bound on partials per rhs of any hop launch
-int hop_nparts(const HopLaunch& h);  // partials per rhs of a tiled hop launch
+int hop_nparts(const HopLaunch& h);  // partials per rhs of a tiled hop launch, as parts_count takes them
 hipError_t launch_hop(const HopLaunch& h, hipStream_t st);
 hipError_t launch_hop_xr(const HopLaunch& h, hipStream_t st);
 
@@ -202,8 +203,6 @@ hipError_t launch_norm2(const void* x, int prec, long n, long rs, int nrhs, doub
 hipError_t launch_reduce(const double* partials, int nparts, int nrhs, double* dst,
                          hipStream_t st);
 hipError_t launch_cg_setup(CGState* s, const double* b2, const double* eta2, const CGSetup& cfg,
-                           hipStream_t st);
-hipError_t launch_cg_alpha(CGState* s, const double* partials, int nparts, int nrhs,
                            hipStream_t st);
 hipError_t launch_cg_beta(CGState* s, const double* partials, int nparts, int nrhs,
                           hipStream_t st);

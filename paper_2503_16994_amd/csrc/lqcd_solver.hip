@@ -193,10 +193,16 @@ HopLaunch dw_full_launch(const Ctl& c) {
 // the tuned rhs tile and direction split decide the block size)
 int full_parts(const Ctl& c) { return hop_nparts(dw_full_launch(c)); }
 
-// out (full, both parities) = [g5] Dw y, optional partials
+// out (full, both parities) = [g5] Dw y, optional partials; with alpha_cg the
+// launch also computes the CG alpha of every rhs from alpha_parts
 hipError_t dw_full(const Ctl& c, const double2* y, double2* out, bool g5, double* partials,
-                   const int* done) {
+                   const int* done, CGState* alpha_cg = nullptr, const double* alpha_parts = nullptr,
+                   int alpha_nparts = 0) {
   HopLaunch h = dw_full_launch(c);
+  h.alpha_cg = alpha_cg;
+  h.alpha_parts = alpha_parts;
+  h.alpha_nparts = alpha_nparts;
+  h.alpha_slot = -1;
   const long V2 = c.g->V2p;  // field rows per parity
   h.in_prec = h.out_prec = P_F64;
   h.par_stride = 12 * V2;
@@ -509,8 +515,8 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
       nb_r = nb_it;
     } else {
       if ((e = dw_full(c, (const double2*)pin.p, (double2*)qin.p, true, parts, done))) return e;
-      if ((e = launch_cg_alpha(cg, parts, nb_op, N, st))) return e;
-      if ((e = dw_full(dg(c), (const double2*)qin.p, (double2*)api.p, true, nullptr, done))) return e;
+      if ((e = dw_full(dg(c), (const double2*)qin.p, (double2*)api.p, true, nullptr, done, cg, parts, nb_op)))
+        return e;  // + alpha
       if ((e = launch_cg_xr(xi.p, xi.prec, xi.rs, ri.p, pi.p, api.p, ri.prec, n_vec, ri.rs, N, cg, parts,
                             st)))
         return e;

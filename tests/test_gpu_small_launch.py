@@ -1,0 +1,63 @@
+"""Small hop launches (one site spread over eight waves) against the general
+kernels, bit for bit: the library takes the small form by sites times fields,
+so the same column applied or solved alone (small) and in a batch of many
+(general) must agree exactly, partial sums included.
+
+10x6x6x10 has V/2 = 1800 sites: 28 full 64-site blocks and a ragged one, an
+odd number (the last partial has no partner).  36 fields are above the line
+in every precision, one field is below it.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2503_16994_amd import inputs, lqcd
+
+pytestmark = pytest.mark.gpu
+
+P, SF, OPEN = 0, 1, 2
+PM = lqcd.PM_F64 | lqcd.PM_F32 | lqcd.PM_BF16
+N = 36
+
+
+def system(L, bc, two_row):
+    th = (1, 1, 1, -1) if bc == P else tuple(np.exp(1j * np.array([0.3, -1.2, 2.2, 0.0])))
+    lat = lqcd.Lattice(L, bc, th)
+    U = torch.from_numpy(inputs.gauge_field(L, 0.2, seed=sum(L) + bc, bc=bc))
+    return lat, lqcd.GaugeField(lat, U, PM | (lqcd.PM_TWO_ROW if two_row else 0))
+
+
+@pytest.mark.parametrize("mu", [0.0, 0.05], ids=["mu0", "mu"])
+@pytest.mark.parametrize("prec", [lqcd.F64, lqcd.F32, lqcd.BF16], ids=["f64", "f32", "bf16"])
+@pytest.mark.parametrize("bc,two_row", [(P, True), (SF, False), (OPEN, True)], ids=["P", "SF", "OPEN"])
+def test_small_operators_equal_the_general_ones(bc, two_row, prec, mu):
+    L = (10, 6, 6, 10)
+    print(f"\n[gpu case] small launch {L} bc {bc} prec {prec} mu {mu}", flush=True)
+    lat, g = system(L, bc, two_row)
+    d = lqcd.dirac(0.123, 1.7, 1.1, mu)
+    x = torch.from_numpy(np.stack([inputs.gaussian_spinor(L, k, bc) for k in range(N)])).cuda()
+    one, many = lqcd.Workspace(lat, PM, 1), lqcd.Workspace(lat, PM, N)
+    for tune in ((1, 1, 1), (2, 0, 2), (3, 3, 4)):
+        lqcd.set_tuning(many, prec, *tune)
+        for op in range(9):  # every operator
+            batch = lqcd.dw_apply(g, d, x, op=op, prec=prec, ws=many)
+            for j in (0, 17, N - 1):
+                alone = lqcd.dw_apply(g, d, x[j:j + 1], op=op, prec=prec, ws=one)
+                assert torch.equal(alone[0], batch[j]), (tune, op, j)
+
+
+@pytest.mark.parametrize("solver,inner,mu", [(lqcd.SOLVER_CG_FULL, lqcd.F64, 0.0), (lqcd.SOLVER_CG_EO, lqcd.F64, 0.0),
+                                             (lqcd.SOLVER_CG_EO, lqcd.F64, 0.05), (lqcd.SOLVER_CG_EO, lqcd.F32, 0.0)],
+                         ids=["full", "eo", "eo-mu", "f32"])
+def test_small_solves_equal_the_general_ones(solver, inner, mu):
+    L = (10, 6, 6, 10)
+    print(f"\n[gpu case] small solve {L} solver {solver} inner {inner} mu {mu}", flush=True)
+    lat, g = system(L, P, True)
+    x = torch.from_numpy(np.stack([inputs.gaussian_spinor(L, k, P) for k in range(N)])).cuda()
+    kw = dict(tol=1e-10, solver=solver, inner_prec=inner, mu=mu)
+    batch = lqcd.solve(g, x, 0.123, 1.7, ws=lqcd.Workspace(lat, PM, N), **kw)
+    ws = lqcd.Workspace(lat, PM, 1)
+    for j in (0, N - 1):
+        alone = lqcd.solve(g, x[j:j + 1], 0.123, 1.7, ws=ws, **kw)
+        assert alone.info[0]["iters"] == batch.info[j]["iters"]
+        assert torch.equal(alone.psi[0], batch.psi[j]), j
