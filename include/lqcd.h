@@ -262,7 +262,9 @@ enum { LQCD_TUNE_NT_STORE = 1, LQCD_TUNE_CACHED_GAUGE = 2, LQCD_TUNE_OCC_SHIFT =
        LQCD_TUNE_DIR_SPLIT = 16 };
 
 /* Hop-kernel configuration used by a workspace for precision `prec`
- * (default: nr_tile 1, block_order 1, rhs_lanes 1).  A launch over n rhs uses
+ * (default: nr_tile 1, block_order 1, rhs_lanes 1, as lqcd_ws_get_tuning
+ * returns it; until a configuration is set or autotuned, launches choose
+ * theirs by lattice size, precision and rhs count).  A launch over n rhs uses
  * the largest rhs_lanes and nr_tile not above these whose product divides n.
  * EINVAL for values out of range.  None of these changes the arithmetic of
  * any rhs, except LQCD_TUNE_DIR_SPLIT: with it the eight hop terms of a site

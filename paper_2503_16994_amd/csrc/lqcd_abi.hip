@@ -384,7 +384,7 @@ static HopLaunch base_launch(const OpCtx& c, bool dag) {
   h.hop = true;
   h.tm_mu = dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
-  apply_tuning(h, c.w->tune[c.prec]);
+  apply_tuning(h, tuning_of(c.w, c.prec, c.nrhs));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
 }
@@ -625,6 +625,7 @@ extern "C" int lqcd_ws_set_tuning(lqcd_ws_t* w, int prec, const lqcd_tuning* t) 
                      LQCD_TUNE_DIR_SPLIT)))
     return fail(LQCD_EINVAL, "lqcd_ws_set_tuning: value out of range");
   w->tune[prec] = *t;
+  w->tune_set[prec] = true;
   return LQCD_OK;
 }
 
@@ -653,6 +654,8 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
   LQCD_HIP(hipEventCreate(&e0));
   LQCD_HIP(hipEventCreate(&e1));
   const lqcd_tuning saved = w->tune[prec];
+  const bool saved_set = w->tune_set[prec];
+  w->tune_set[prec] = true;  // the trials set it
   const int keep = saved.flags & LQCD_TUNE_DIR_SPLIT;  // the caller's choice
   double best_t = 1e300;
   lqcd_tuning best_cfg = saved;
@@ -716,6 +719,7 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
   (void)hipEventDestroy(e1);
   if (err != hipSuccess) {
     w->tune[prec] = saved;
+    w->tune_set[prec] = saved_set;
     return hip_status(err, "lqcd_autotune");
   }
   w->tune[prec] = best_cfg;

@@ -82,6 +82,7 @@ struct lqcd_ws {
   int clover_pmask = 0;
   std::vector<GraphEntry> graphs;
   lqcd_tuning tune[3] = {{1, 1, 1, 0}, {1, 1, 1, 0}, {1, 1, 1, 0}};  // nr, order, lanes, flags
+  bool tune_set[3] = {false, false, false};  // set by the caller or the autotuner (else: own_tuning)
 };
 
 namespace lqcd {
@@ -120,6 +121,45 @@ struct HopSpec {
   bool g5 = false;
   double scale = 0.0;
 };
+
+// Launch configuration of a workspace that nobody tuned, by sites V, storage
+// precision and rhs count n (no configuration changes a result).
+//  * Links and clover blocks: with several rhs per site they are re-read, and
+//    up to a few 10^5 sites they stay in the last-level cache from launch to
+//    launch, so ordinary loads beat non-temporal ones; one rhs of a larger
+//    lattice streams them once and keeps the non-temporal ones.
+//  * rhs per thread: one while the launch needs its threads to hide latency,
+//    two (or three for a multiple of three, or an odd n) once there are enough.
+//  * From 10^6 sites on, z-slabs per XCD.
+// Measured, us per pair of hops, non-temporal loads and one rhs per thread
+// against this choice: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
+// 4 rhs 136 / 98, 12 rhs 391 / 299, 24^3x48 12 rhs 2632 / 1707, 32^3x64 1 rhs
+// 753 / 694, 12 rhs 7936 / 4119; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
+// / 113, 32^3x64 12 rhs 4076 / 2395; BF16 32^3x64 12 rhs 1533 / 1188.
+inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
+  constexpr int kCached = LQCD_TUNE_NT_STORE | LQCD_TUNE_CACHED_GAUGE, kStream = LQCD_TUNE_NT_STORE;
+  const int64_t vn = V * n, large = 1000000;
+  lqcd_tuning t = {1, 1, 1, 0};
+  if (V >= large && n > 1) {
+    t.block_order = 2;
+    t.nr_tile = (n % 3 == 0 && prec != LQCD_BF16) || n == 3 ? 3 : 2;
+  }
+  if (prec == LQCD_BF16) {
+    if (n >= 4 && vn >= 390000) t.nr_tile = 2;
+  } else if (n < 4) {
+    const bool fits = V <= (prec == LQCD_F64 ? 250000 : large);
+    t.flags = fits ? kCached : kStream;
+    if (!fits && n > 1) t.nr_tile = n;
+  } else {
+    t.flags = kCached;
+    if (V < large && vn >= (prec == LQCD_F64 ? 1200000 : 360000)) t.nr_tile = 2;
+  }
+  return t;
+}
+// the configuration of launches over n rhs in precision prec
+inline lqcd_tuning tuning_of(const lqcd_ws* w, int prec, int n) {
+  return w->tune_set[prec] ? w->tune[prec] : own_tuning(w->g->V, prec, n);
+}
 
 // rhs tiling of a launch over nrhs fields: rhs_lanes lanes per site, each
 // with nr_tile rhs; both are reduced until their product divides nrhs

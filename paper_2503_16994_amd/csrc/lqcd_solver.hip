@@ -93,7 +93,7 @@ HopLaunch mk(const Ctl& c, int lprec) {
   h.hop = true;
   h.tm_mu = c.dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
-  apply_tuning(h, c.w->tune[lprec]);
+  apply_tuning(h, tuning_of(c.w, lprec, c.nrhs));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
 }
@@ -545,11 +545,12 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   auto run_chunk = [&](const int len) -> int {
     if (use_graph) {
       const int key_prec = lo ? ip : LQCD_F64;
+      const lqcd_tuning tn = tuning_of(w, key_prec, N), t64 = tuning_of(w, P_F64, N), t32 = tuning_of(w, P_F32, N);
       hipGraphExec_t exec = nullptr;
       for (auto& e : w->graphs)
         if (e.gauge_uid == u->uid && e.solver == prm->solver && e.inner_prec == key_prec && e.nrhs == N &&
-            e.chunk == len && e.mu == c.mu && same_tuning(e.tune_inner, w->tune[key_prec]) &&
-            same_tuning(e.tune_f64, w->tune[P_F64]) && same_tuning(e.tune_f32, w->tune[P_F32]))
+            e.chunk == len && e.mu == c.mu && same_tuning(e.tune_inner, tn) && same_tuning(e.tune_f64, t64) &&
+            same_tuning(e.tune_f32, t32))
           exec = e.exec;
       if (!exec) {
         LQCD_HIP(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
@@ -567,8 +568,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
           (void)hipGraphDestroy(gr);
           return hip_status(e3, "hipGraphInstantiate");
         }
-        w->graphs.push_back(GraphEntry{u->uid, prm->solver, key_prec, N, len, c.mu, w->tune[key_prec],
-                                       w->tune[P_F64], w->tune[P_F32], gr, exec});
+        w->graphs.push_back(GraphEntry{u->uid, prm->solver, key_prec, N, len, c.mu, tn, t64, t32, gr, exec});
       }
       LQCD_HIP(hipGraphLaunch(exec, st));
       return LQCD_OK;
