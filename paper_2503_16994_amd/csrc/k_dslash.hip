@@ -79,11 +79,10 @@ __device__ inline bool hop_phase(const KGeom& g, const Coord& c, bool& edge, A& 
   return !(pr == (A)0 && pi == (A)0);
 }
 
+// the link of a hop (neighbour index sn)
 template <int MU, int DIR, int NR, typename SG, typename SI>
-__device__ inline void hop_fetch(HopOperands<NR, SG, SI>& f, const HopLaunch& a, const SI* yb, int p, int s,
-                                 const Coord& c, int rhs0) {
+__device__ inline void link_fetch(HopOperands<NR, SG, SI>& f, const HopLaunch& a, int p, int s, int sn) {
   const KGeom& g = a.g;
-  const int sn = nb_index(g, s, c, MU, DIR);
   const int ne = a.two_row ? 6 : 9;                // stored complex per link
   const size_t par = (size_t)4 * ne * g.V2p;      // one parity of the link field
   const SG* Ub = static_cast<const SG*>(a.U);
@@ -95,6 +94,13 @@ __device__ inline void hop_fetch(HopOperands<NR, SG, SI>& f, const HopLaunch& a,
 #pragma unroll
     for (int e = 6; e < 9; ++e) f.u[e] = a.cached_gauge ? raw_ld(up + e * kTile) : raw_ld_nt(up + e * kTile);
   }
+}
+
+template <int MU, int DIR, int NR, typename SG, typename SI>
+__device__ inline void hop_fetch(HopOperands<NR, SG, SI>& f, const HopLaunch& a, const SI* yb, int p, int s,
+                                 const Coord& c, int rhs0) {
+  const int sn = nb_index(a.g, s, c, MU, DIR);
+  link_fetch<MU, DIR>(f, a, p, s, sn);
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const SI* yp = yb + (size_t)(rhs0 + r) * a.y_rs + tix(sn, 12);
@@ -583,8 +589,48 @@ __device__ inline void fused_alpha(const HopLaunch& a, double* sh) {
   __syncthreads();
 }
 
-template <typename SG, typename SI, typename SO, int PRE, int POST, bool HOP, int NR, int RL, bool SPLIT, bool TM>
+// Canonical output of k_hop (FP64): the NC components of each of a wave's 64
+// sites pass through LDS (a pitch of NC + 1 complex keeps the 16-byte accesses
+// free of bank conflicts) and leave as contiguous runs of NC 16-byte words per
+// site, instead of an internal vector that a second pass reads back: Dw at
+// 32^3x64 from canonical to canonical 1028 -> 863 us, of 12 fields on 16^3x32 525
+// -> 407 us.
+template <int NC>
+__device__ inline void canon_store(const HopLaunch& a, const cpx<double> (&v)[12], int p, int s, int rhs, int c0,
+                                   double2* sh) {
+  const KGeom& g = a.g;
+  const int l = threadIdx.x & 63;
+  double2* w = sh + (threadIdx.x >> 6) * 64 * (NC + 1);
+#pragma unroll
+  for (int k = 0; k < NC; ++k) w[l * (NC + 1) + k] = make_double2(v[k].re, v[k].im);
+  const Coord c = site_coord(g, s < g.V2 ? s : 0, p);
+  // this lane's site as an offset into the rhs's field (-1: padding)
+  const int own = s < g.V2 ? 2 * s + (c.x & 1) : -1;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  double2* base = a.cout + (size_t)rhs * 24 * g.V2;
+#pragma unroll
+  for (int i = 0; i < NC; ++i) {
+    const int idx = i * 64 + l, site = idx / NC, k = idx % NC;
+    const int lex = __shfl(own, site, 64);
+    if (lex < 0) continue;
+    const double2 t = w[site * (NC + 1) + k];
+    const nt_d2 tv = {t.x, t.y}, zero = {0.0, 0.0};
+    __builtin_nontemporal_store(tv, reinterpret_cast<nt_d2*>(base + (size_t)lex * 12 + c0 + k));
+    if (a.cout_zero)
+      __builtin_nontemporal_store(zero, reinterpret_cast<nt_d2*>(base + (size_t)(lex ^ 1) * 12 + c0 + k));
+  }
+  // the next rhs overwrites the LDS
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+static unsigned canon_lds(bool split) { return (kHopBlock / 64) * 64 * (split ? 7 : 13) * (unsigned)sizeof(double2); }
+
+template <typename SG, typename SI, typename SO, int PRE, int POST, bool HOP, int NR, int RL, bool SPLIT, bool TM,
+          bool CANON = false>
 __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
+  static_assert(!CANON || (RL == 1 && std::is_same<SO, double2>::value), "canonical output: FP64, one lane per site");
   using A = typename StoreTraits<SG>::acc;
   constexpr int NC = SPLIT ? 6 : 12;  // output components per thread
   __shared__ double red[(kHopBlock / 64) * RL > 4 ? (kHopBlock / 64) * RL : 4];
@@ -593,6 +639,12 @@ __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
   ThreadSite ts;
   cpx<A> v[NR][12];
   if (!hop_thread<SG, SI, PRE, POST, HOP, NR, RL, SPLIT, TM>(a, ts, v, xch)) return;
+  if constexpr (CANON) {
+    extern __shared__ double2 canon_sh[];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) canon_store<NC>(a, v[r], ts.p, ts.s, ts.rhs0 + r, ts.c0, canon_sh);
+    return;
+  }
   SO* ob = static_cast<SO*>(a.out);
   if (a.both) ob += ts.p * a.par_stride;
   // padding sites of the last tile (inactive, v = 0) are written too, so
@@ -710,7 +762,18 @@ __device__ inline cpx<A> spread_add(cpx<A> acc, int b, int q, const cpx<A>* w, i
   return neg ? csub(acc, v) : cadd(acc, v);
 }
 
-template <int K, typename A, typename SG, typename SI>
+// component k of a canonical field's site, rounded to the storage type of an
+// internal vector (as the layout conversion rounds it)
+template <typename SI>
+__device__ inline SI canon_ld(const double2* site, int k, bool g5) {
+  double2 v = site[k];
+  if (g5 && k >= 6) v = make_double2(-v.x, -v.y);
+  SI t;
+  st(&t, cpx<double>{v.x, v.y});
+  return t;
+}
+
+template <int K, bool CANON, typename A, typename SG, typename SI>
 __device__ inline void spread_hop(const HopLaunch& a, const SI* yb, int p, int s, const Coord& c, int rhs, cpx<A>* w,
                                   int l) {
   constexpr int MU = K / 2, DIR = (K & 1) ? -1 : 1;
@@ -719,7 +782,18 @@ __device__ inline void spread_hop(const HopLaunch& a, const SI* yb, int p, int s
   cpx<A> v[2][3];
   if (hop_phase<MU, DIR, A>(a.g, c, edge, pr, pi)) {
     HopOperands<1, SG, SI> f;
-    fetch_k<K>(f, a, yb, p, s, c, rhs);
+    bool internal = true;
+    if constexpr (CANON) {
+      if (a.cy) {  // uniform over the launch
+        internal = false;
+        const int sn = nb_index(a.g, s, c, MU, DIR);
+        link_fetch<MU, DIR>(f, a, p, s, sn);
+        const double2* yp = a.cy + ((size_t)rhs * 2 * a.g.V2 + 2 * sn + ((c.x + (MU == 0 ? 1 : 0)) & 1)) * 12;
+#pragma unroll
+        for (int k = 0; k < 12; ++k) f.y[0][k] = canon_ld<SI>(yp, k, a.g5_in);
+      }
+    }
+    if (internal) fetch_k<K>(f, a, yb, p, s, c, rhs);
     cpx<A> U[9];
     hop_link(U, f, a);
     hop_half<MU, DIR>(U, f.y[0], edge, pr, pi, v);
@@ -761,10 +835,12 @@ __device__ inline cpx<A> row_mul(const cpx<A> (&m)[6], int i, const cpx<A> (&v)[
   return acc;
 }
 
-template <typename SG, typename SI, typename SO, bool XR>
+// CANON: input and output may be canonical fields (HopLaunch::cy, cz, cout),
+// which saves a small operator application its two layout conversions.
+template <typename SG, typename SI, typename SO, bool XR, bool CANON>
 __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) {
   using A = typename StoreTraits<SG>::acc;
-  __shared__ cpx<A> wls[8 * 6 * kSpreadSites];  // the hops; later the site vectors of the clover products
+  __shared__ __attribute__((aligned(16))) cpx<A> wls[8 * 6 * kSpreadSites];  // the hops; later the site vectors
   __shared__ double nls[12 * kSpreadSites];  // |component|^2 of the sites
   const KGeom& g = a.g;
   const int l = threadIdx.x & 63;
@@ -824,24 +900,40 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
       load_row(first, b, 3 + col, s, m1);
     }
     if (a.pre != PRE_NONE) {
-      const SI* zp = zb + (size_t)rhs * a.z_rs + tix(s, 12) + 6 * b * kTile;
+      bool internal = true;
+      if constexpr (CANON) {
+        if (a.cz) {
+          internal = false;
+          const double2* zp = a.cz + ((size_t)rhs * 2 * g.V2 + 2 * s + (c.x & 1)) * 12 + 6 * b;
+          const bool neg = a.g5_in && b == 1;
 #pragma unroll
-      for (int i = 0; i < 6; ++i) {
-        const auto t = ld(zp + i * kTile);
-        z[i] = {(A)t.re, (A)t.im};
+          for (int i = 0; i < 6; ++i) {
+            const SI t = canon_ld<SI>(zp, i, false);
+            z[i] = widen<A>(t);
+            if (neg) z[i] = {-z[i].re, -z[i].im};
+          }
+        }
+      }
+      if (internal) {
+        const SI* zp = zb + (size_t)rhs * a.z_rs + tix(s, 12) + 6 * b * kTile;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+          const auto t = ld(zp + i * kTile);
+          z[i] = {(A)t.re, (A)t.im};
+        }
       }
     }
   }
   if (active) {
     switch (w) {
-      case 0: spread_hop<0, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 1: spread_hop<1, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 2: spread_hop<2, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 3: spread_hop<3, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 4: spread_hop<4, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 5: spread_hop<5, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 6: spread_hop<6, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      default: spread_hop<7, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 0: spread_hop<0, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 1: spread_hop<1, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 2: spread_hop<2, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 3: spread_hop<3, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 4: spread_hop<4, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 5: spread_hop<5, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 6: spread_hop<6, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      default: spread_hop<7, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
     }
   }
   __syncthreads();
@@ -948,6 +1040,8 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
           n2[q] = cnorm2(rv);
         }
       }
+    } else if (CANON && a.cout) {
+      // through LDS below
     } else if (s < g.V2p) {  // padding sites (v = 0) too
       SO* op = static_cast<SO*>(a.out) + (a.both ? p * a.par_stride : 0) + (size_t)rhs * a.out_rs + site;
 #pragma unroll
@@ -955,6 +1049,34 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
         st(op + 3 * q * kTile, v[q]);
         n2[q] = cnorm2(v[q]);
       }
+    }
+  }
+  if constexpr (CANON) {
+    if (a.cout) {
+      // lane-per-site components to contiguous runs of 12 words per site; the
+      // value is what the output storage type holds
+      __syncthreads();
+      static_assert(13 * kSpreadSites * sizeof(double2) <= sizeof(wls), "output staging");
+      double2* sh = reinterpret_cast<double2*>(wls);
+      if (owner) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          SO t;
+          st(&t, v[q]);
+          const auto r = ld(&t);
+          sh[l * 13 + 6 * b + 3 * q + col] = make_double2((double)r.re, (double)r.im);
+        }
+      }
+      __syncthreads();
+      double2* base = a.cout + (size_t)rhs * 24 * g.V2;
+      for (int idx = threadIdx.x; idx < 12 * kSpreadSites; idx += kSpreadBlock) {
+        const int site = idx / 12, k = idx % 12, so = bx * kSpreadSites + site;
+        if (so >= g.V2) break;
+        const int lex = 2 * so + (site_coord(g, so, p).x & 1);
+        base[(size_t)lex * 12 + k] = sh[site * 13 + k];
+        if (a.cout_zero) base[(size_t)(lex ^ 1) * 12 + k] = make_double2(0.0, 0.0);
+      }
+      return;
     }
   }
   if (a.partials) {
@@ -990,15 +1112,17 @@ static bool tm_on(const HopLaunch& h) { return h.tm_post != 0 || h.tm_mu != 0.0;
 
 // Launches of k_hop_spread: those with too few threads in flight otherwise (a
 // site and rhs is one thread of k_hop).  Measured with k_hop against
-// k_hop_spread, us per hop: V2 x rhs = 2048: FP64 10.1 / 5.9, FP32 9.5 / 5.5,
+// k_hop_spread, us per hop: output sites x rhs = 2048: FP64 10.1 / 5.9, FP32 9.5 / 5.5,
 // BF16 7.6 / 4.7; 16384: 14.4 / 9.4, 11.5 / 6.4, 7.6 / 4.8; 31104: 15.3 / 14.4,
 // 11.4 / 8.9, 8.1 / 6.7; 32768: 16.5 / 17.3, 12.7 / 9.9, 7.8 / 6.2; 41472:
 // 18.9 / 19.4, 13.2 / 12.3, 9.1 / 8.4; 65536: 24.4 / 30.9, 15.4 / 16.6, 10.2 /
 // 11.9.  FP64 has one workgroup per CU (183 registers), FP32 and BF16 two.
 // The caller's direction split sums in another order and keeps its own kernel.
 constexpr long kSpreadMax64 = 30 * 1024, kSpreadMax32 = 44 * 1024;
+// output sites times rhs of a launch
+static long launch_sites(const HopLaunch& h) { return (h.both ? 2L : 1L) * h.g.V2 * h.nrhs; }
 static bool spread_on(const HopLaunch& h) {
-  return h.hop && !split_on(h) && (long)h.g.V2 * h.nrhs <= (h.prec == P_F64 ? kSpreadMax64 : kSpreadMax32);
+  return h.hop && !split_on(h) && launch_sites(h) <= (h.prec == P_F64 ? kSpreadMax64 : kSpreadMax32);
 }
 
 // Unused dynamic LDS that caps the workgroups resident per CU (160 KiB of LDS
@@ -1038,11 +1162,29 @@ static int spread_nparts(const HopLaunch& h) {
   return -(h.both ? 2 : 1) * ((per + 1) & ~1);
 }
 
+// Canonical input is read site by site (192 contiguous bytes per lane, no
+// coalescing over lanes), which pays while the launch is one round of a
+// workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
+// conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
+// 33.2.
+bool hop_reads_canonical(const HopLaunch& h0) {
+  HopLaunch h = h0;
+  if (h.prec == P_F64) h.rhs_lanes = 1;
+  return spread_on(h) && launch_sites(h) <= 256 * kSpreadSites;
+}
+
 template <typename SG, typename SI, typename SO, bool XR>
 static hipError_t launch_spread(HopLaunch h, hipStream_t st) {
   h.nbs = spread_nblocks(h);
   const unsigned grid = (unsigned)h.nbs * (unsigned)h.nrhs + (h.alpha_cg ? (unsigned)h.nrhs : 0u);
-  k_hop_spread<SG, SI, SO, XR><<<grid, kSpreadBlock, 0, st>>>(h);
+  if constexpr (!XR && std::is_same<SI, SO>::value) {
+    if (h.cy || h.cz || h.cout) {
+      k_hop_spread<SG, SI, SO, false, true><<<grid, kSpreadBlock, 0, st>>>(h);
+      return hipGetLastError();
+    }
+  }
+  if (h.cy || h.cz || h.cout) return hipErrorInvalidValue;
+  k_hop_spread<SG, SI, SO, XR, false><<<grid, kSpreadBlock, 0, st>>>(h);
   return hipGetLastError();
 }
 
@@ -1071,6 +1213,27 @@ static bool prepare(HopLaunch& h) {
   if (h.order == 4 && !slab_ok) h.order = 3;
   if (h.order < 0 || h.order > 6) h.order = 1;
   return true;
+}
+
+// canonical output (HopLaunch::cout), FP64
+template <bool SPLIT, bool TM, int NR>
+static hipError_t launch_canon(const HopLaunch& h, hipStream_t st) {
+  const unsigned grid = (unsigned)h.nbs * (unsigned)(h.nrhs / NR), lds = canon_lds(SPLIT);
+  k_hop<double2, double2, double2, PRE_CLOV, POST_NONE, true, NR, 1, SPLIT, TM, true>
+      <<<grid, kHopBlock, lds > h.lds_cap ? lds : h.lds_cap, st>>>(h);
+  return hipGetLastError();
+}
+static hipError_t launch_canon(const HopLaunch& h, hipStream_t st) {
+  if (tm_on(h)) {
+    if (h.nr_tile != 1) return hipErrorInvalidValue;
+    return split_on(h) ? launch_canon<true, true, 1>(h, st) : launch_canon<false, true, 1>(h, st);
+  }
+  switch (h.nr_tile) {
+    case 1: return split_on(h) ? launch_canon<true, false, 1>(h, st) : launch_canon<false, false, 1>(h, st);
+    case 2: return launch_canon<false, false, 2>(h, st);
+    case 3: return launch_canon<false, false, 3>(h, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 template <typename SG, typename SI, typename SO, int PRE, int POST, bool HOP, int RL>
@@ -1114,6 +1277,12 @@ static hipError_t launch_tiled(const HopLaunch& h0, hipStream_t st) {
   if (std::is_same<SG, double2>::value) h.rhs_lanes = 1;
   if (spread_on(h)) return launch_spread<SG, SI, SO, false>(h, st);
   if (!prepare(h)) return hipErrorInvalidValue;
+  if (h.cy || h.cz) return hipErrorInvalidValue;  // the small form only
+  if (h.cout) {
+    if constexpr (std::is_same<SG, double2>::value && PRE == PRE_CLOV && POST == POST_NONE)
+      return h.partials ? hipErrorInvalidValue : launch_canon(h, st);
+    return hipErrorInvalidValue;
+  }
   if constexpr (std::is_same<SG, double2>::value) {
     return launch_rl<SG, SI, SO, PRE, POST, HOP, 1>(h, st);
   } else {

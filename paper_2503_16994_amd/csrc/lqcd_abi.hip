@@ -397,9 +397,18 @@ static char* elem_ptr(void* base, int prec, long elems) {
   return (char*)base + (size_t)elems * elem_bytes(prec);
 }
 
-// out (full) = Dw y on both parities, optional g5 on the output and partials
-static hipError_t apply_dw_full(const OpCtx& c, const void* y, void* out, bool g5, double* partials,
-                                bool dag = false) {
+// Canonical fields in place of internal vectors (all null: internal): `in`
+// for the operands that an operator takes from its argument, `out` for its
+// result (the sites of the other parity zeroed by one-parity operators).
+struct CanonIO {
+  const double2* in = nullptr;
+  double2* out = nullptr;
+  bool g5 = false;  // g5 on the input
+};
+
+// out (full) = Dw y on both parities, optional g5 on the output
+static hipError_t apply_dw_full(const OpCtx& c, const void* y, void* out, bool g5, bool dag = false,
+                                const CanonIO& io = {}) {
   const lqcd_geom_t* g = c.w->g;
   HopLaunch h = base_launch(c, dag);
   h.both = true;
@@ -414,12 +423,15 @@ static hipError_t apply_dw_full(const OpCtx& c, const void* y, void* out, bool g
   h.post = POST_NONE;
   h.scale = -0.5;
   h.g5 = g5;
-  h.partials = partials;
+  h.cy = h.cz = io.in;
+  h.cout = io.out;
+  h.g5_in = io.g5;
   return launch_hop(h, c.st);
 }
 
 // t_o = A_oo^{-1} D_oe y_e (tmp odd part of `t` full vector)
-static hipError_t apply_hop_eo(const OpCtx& c, const void* y_full, void* t_full, bool dag = false) {
+static hipError_t apply_hop_eo(const OpCtx& c, const void* y_full, void* t_full, bool dag = false,
+                               const CanonIO& io = {}) {
   const lqcd_geom_t* g = c.w->g;
   HopLaunch h = base_launch(c, dag);
   h.p_out = 1;
@@ -431,16 +443,21 @@ static hipError_t apply_hop_eo(const OpCtx& c, const void* y_full, void* t_full,
   h.pre = PRE_NONE;
   h.post = POST_CLOV;
   h.scale = -0.5;
+  h.cy = io.in;
+  h.cout = io.out;
+  h.cout_zero = true;
+  h.g5_in = io.g5;
   return launch_hop(h, c.st);
 }
 
-// out_e = A_ee z_e + 1/2 H t_o  (= Dhat z when t = A_oo^{-1} D_oe z)
+// out_e = A_ee z_e + 1/2 H t_o  (= Dhat z when t = A_oo^{-1} D_oe z); t_full
+// null: t is taken from the canonical input too
 static hipError_t apply_hop_oe(const OpCtx& c, const void* z_full, const void* t_full, void* out_full,
-                               bool g5, double* partials, bool dag = false) {
+                               bool g5, bool dag = false, const CanonIO& io = {}) {
   const lqcd_geom_t* g = c.w->g;
   HopLaunch h = base_launch(c, dag);
   h.p_out = 0;
-  h.y = elem_ptr((void*)t_full, c.prec, par_off(g));
+  h.y = t_full ? elem_ptr((void*)t_full, c.prec, par_off(g)) : nullptr;
   h.z = z_full;
   h.out = out_full;
   h.y_rs = h.z_rs = h.out_rs = full_rs(g);
@@ -449,7 +466,11 @@ static hipError_t apply_hop_oe(const OpCtx& c, const void* z_full, const void* t
   h.post = POST_NONE;
   h.scale = 0.5;
   h.g5 = g5;
-  h.partials = partials;
+  h.cz = io.in;
+  h.cy = t_full ? nullptr : io.in;
+  h.cout = io.out;
+  h.cout_zero = true;
+  h.g5_in = io.g5;
   return launch_hop(h, c.st);
 }
 
@@ -473,69 +494,71 @@ extern "C" int lqcd_dw_apply(const lqcd_gauge_t* u, const lqcd_dirac* d, int op,
 
   const lqcd_geom_t* g = w->g;
   OpCtx c{u, w, prec, nrhs, st, d->mu};
-  // internal-layout operands: caller's memory or workspace FP64 slots reused
-  // as storage of any precision (they are the widest)
-  const void* vin = in;
-  void* vout = out;
+  // Internal-layout operands: the caller's memory, or for canonical fields the
+  // workspace's FP64 slots used as storage of any precision (they are the
+  // widest).  Canonical fields skip the conversions where the hop kernels take
+  // them: a small launch reads and writes them itself, and the FP64 hops that
+  // end an operator write them (at 32^3x64 that saves the conversion's second
+  // pass over the result, 805 MB).
   const bool canon = (layout == LQCD_LAYOUT_CANON);
   const bool g5in = (op == LQCD_OP_DW_DAG || op == LQCD_OP_SCHUR_DAG);
+  const bool dag = g5in;
+  HopLaunch shape = base_launch(c, false);
+  shape.both = op <= LQCD_OP_DWDAGDW;
+  const bool small = canon && hop_reads_canonical(shape);
+  const bool write = canon && (small || (prec == P_F64 && op != LQCD_OP_HOP_EO));
+  const size_t full_bytes = (size_t)nrhs * 24 * g->V2p * elem_bytes(prec);
+  void* tmp = w->m.R;  // scratch full vectors
+  void* tmp2 = w->m.P;
+  const void* vin = in;
+  void* vout = out;
+  CanonIO io_in, io_out, io_both;  // canonical operands of an operator's first, last and only launch
   if (canon) {
     vin = w->m.X;
     vout = w->m.TMP;
-    LQCD_HIP(launch_pack(g->kg, (const double2*)in, (void*)vin, prec, nrhs, g5in, st));
+    if (small) {
+      io_in.in = io_both.in = (const double2*)in;
+      io_in.g5 = io_both.g5 = g5in;
+    } else {
+      LQCD_HIP(launch_pack(g->kg, (const double2*)in, (void*)vin, prec, nrhs, g5in, st));
+    }
+    if (write) io_out.out = io_both.out = (double2*)out;
+    // one-parity operators leave the other sites of a canonical result zero
+    else if (op >= LQCD_OP_SCHUR) LQCD_HIP(launch_fill_zero(vout, full_bytes, st));
+  } else if (g5in) {  // g5 on the input of an internal vector: copy with g5
+    LQCD_HIP(hipMemcpyAsync(tmp2, vin, full_bytes, hipMemcpyDeviceToDevice, st));
+    LQCD_HIP(launch_g5(tmp2, prec, g->V2p, 12L * g->V2p, 2 * nrhs, st));
+    vin = tmp2;
   }
-  const size_t full_bytes = (size_t)nrhs * 24 * g->V2p * elem_bytes(prec);
-  void* tmp = w->m.R;  // scratch full vector
-  void* tmp2 = w->m.P;
   switch (op) {
     case LQCD_OP_DW:
     case LQCD_OP_G5DW:
-      LQCD_HIP(apply_dw_full(c, vin, vout, op == LQCD_OP_G5DW, nullptr));
-      break;
     case LQCD_OP_DW_DAG:
-      if (!canon) {  // g5 on the input of an internal vector: copy with g5
-        LQCD_HIP(hipMemcpyAsync(tmp2, vin, full_bytes, hipMemcpyDeviceToDevice, st));
-        LQCD_HIP(launch_g5(tmp2, prec, g->V2p, 12L * g->V2p, 2 * nrhs, st));
-        vin = tmp2;
-      }
-      LQCD_HIP(apply_dw_full(c, vin, vout, true, nullptr, true));
+      LQCD_HIP(apply_dw_full(c, vin, vout, op != LQCD_OP_DW, dag, io_both));
       break;
     case LQCD_OP_DWDAGDW:  // g5 D(-mu) g5 D(mu)
-      LQCD_HIP(apply_dw_full(c, vin, tmp, true, nullptr));
-      LQCD_HIP(apply_dw_full(c, tmp, vout, true, nullptr, true));
+      LQCD_HIP(apply_dw_full(c, vin, tmp, true, false, io_in));
+      LQCD_HIP(apply_dw_full(c, tmp, vout, true, true, io_out));
       break;
     case LQCD_OP_SCHUR:
-    case LQCD_OP_SCHUR_DAG:
-      if (op == LQCD_OP_SCHUR_DAG && !canon) {
-        LQCD_HIP(hipMemcpyAsync(tmp2, vin, full_bytes, hipMemcpyDeviceToDevice, st));
-        LQCD_HIP(launch_g5(tmp2, prec, g->V2p, 12L * g->V2p, 2 * nrhs, st));
-        vin = tmp2;
-      }
-      if (canon) LQCD_HIP(launch_fill_zero(vout, full_bytes, st));
-      {
-        const bool dag = (op == LQCD_OP_SCHUR_DAG);  // g5 Dhat(-mu) g5
-        LQCD_HIP(apply_hop_eo(c, vin, tmp, dag));
-        LQCD_HIP(apply_hop_oe(c, vin, tmp, vout, dag, nullptr, dag));
-      }
+    case LQCD_OP_SCHUR_DAG:  // g5 Dhat(-mu) g5
+      LQCD_HIP(apply_hop_eo(c, vin, tmp, dag, io_in));
+      LQCD_HIP(apply_hop_oe(c, vin, tmp, vout, dag, dag, io_both));
       break;
     case LQCD_OP_SCHUR_NORMAL:  // g5 Dhat(-mu) g5 Dhat(mu)
-      if (canon) LQCD_HIP(launch_fill_zero(vout, full_bytes, st));
-      LQCD_HIP(apply_hop_eo(c, vin, tmp));
-      LQCD_HIP(apply_hop_oe(c, vin, tmp, tmp2, true, nullptr));
+      LQCD_HIP(apply_hop_eo(c, vin, tmp, false, io_in));
+      LQCD_HIP(apply_hop_oe(c, vin, tmp, tmp2, true, false, io_in));
       LQCD_HIP(apply_hop_eo(c, tmp2, tmp, true));
-      LQCD_HIP(apply_hop_oe(c, tmp2, tmp, vout, true, nullptr, true));
+      LQCD_HIP(apply_hop_oe(c, tmp2, tmp, vout, true, true, io_out));
       break;
     case LQCD_OP_HOP_EO:
-      if (canon) LQCD_HIP(launch_fill_zero(vout, full_bytes, st));
-      LQCD_HIP(apply_hop_eo(c, vin, vout));
+      LQCD_HIP(apply_hop_eo(c, vin, vout, false, io_both));
       break;
-    case LQCD_OP_HOP_OE: {
-      if (canon) LQCD_HIP(launch_fill_zero(vout, full_bytes, st));
-      LQCD_HIP(apply_hop_oe(c, vin, vin, vout, false, nullptr));
+    case LQCD_OP_HOP_OE:
+      LQCD_HIP(apply_hop_oe(c, vin, small ? nullptr : vin, vout, false, false, io_both));
       break;
-    }
   }
-  if (canon) LQCD_HIP(launch_unpack(g->kg, vout, prec, (double2*)out, nrhs, st));
+  if (canon && !write) LQCD_HIP(launch_unpack(g->kg, vout, prec, (double2*)out, nrhs, st));
   return LQCD_OK;
 }
 
@@ -668,7 +691,7 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
   auto trial = [&]() {
     auto once = [&]() -> hipError_t {
       hipError_t e = apply_hop_eo(c, w->m.X, w->m.R);
-      if (e == hipSuccess) e = apply_hop_oe(c, w->m.X, w->m.R, w->m.TMP, false, nullptr);
+      if (e == hipSuccess) e = apply_hop_oe(c, w->m.X, w->m.R, w->m.TMP, false);
       return e;
     };
     for (int i = 0; i < 2 && err == hipSuccess; ++i) err = once();

@@ -82,6 +82,14 @@ struct HopLaunch {
   long xr_rs;    // rhs stride of r and p
   long xr_xrs;   // rhs stride of x
   const struct CGState* cg;
+  // Canonical complex128 fields [rhs][lex][12] in place of internal vectors.
+  // cy, cz (hop_reads_canonical only): the input y, z, g5 applied to both if
+  // g5_in; cout (FP64, PRE_CLOV): the output, with zeros written to the other
+  // site of each lexical pair if cout_zero.
+  const double2* cy;
+  const double2* cz;
+  double2* cout;
+  bool g5_in, cout_zero;
   // CG alpha fused into a hop launch that does not need it (k_hop only):
   // alpha = rr / pAp with pAp the fixed-order sum of alpha_nparts partials per
   // rhs; rhs r is handled by workgroup r mod grid, before its stencil work (in a
@@ -96,6 +104,8 @@ int hop_nblocks(const HopLaunch& h);
 int hop_max_parts(long V2);  // bound on partials per rhs of any hop launch
 int hop_nparts(const HopLaunch& h);  // partials per rhs of a tiled hop launch, as parts_count takes them
 hipError_t launch_hop(const HopLaunch& h, hipStream_t st);
+// whether a launch of this shape takes canonical input (HopLaunch::cy, cz)
+bool hop_reads_canonical(const HopLaunch& h);
 hipError_t launch_hop_xr(const HopLaunch& h, hipStream_t st);
 
 // Gauge import: canonical complex128 U -> internal links (any non-null
