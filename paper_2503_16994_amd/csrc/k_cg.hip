@@ -330,35 +330,13 @@ __global__ void k_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, co
   }
 }
 
-// step 2: s = g5 (b - y) with |s|^2 partials (y = Dhat x or Dw x); b, y, s
-// are tiled 12-component fields (one or two parities per rhs), spins 2,3 (the
-// upper half of every tile) negated
-__global__ void k_ru_sub(const double2* __restrict__ b, const double2* __restrict__ y, double2* s, long n,
-                         long rs, const CGState* cs, double* partials) {
-  __shared__ double sh[4];
-  const int q = blockIdx.y;
-  if (ru_skip(cs[q])) return;
-  const size_t o = (size_t)q * rs;
-  double acc = 0.0;
-  for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
-    double2 u = b[o + i], v = y[o + i];
-    double2 d = make_double2(u.x - v.x, u.y - v.y);
-    acc += d.x * d.x + d.y * d.y;
-    const long k = (i % (12 * kTile)) / kTile;  // component index within its tile
-    if (k >= 6) d = make_double2(-d.x, -d.y);
-    s[o + i] = d;
-  }
-  double t = bsum(acc, sh);
-  if (threadIdx.x == 0) partials[(size_t)q * gridDim.x + blockIdx.x] = t;
-}
-
-// step 3 (mixed only): r_lo = (float) r_true
-template <typename S>
-__global__ void k_ru_copy(const S* __restrict__ R, long rsR, float2* rl, long rsl, long n, const CGState* cs) {
+// (step 2, s = g5 (b - Dhat x) with its norm, is the last hop of that product)
+// step 3 (without FP32 operators): r_lo = (float) r_true
+__global__ void k_ru_copy(const double2* __restrict__ R, long rsR, float2* rl, long rsl, long n, const CGState* cs) {
   const int q = blockIdx.y;
   if (ru_skip(cs[q])) return;
   for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
-    const S v = R[(size_t)q * rsR + i];
+    const double2 v = R[(size_t)q * rsR + i];
     rl[(size_t)q * rsl + i] = make_float2((float)v.x, (float)v.y);
   }
 }
@@ -369,7 +347,7 @@ __global__ void k_ru_finish(CGState* s, const double* part_res, int n_res, const
   __shared__ double sh[4];
   const int r = blockIdx.x;
   if (ru_skip(s[r])) return;
-  const double res2 = psum(part_res + (size_t)r * n_res, n_res, sh);
+  const double res2 = psum(part_res + (size_t)r * parts_stride(n_res), n_res, sh);
   const double rr = psum(part_r + (size_t)r * parts_stride(n_r), n_r, sh);
   if (threadIdx.x != 0) return;
   CGState& c = s[r];
@@ -539,22 +517,10 @@ hipError_t launch_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, in
   k_ru_fold<<<grid, kB, 0, st>>>(X, rsX, xl, rsl, n, s);
   return hipGetLastError();
 }
-hipError_t launch_ru_sub(const double2* b, const double2* y, double2* s_out, long n, long rs,
-                         int nrhs, const CGState* s, double* partials, hipStream_t st) {
-  dim3 grid(blas_nblocks(n), nrhs);
-  k_ru_sub<<<grid, kB, 0, st>>>(b, y, s_out, n, rs, s, partials);
-  return hipGetLastError();
-}
 hipError_t launch_ru_copy(const double2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
                           const CGState* s, hipStream_t st) {
   dim3 grid(blas_nblocks(n), nrhs);
-  k_ru_copy<double2><<<grid, kB, 0, st>>>(R, rsR, rl, rsl, n, s);
-  return hipGetLastError();
-}
-hipError_t launch_ru_copy(const float2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
-                          const CGState* s, hipStream_t st) {
-  dim3 grid(blas_nblocks(n), nrhs);
-  k_ru_copy<float2><<<grid, kB, 0, st>>>(R, rsR, rl, rsl, n, s);
+  k_ru_copy<<<grid, kB, 0, st>>>(R, rsR, rl, rsl, n, s);
   return hipGetLastError();
 }
 hipError_t launch_ru_finish(CGState* s, const double* part_res, int n_res, const double* part_r, int n_r,

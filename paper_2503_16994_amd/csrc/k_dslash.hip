@@ -645,8 +645,10 @@ __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
     for (int r = 0; r < NR; ++r) canon_store<NC>(a, v[r], ts.p, ts.s, ts.rhs0 + r, ts.c0, canon_sh);
     return;
   }
+  // launches that may form a residual (HopLaunch::res)
+  constexpr bool RES = PRE == PRE_CLOV && POST == POST_NONE && std::is_same<SG, double2>::value;
   SO* ob = static_cast<SO*>(a.out);
-  if (a.both) ob += ts.p * a.par_stride;
+  if (a.both && ob) ob += ts.p * a.par_stride;
   // padding sites of the last tile (inactive, v = 0) are written too, so
   // every output vector holds zeros there
   const bool store = ts.s < a.g.V2p;
@@ -654,13 +656,34 @@ __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
   for (int r = 0; r < NR; ++r) {
     double nrm = 0.0;
     if (store) {
-      SO* op = ob + (size_t)(ts.rhs0 + r) * a.out_rs + tix(ts.s, 12) + ts.c0 * kTile;
-      if (a.nt_out) {
+      const size_t site = tix(ts.s, 12) + ts.c0 * kTile;
+      bool put = !a.masked_out || a.done[(ts.rhs0 + r) * (int)(sizeof(CGState) / sizeof(int))] == 0;
+      if constexpr (RES) {
+        if (a.res) {  // uniform over the launch
+          const double2* bp = a.res + (a.both ? ts.p * a.par_stride : 0) + (size_t)(ts.rhs0 + r) * a.res_rs + site;
 #pragma unroll
-        for (int k = 0; k < NC; ++k) st_nt(op + k * kTile, v[r][k]);
-      } else {
+          for (int k = 0; k < NC; ++k) {
+            const auto bv = ld(bp + k * kTile);
+            v[r][k] = csub(bv, v[r][k]);
+            if (a.res_g5 && ts.c0 + k >= 6) v[r][k] = {-v[r][k].re, -v[r][k].im};
+          }
+          if (a.out32) {
+            float2* op = a.out32 + (size_t)(ts.rhs0 + r) * a.out32_rs + site;
 #pragma unroll
-        for (int k = 0; k < NC; ++k) st(op + k * kTile, v[r][k]);
+            for (int k = 0; k < NC; ++k) st(op + k * kTile, v[r][k]);
+          }
+          put = put && ob != nullptr;
+        }
+      }
+      if (put) {
+        SO* op = ob + (size_t)(ts.rhs0 + r) * a.out_rs + site;
+        if (a.nt_out) {
+#pragma unroll
+          for (int k = 0; k < NC; ++k) st_nt(op + k * kTile, v[r][k]);
+        } else {
+#pragma unroll
+          for (int k = 0; k < NC; ++k) st(op + k * kTile, v[r][k]);
+        }
       }
       if (a.partials) {
 #pragma unroll
@@ -1043,10 +1066,21 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
     } else if (CANON && a.cout) {
       // through LDS below
     } else if (s < g.V2p) {  // padding sites (v = 0) too
-      SO* op = static_cast<SO*>(a.out) + (a.both ? p * a.par_stride : 0) + (size_t)rhs * a.out_rs + site;
+      const long po = a.both ? p * a.par_stride : 0;
+      if constexpr (std::is_same<SG, double2>::value) {
+        if (a.res) {
+          const double2* bp = a.res + po + (size_t)rhs * a.res_rs + site;
 #pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        st(op + 3 * q * kTile, v[q]);
+          for (int q = 0; q < 2; ++q) {
+            v[q] = csub(ld(bp + 3 * q * kTile), v[q]);
+            if (a.res_g5 && b == 1) v[q] = {-v[q].re, -v[q].im};
+            if (a.out32) st(a.out32 + (size_t)rhs * a.out32_rs + site + 3 * q * kTile, v[q]);
+          }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {  // one rhs per workgroup: masked_out is the early exit above
+        if (a.out) st(static_cast<SO*>(a.out) + po + (size_t)rhs * a.out_rs + site + 3 * q * kTile, v[q]);
         n2[q] = cnorm2(v[q]);
       }
     }

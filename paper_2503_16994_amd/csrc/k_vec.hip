@@ -289,30 +289,6 @@ hipError_t launch_axpby(double a, const void* x, int xprec, double b, void* y, i
   return hipGetLastError();
 }
 
-// out = x - y with partial |out|^2
-__global__ void k_sub_norm(const double2* __restrict__ x, const double2* __restrict__ y, double2* out,
-                           long n, long rs, double* partials) {
-  __shared__ double sh[4];
-  const int q = blockIdx.y;
-  const size_t o = (size_t)q * rs;
-  double acc = 0.0;
-  for (long i = (long)blockIdx.x * kVecBlock + threadIdx.x; i < n; i += (long)gridDim.x * kVecBlock) {
-    double2 a = x[o + i], b = y[o + i];
-    double2 d = make_double2(a.x - b.x, a.y - b.y);
-    out[o + i] = d;
-    acc += d.x * d.x + d.y * d.y;
-  }
-  double b = block_sum256(acc, sh);
-  if (threadIdx.x == 0) partials[(size_t)q * gridDim.x + blockIdx.x] = b;
-}
-
-hipError_t launch_sub_norm(const double2* x, const double2* y, double2* out, long n, long rs, int nrhs,
-                           double* partials, hipStream_t st) {
-  dim3 grid(blas_nblocks(n), nrhs);
-  k_sub_norm<<<grid, kVecBlock, 0, st>>>(x, y, out, n, rs, partials);
-  return hipGetLastError();
-}
-
 // zero fill with a kernel (graph-capturable, unlike a memset node)
 __global__ void k_fill_zero(uint4* p, size_t n16) {
   for (size_t i = (size_t)blockIdx.x * kVecBlock + threadIdx.x; i < n16; i += (size_t)gridDim.x * kVecBlock)
@@ -335,6 +311,30 @@ hipError_t launch_fill_zero(void* x, size_t bytes, hipStream_t st) {
     if (nb > kVecMaxBlocks) nb = kVecMaxBlocks;
     k_fill_zero_bytes<<<(unsigned)nb, kVecBlock, 0, st>>>((unsigned char*)x, bytes);
   }
+  return hipGetLastError();
+}
+
+__global__ void k_fill_zero_rhs(double2* x, long n, long rs) {
+  double2* p = x + (size_t)blockIdx.y * rs;
+  for (long i = (long)blockIdx.x * kVecBlock + threadIdx.x; i < n; i += (long)gridDim.x * kVecBlock)
+    p[i] = make_double2(0.0, 0.0);
+}
+hipError_t launch_fill_zero_rhs(double2* x, long n, long rs, int nrhs, hipStream_t st) {
+  k_fill_zero_rhs<<<dim3(blas_nblocks(n), nrhs), kVecBlock, 0, st>>>(x, n, rs);
+  return hipGetLastError();
+}
+
+// out = g5 x on a half vector (see k_g5)
+__global__ void k_g5_copy(const double2* __restrict__ x, double2* out, long n, long rs) {
+  const size_t o = (size_t)blockIdx.y * rs;
+  for (long i = (long)blockIdx.x * kVecBlock + threadIdx.x; i < n; i += (long)gridDim.x * kVecBlock) {
+    double2 v = x[o + i];
+    if (i % (12 * kTile) >= 6 * kTile) v = make_double2(-v.x, -v.y);
+    out[o + i] = v;
+  }
+}
+hipError_t launch_g5_copy(const double2* x, double2* out, long V2p, long rs, int nrhs, hipStream_t st) {
+  k_g5_copy<<<dim3(blas_nblocks(12 * V2p), nrhs), kVecBlock, 0, st>>>(x, out, 12 * V2p, rs);
   return hipGetLastError();
 }
 

@@ -82,6 +82,15 @@ struct HopLaunch {
   long xr_rs;    // rhs stride of r and p
   long xr_xrs;   // rhs stride of x
   const struct CGState* cg;
+  // Residual in place of the result (FP64, PRE_CLOV): res - result, res like
+  // out, then g5 if res_g5; written to out, or rounded to FP32 to out32, or (both
+  // null) only summed into `partials`.
+  const double2* res;
+  long res_rs;
+  bool res_g5;
+  float2* out32;
+  long out32_rs;
+  bool masked_out;  // no output for rhs whose `done` flag is set
   // Canonical complex128 fields [rhs][lex][12] in place of internal vectors.
   // cy, cz (hop_reads_canonical only): the input y, z, g5 applied to both if
   // g5_in; cout (FP64, PRE_CLOV): the output, with zeros written to the other
@@ -240,12 +249,8 @@ hipError_t launch_cg_xflush(float2* x, long rsx, const PWindow& pw, long n, long
 // reliable-update kernels (each skips rhs without a pending update)
 hipError_t launch_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, int nrhs,
                           const CGState* s, hipStream_t st);
-hipError_t launch_ru_sub(const double2* b, const double2* y, double2* s_out, long n, long rs,
-                         int nrhs, const CGState* s, double* partials, hipStream_t st);
 // rl = R (rounded to FP32) for every rhs with a pending reliable update
 hipError_t launch_ru_copy(const double2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
-                          const CGState* s, hipStream_t st);
-hipError_t launch_ru_copy(const float2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
                           const CGState* s, hipStream_t st);
 hipError_t launch_ru_finish(CGState* s, const double* part_res, int n_res, const double* part_r,
                             int n_r, int nrhs, hipStream_t st);
@@ -262,10 +267,11 @@ hipError_t launch_axpby(double a, const void* x, int xprec, double b, void* y, i
 // y = x converted between precisions
 hipError_t launch_convert(const void* x, int xprec, void* y, int yprec, long n, long rs_x,
                           long rs_y, int nrhs, hipStream_t st);
-// out = x - y (FP64) with partial |out|^2
-hipError_t launch_sub_norm(const double2* x, const double2* y, double2* out, long n, long rs,
-                           int nrhs, double* partials, hipStream_t st);
 hipError_t launch_fill_zero(void* x, size_t bytes, hipStream_t st);
+// n elements (16 bytes each) of every rhs set to zero
+hipError_t launch_fill_zero_rhs(double2* x, long n, long rs, int nrhs, hipStream_t st);
+// out = g5 x on half vectors (one parity, tiled 12-component fields), FP64
+hipError_t launch_g5_copy(const double2* x, double2* out, long V2p, long rs, int nrhs, hipStream_t st);
 // x (even half vector) *= g5 in place
 hipError_t launch_g5(void* x, int prec, long V2p, long rs, int nrhs, hipStream_t st);
 

@@ -126,10 +126,12 @@ hipError_t hop_eo(const Ctl& c, int lprec, Vec y, Vec out_o, const int* done, in
   return launch_hop(h, c.st);
 }
 
-// out_e = [g5] (A_ee z_e + 1/2 H t_o), optional |out|^2 partials
+// out_e = [g5] (A_ee z_e + 1/2 H t_o), optional |out|^2 partials; masked: only
+// for rhs whose done flag is not set
 hipError_t hop_oe(const Ctl& c, int lprec, Vec z, Vec t_o, Vec out, bool g5, double* partials,
-                  const int* done, int nr_tile) {
+                  const int* done, int nr_tile, bool masked = false) {
   HopLaunch h = mk(c, lprec);
+  h.masked_out = masked;
   h.p_out = 0;
   h.in_prec = z.prec;
   h.out_prec = out.prec;
@@ -144,6 +146,36 @@ hipError_t hop_oe(const Ctl& c, int lprec, Vec z, Vec t_o, Vec out, bool g5, dou
   h.post = POST_NONE;
   h.scale = 0.5;
   h.g5 = g5;
+  h.partials = partials;
+  h.done = done;
+  if (nr_tile == 1) single_tile(h);
+  return launch_hop(h, c.st);
+}
+
+// FP64 residual s_e = g5 (b_e - (A_ee z_e + 1/2 H t_o)) with |s|^2 partials; out
+// FP64, or FP32 (rounded)
+hipError_t hop_oe_res(const Ctl& c, Vec z, Vec t_o, Vec b, Vec out, double* partials, const int* done, int nr_tile) {
+  HopLaunch h = mk(c, P_F64);
+  h.p_out = 0;
+  h.in_prec = h.out_prec = P_F64;
+  h.y = t_o.p;
+  h.y_rs = t_o.rs;
+  h.z = z.p;
+  h.z_rs = z.rs;
+  h.res = (const double2*)b.p;
+  h.res_rs = b.rs;
+  h.res_g5 = true;
+  if (out.prec == P_F64) {
+    h.out = out.p;
+    h.out_rs = out.rs;
+  } else {
+    h.out32 = (float2*)out.p;
+    h.out32_rs = out.rs;
+  }
+  h.Cpre = clov_of(c.w, P_F64);
+  h.pre = PRE_CLOV;
+  h.post = POST_NONE;
+  h.scale = 0.5;
   h.partials = partials;
   h.done = done;
   if (nr_tile == 1) single_tile(h);
@@ -193,12 +225,18 @@ HopLaunch dw_full_launch(const Ctl& c) {
 // the tuned rhs tile and direction split decide the block size)
 int full_parts(const Ctl& c) { return hop_nparts(dw_full_launch(c)); }
 
-// out (full, both parities) = [g5] Dw y, optional partials; with alpha_cg the
-// launch also computes the CG alpha of every rhs from alpha_parts
+// out (full, both parities) = [g5] Dw y, or with res g5 (res - Dw y); optional
+// partials (and out null: nothing but them); masked: only for rhs whose done
+// flag is not set; with alpha_cg the launch also
+// computes the CG alpha of every rhs from alpha_parts
 hipError_t dw_full(const Ctl& c, const double2* y, double2* out, bool g5, double* partials,
                    const int* done, CGState* alpha_cg = nullptr, const double* alpha_parts = nullptr,
-                   int alpha_nparts = 0) {
+                   int alpha_nparts = 0, const double2* res = nullptr, bool masked = false) {
   HopLaunch h = dw_full_launch(c);
+  h.masked_out = masked;
+  h.res = res;
+  h.res_rs = 24 * c.g->V2p;
+  h.res_g5 = true;
   h.alpha_cg = alpha_cg;
   h.alpha_parts = alpha_parts;
   h.alpha_nparts = alpha_nparts;
@@ -215,7 +253,7 @@ hipError_t dw_full(const Ctl& c, const double2* y, double2* out, bool g5, double
   h.pre = PRE_CLOV;
   h.post = POST_NONE;
   h.scale = -0.5;
-  h.g5 = g5;
+  h.g5 = g5 && !res;
   h.partials = partials;
   h.done = done;
   return launch_hop(h, c.st);
@@ -336,9 +374,8 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   CGState* cg = m.cg;
   const int* done = &cg[0].done;
   const int* skip_ru = &cg[0].skip_ru;
-  // partials per rhs of an FP64 single-tile hop launch (setup, and the
-  // reliable updates of FP64 phases), and of an FP64 launch in the
-  // workspace's tuning (the reliable updates of low-precision phases)
+  // partials per rhs of an FP64 single-tile hop launch (setup), and of an FP64
+  // launch in the workspace's tuning (the reliable updates)
   HopLaunch h1 = mk(c, P_F64);
   single_tile(h1);
   const int nb_hop = hop_nparts(h1);
@@ -353,18 +390,15 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   LQCD_HIP(launch_pack(g->kg, (const double2*)eta, m.E, P_F64, N, false, st));
   if (x0)
     LQCD_HIP(launch_pack(g->kg, (const double2*)x0, m.X, P_F64, N, false, st));
-  else
-    LQCD_HIP(launch_fill_zero(m.X, full_bytes, st));
+  else  // even-odd: the odd half is written by the reconstruction
+    LQCD_HIP(launch_fill_zero_rhs(m.X, eo ? HRS : FRS, FRS, N, st));
 
   // b = Dhat^+ eta_hat (eo) or Dw^+ eta (full) into R, with |b|^2
   int nb_op;  // partial count of the norm-producing operator launch
   if (eo) {
-    LQCD_HIP(launch_fill_zero(m.EH, full_bytes, st));
-    LQCD_HIP(launch_fill_zero(m.TMP, full_bytes, st));
     LQCD_HIP(clover_inv_apply(c, odd_part(E, V2), E, odd_part(TMP, V2), false, 0.0));  // A_oo^-1 eta_o
     LQCD_HIP(hop_oe_ident(c, E, odd_part(TMP, V2), EH));                               // eta_hat
-    LQCD_HIP(hipMemcpyAsync(m.AP, m.EH, full_bytes, hipMemcpyDeviceToDevice, st));
-    LQCD_HIP(launch_g5(m.AP, P_F64, V2, FRS, N, st));
+    LQCD_HIP(launch_g5_copy(m.EH, m.AP, V2, FRS, N, st));
     LQCD_HIP(hop_eo(dg(c), P_F64, AP, odd_part(TMP, V2), nullptr, 1));
     LQCD_HIP(hop_oe(dg(c), P_F64, AP, odd_part(TMP, V2), R, true, parts, nullptr, 1));
     nb_op = nb_hop;
@@ -400,7 +434,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   };
   select(mixed);
   if (!mixed) {
-    LQCD_HIP(hipMemcpyAsync(m.P, m.R, full_bytes, hipMemcpyDeviceToDevice, st));
+    LQCD_HIP(launch_convert(m.R, P_F64, m.P, P_F64, n_vec, FRS, FRS, N, st));
   } else {
     LQCD_HIP(launch_fill_zero(m.xl, (size_t)N * HRS * 8, st));
     LQCD_HIP(launch_convert(m.R, P_F64, m.rl, P_F32, n_vec, FRS, HRS, N, st));
@@ -420,45 +454,37 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   LQCD_HIP(launch_cg_setup(cg, scal, scal + N, cfg, st));
 
   // ---- reliable update group (skips rhs without a pending request) ---------
-  // The FP64 hops skip whole rhs tiles whose rhs have no pending request.  In
-  // an FP64 phase the update writes the recursion's own residual R, so every
-  // rhs is its own tile; in a low-precision phase the hops write only FP64
-  // scratch (TMP, Q, AP) that the other rhs do not use (the fold, the
-  // residual and the copy into the recursion skip them), so the hops run in
-  // the workspace's FP64 tuning: with the rhs of a propagator requesting
-  // their updates together, one multi-rhs launch instead of one per rhs.
+  // The hops skip whole rhs tiles whose rhs have no pending request.  A tile
+  // with one computes all its rhs: only scratch (TMP, Q, AP, and the FP32 t
+  // and Ap) is written for the others, the recursion's own r under a mask (the
+  // fold and the finish skip them too).
   auto reliable_update = [&]() -> hipError_t {
     hipError_t e;
     if (eo) {
-      const int ru_tile = lo ? 0 : 1;
-      const int nb_ru = lo ? nb_hop_tuned : nb_hop;
       // (with deferred x updates the flush before the update has folded x)
       if (lo && !lo16 && (e = launch_ru_fold(m.X, FRS, m.xl, HRS, 12 * V2, N, cg, st))) return e;
-      if ((e = hop_eo(c, P_F64, X, odd_part(TMP, V2), skip_ru, ru_tile))) return e;
-      if ((e = hop_oe(c, P_F64, X, odd_part(TMP, V2), Q, false, nullptr, skip_ru, ru_tile))) return e;
-      if ((e = launch_ru_sub(m.EH, m.Q, m.AP, 12 * V2, FRS, N, cg, parts2, st))) return e;
+      if ((e = hop_eo(c, P_F64, X, odd_part(TMP, V2), skip_ru, 0))) return e;
       if (lo && ru32) {
         // s rounded into FP32 scratch, Dhat^+ in the workspace's FP32 tuning,
-        // the result copied into the recursion's r (pending rhs only).  The
+        // the result written into the recursion's r (pending rhs only).  The
         // scratch vectors are free at this point of an iteration: the FP32
-        // t and Ap, and the FP32 q (FP32 recursion) or the two window slots
-        // kept in the FP32 p (BF16 recursion), which the flush has consumed.
-        const Vec s32{m.apl, P_F32, HRS}, t32{m.tl, P_F32, HRS}, r32{lo16 ? m.pl : m.ql, P_F32, HRS};
-        if ((e = launch_ru_copy(m.AP, FRS, m.apl, HRS, 12 * V2, N, cg, st))) return e;
+        // t and Ap.
+        const Vec s32{m.apl, P_F32, HRS}, t32{m.tl, P_F32, HRS};
+        if ((e = hop_oe_res(c, X, odd_part(TMP, V2), EH, s32, parts2, skip_ru, 0))) return e;
         if ((e = hop_eo(dg(c), P_F32, s32, t32, skip_ru, 0))) return e;
-        if ((e = hop_oe(dg(c), P_F32, s32, t32, r32, true, parts, skip_ru, 0))) return e;
-        if ((e = launch_ru_copy((const float2*)r32.p, HRS, m.rl, HRS, 12 * V2, N, cg, st))) return e;
-        return launch_ru_finish(cg, parts2, blas_nblocks(12 * V2), parts, nb_ru32, N, st);
+        if ((e = hop_oe(dg(c), P_F32, s32, t32, Vec{m.rl, P_F32, HRS}, true, parts, skip_ru, 0, true))) return e;
+        return launch_ru_finish(cg, parts2, nb_hop_tuned, parts, nb_ru32, N, st);
       }
-      if ((e = hop_eo(dg(c), P_F64, AP, odd_part(TMP, V2), skip_ru, ru_tile))) return e;
-      if ((e = hop_oe(dg(c), P_F64, AP, odd_part(TMP, V2), lo ? Q : R, true, parts, skip_ru, ru_tile))) return e;
+      if ((e = hop_oe_res(c, X, odd_part(TMP, V2), EH, AP, parts2, skip_ru, 0))) return e;
+      if ((e = hop_eo(dg(c), P_F64, AP, odd_part(TMP, V2), skip_ru, 0))) return e;
+      if ((e = hop_oe(dg(c), P_F64, AP, odd_part(TMP, V2), lo ? Q : R, true, parts, skip_ru, 0, !lo)))
+        return e;
       if (lo && (e = launch_ru_copy(m.Q, FRS, m.rl, HRS, 12 * V2, N, cg, st))) return e;
-      return launch_ru_finish(cg, parts2, blas_nblocks(12 * V2), parts, nb_ru, N, st);
+      return launch_ru_finish(cg, parts2, nb_hop_tuned, parts, nb_hop_tuned, N, st);
     }
-    if ((e = dw_full(c, m.X, m.TMP, false, nullptr, skip_ru))) return e;
-    if ((e = launch_ru_sub(m.E, m.TMP, m.AP, 24 * V2, FRS, N, cg, parts2, st))) return e;
-    if ((e = dw_full(dg(c), m.AP, m.R, true, parts, skip_ru))) return e;
-    return launch_ru_finish(cg, parts2, blas_nblocks(24 * V2), parts, full_parts(c), N, st);
+    if ((e = dw_full(c, m.X, m.AP, false, parts2, skip_ru, nullptr, nullptr, 0, m.E))) return e;
+    if ((e = dw_full(dg(c), m.AP, m.R, true, parts, skip_ru, nullptr, nullptr, 0, nullptr, true))) return e;
+    return launch_ru_finish(cg, parts2, full_parts(c), parts, full_parts(c), N, st);
   };
 
   // ---- initial guess: the first residual comes from a reliable update ------
@@ -652,9 +678,8 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   if (mixed) LQCD_HIP(launch_axpby(1.0, m.xl, P_F32, 1.0, m.X, P_F64, n_vec, HRS, FRS, N, st));
   if (eo) LQCD_HIP(clover_inv_apply(c, odd_part(E, V2), X, odd_part(X, V2), true, 0.5));
   LQCD_HIP(launch_unpack(g->kg, m.X, P_F64, (double2*)psi, N, st));
-  LQCD_HIP(dw_full(c, m.X, m.TMP, false, nullptr, nullptr));
-  LQCD_HIP(launch_sub_norm(m.E, m.TMP, m.AP, 24 * V2, FRS, N, parts, st));
-  LQCD_HIP(launch_reduce(parts, blas_nblocks(24 * V2), N, scal + 3 * N, st));
+  LQCD_HIP(dw_full(c, m.X, nullptr, false, parts, nullptr, nullptr, nullptr, 0, m.E));  // |eta - Dw psi|^2 alone
+  LQCD_HIP(launch_reduce(parts, full_parts(c), N, scal + 3 * N, st));
   std::vector<double> fres(N);
   LQCD_HIP(hipMemcpyAsync(fres.data(), scal + 3 * N, sizeof(double) * N, hipMemcpyDeviceToHost, st));
   LQCD_HIP(hipMemcpyAsync(hs.data(), cg, sizeof(CGState) * N, hipMemcpyDeviceToHost, st));

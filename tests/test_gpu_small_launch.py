@@ -53,11 +53,19 @@ def test_small_solves_equal_the_general_ones(solver, inner, mu):
     L = (10, 6, 6, 10)
     print(f"\n[gpu case] small solve {L} solver {solver} inner {inner} mu {mu}", flush=True)
     lat, g = system(L, P, True)
-    x = torch.from_numpy(np.stack([inputs.gaussian_spinor(L, k, P) for k in range(N)])).cuda()
+    # noise and point sources side by side: the columns of one rhs tile ask for
+    # their reliable updates in different iterations
+    src = [inputs.gaussian_spinor(L, k, P) if k % 3 else inputs.point_source(L, (0, 0, 0, k % 5), k % 4, 0)
+           for k in range(N)]
+    x = torch.from_numpy(np.stack(src)).cuda()
     kw = dict(tol=1e-10, solver=solver, inner_prec=inner, mu=mu)
-    batch = lqcd.solve(g, x, 0.123, 1.7, ws=lqcd.Workspace(lat, PM, N), **kw)
     ws = lqcd.Workspace(lat, PM, 1)
-    for j in (0, N - 1):
-        alone = lqcd.solve(g, x[j:j + 1], 0.123, 1.7, ws=ws, **kw)
-        assert alone.info[0]["iters"] == batch.info[j]["iters"]
-        assert torch.equal(alone.psi[0], batch.psi[j]), j
+    alone = {j: lqcd.solve(g, x[j:j + 1], 0.123, 1.7, ws=ws, **kw) for j in (0, 1, 2, N - 2, N - 1)}
+    for tune in (None, (3, 1, 1)):
+        many = lqcd.Workspace(lat, PM, N)
+        if tune:
+            lqcd.set_tuning(many, lqcd.F64, *tune)
+        batch = lqcd.solve(g, x, 0.123, 1.7, ws=many, **kw)
+        for j, one in alone.items():
+            assert one.info[0]["iters"] == batch.info[j]["iters"], (tune, j)
+            assert torch.equal(one.psi[0], batch.psi[j]), (tune, j)
