@@ -134,15 +134,15 @@ struct HopSpec {
 // Measured, us per pair of hops, non-temporal loads and one rhs per thread
 // against this choice: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
 // 4 rhs 136 / 98, 12 rhs 391 / 299, 24^3x48 12 rhs 2632 / 1707, 32^3x64 1 rhs
-// 753 / 694, 12 rhs 7936 / 4119; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
+// 753 / 645, 12 rhs 7936 / 4119; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
 // / 113, 32^3x64 12 rhs 4076 / 2395; BF16 32^3x64 12 rhs 1533 / 1188.
 inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
   constexpr int kCached = LQCD_TUNE_NT_STORE | LQCD_TUNE_CACHED_GAUGE, kStream = LQCD_TUNE_NT_STORE;
   const int64_t vn = V * n, large = 1000000;
   lqcd_tuning t = {1, 1, 1, 0};
-  if (V >= large && n > 1) {
+  if (V >= large) {
     t.block_order = 2;
-    t.nr_tile = (n % 3 == 0 && prec != LQCD_BF16) || n == 3 ? 3 : 2;
+    if (n > 1) t.nr_tile = (n % 3 == 0 && prec != LQCD_BF16) || n == 3 ? 3 : 2;
   }
   if (prec == LQCD_BF16) {
     if (n >= 4 && vn >= 390000) t.nr_tile = 2;
