@@ -25,6 +25,7 @@
 // ill-conditioned system is not a stall, and eight such updates without a
 // halving are needed.  Healthy solves gain about a factor ten per update.
 #include <algorithm>
+#include <type_traits>
 
 #include "lqcd_kernels.h"
 
@@ -49,6 +50,15 @@ __device__ inline double bsum(double v, double* sh) {
 // fixed-order sum of the partials of one rhs (n as in parts_count), result
 // broadcast to the block
 __device__ inline double psum(const double* p, int n, double* sh) {
+  if (parts_count(n) <= 64) {
+    // every wave forms the sum of the general route's first wave (the others
+    // add zeros there), and no barrier is needed
+    const int l = threadIdx.x & 63;
+    double v = l < parts_count(n) ? parts_at(p, n, l) : 0.0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+  }
   double acc = 0.0;
   for (int i = threadIdx.x; i < parts_count(n); i += kB) acc += parts_at(p, n, i);
   double s = bsum(acc, sh);
@@ -192,42 +202,69 @@ __device__ inline void st4(float2* p, const cpx<float> (&v)[4]) {
 }
 
 // pn = r + beta p over the n elements of one rhs (offset o), and plo = pn if
-// given; p and pn may be the same vector
-template <typename S, typename SP, typename SL, typename A>
-__device__ inline void p_update(const SP* p, SP* pn, const S* r, SL* plo, A beta, size_t o, long n) {
-  for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
+// given; p and pn may be the same vector.  load() fetches this thread's first
+// elements, so that a small launch has them in flight while beta is formed;
+// run() does the update.  BF16-only directions move four elements a lane.
+template <typename S, typename SP, typename SL>
+struct PUpdate {
+  using A = typename StoreTraits<S>::acc;
+  const SP* p;
+  SP* pn;
+  const S* r;
+  SL* plo;
+  size_t o;
+  long n;
+  bool four;
+  cpx<A> pv[4], rv[4];
+  __device__ inline PUpdate(const SP* p_, SP* pn_, const S* r_, SL* plo_, size_t o_, long n_)
+      : p(p_), pn(pn_), r(r_), plo(plo_), o(o_), n(n_) {
+    four = std::is_same<SP, bf16x2>::value && plo == nullptr && (n & 3) == 0 && (o & 3) == 0;
+  }
+  __device__ inline long first() const { return (long)blockIdx.x * kB + threadIdx.x; }
+  __device__ inline long count() const { return four ? n >> 2 : n; }
+  __device__ inline void load(long i) {
+    if constexpr (std::is_same<SP, bf16x2>::value) {
+      if (four) {
+        ld4(p + o + 4 * i, pv);
+        ld4(r + o + 4 * i, rv);
+        return;
+      }
+    }
     const auto p0 = ld(p + o + i);
-    const auto rv = ld(r + o + i);
-    const cpx<A> pv = {rv.re + beta * (A)p0.re, rv.im + beta * (A)p0.im};
-    st(pn + o + i, pv);
-    if (plo) st(plo + o + i, pv);
+    pv[0] = {(A)p0.re, (A)p0.im};
+    rv[0] = ld(r + o + i);
   }
-}
-// the BF16-only direction of BF16-operand iterations, four elements a lane
-__device__ inline void p_update(const bf16x2* p, bf16x2* pn, const float2* r, bf16x2* plo, float beta, size_t o,
-                                long n) {
-  if (plo != nullptr || (n & 3) != 0 || (o & 3) != 0) {
-    p_update<float2, bf16x2, bf16x2, float>(p, pn, r, plo, beta, o, n);
-    return;
+  __device__ inline void load() {
+    if (first() < count()) load(first());
   }
-  for (long i = (long)blockIdx.x * kB + threadIdx.x; i < (n >> 2); i += (long)gridDim.x * kB) {
-    cpx<float> pv[4], rv[4];
-    ld4(p + o + 4 * i, pv);
-    ld4(r + o + 4 * i, rv);
+  __device__ inline void run(A beta) {
+    for (long i = first(); i < count(); i += (long)gridDim.x * kB) {
+      if (i != first()) load(i);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) pv[k] = {rv[k].re + beta * pv[k].re, rv[k].im + beta * pv[k].im};
-    st4(pn + o + 4 * i, pv);
+      for (int k = 0; k < 4; ++k)
+        if (k == 0 || std::is_same<SP, bf16x2>::value)
+          pv[k] = {rv[k].re + beta * pv[k].re, rv[k].im + beta * pv[k].im};
+      if constexpr (std::is_same<SP, bf16x2>::value) {
+        if (four) {
+          st4(pn + o + 4 * i, pv);
+          continue;
+        }
+      }
+      st(pn + o + i, pv[0]);
+      if (plo) st(plo + o + i, pv[0]);
+    }
   }
-}
+};
 
 // p = r + beta p ; optional low-precision copy of p
 template <typename S, typename SP, typename SL>
 __global__ void k_cg_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, const CGState* cs, SL* plo) {
   const int q = blockIdx.y;
+  PUpdate<S, SP, SL> u(p, pn, r, plo, (size_t)q * rs, n);
+  u.load();
   if (cs[q].done) return;
   using A = typename StoreTraits<S>::acc;
-  const A beta = (A)cs[q].beta;
-  p_update(p, pn, r, plo, beta, (size_t)q * rs, n);
+  u.run((A)cs[q].beta);
 }
 
 // beta step fused with p = r + beta p (iterations without a reliable update):
@@ -242,14 +279,15 @@ __global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n
   __shared__ double sh[4];
   const int q = blockIdx.y;
   CGState& c = cs[q];
+  PUpdate<S, SP, SL> u(p, pn, r, plo, (size_t)q * rs, n);
+  u.load();
+  const double rr0 = c.rr_prev;
   if (c.done) return;
   const double v = psum(partials + (size_t)q * parts_stride(nparts), nparts, sh);
-  const double rr0 = c.rr_prev;
   if (blockIdx.x == 0 && threadIdx.x == 0) beta_step(c, v);
   if (!finite(v)) return;
   using A = typename StoreTraits<S>::acc;
-  const A beta = (A)((rr0 > 0.0) ? v / rr0 : 0.0);
-  p_update(p, pn, r, plo, beta, (size_t)q * rs, n);
+  u.run((A)((rr0 > 0.0) ? v / rr0 : 0.0));
 }
 
 __device__ inline bool ru_skip(const CGState& c) { return c.skip_ru != 0 || c.done != 0; }
