@@ -292,83 +292,79 @@ __global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n
 
 __device__ inline bool ru_skip(const CGState& c) { return c.skip_ru != 0 || c.done != 0; }
 
-// x += sum_j alpha_w[j] p_j (the deferred updates of one window), summed in
-// slot order in FP32; a slot whose alpha is 0 (an iteration the rhs skipped)
-// is not read.  With X given, a rhs with a pending reliable update also gets
-// the update's first step here: X += x (FP64), x = 0, so that x is not
-// written and read back in between.
-__global__ void k_cg_xflush(float2* x, long rsx, const PWindow pw, long n, long rs, const CGState* cs,
-                            double2* X, long rsX) {
+// x += sum_j alpha_w[j] p_j (the deferred updates of one window) in x's
+// precision and in slot order, the operations of an update in every iteration;
+// a slot whose alpha is 0 (an iteration the rhs skipped) is not read.  With X
+// given (x in FP32), a rhs with a pending reliable update also gets the
+// update's first step here: X += x (FP64), x = 0, so that x is not written and
+// read back in between.  BF16 directions move four elements a lane.
+// Bound: HBM.  An iteration that updates x itself reads x and p and writes x;
+// deferred over five iterations that is 1.4 passes instead of 3.
+template <typename SX, typename SP>
+__global__ void k_cg_xflush(SX* x, long rsx, const PWindow pw, long n, long rs, const CGState* cs, double2* X,
+                            long rsX) {
+  using A = typename StoreTraits<SX>::acc;
   const int q = blockIdx.y;
-  float a[kXWindow];
+  A a[kXWindow];
   bool any = false;
 #pragma unroll
   for (int j = 0; j < kXWindow; ++j) {
-    a[j] = (float)cs[q].alpha_w[j];
-    any = any || a[j] != 0.f;
+    a[j] = (A)cs[q].alpha_w[j];
+    any = any || a[j] != (A)0;
   }
   const bool fold = X != nullptr && !ru_skip(cs[q]);
   if (!any && !fold) return;
   const size_t o = (size_t)q * rs, ox = (size_t)q * rsx, oX = (size_t)q * rsX;
-  if (((n | (long)o | (long)ox) & 3) == 0) {  // four elements a lane
-    for (long i = (long)blockIdx.x * kB + threadIdx.x; i < (n >> 2); i += (long)gridDim.x * kB) {
-      cpx<float> xv[4];
-      ld4(x + ox + 4 * i, xv);
+  if constexpr (std::is_same<SP, bf16x2>::value) {
+    if (((n | (long)o | (long)ox) & 3) == 0) {  // four elements a lane
+      for (long i = (long)blockIdx.x * kB + threadIdx.x; i < (n >> 2); i += (long)gridDim.x * kB) {
+        cpx<float> xv[4];
+        ld4(x + ox + 4 * i, xv);
 #pragma unroll
-      for (int j = 0; j < kXWindow; ++j) {
-        if (a[j] == 0.f) continue;  // uniform over the workgroup
-        cpx<float> pv[4];
-        ld4(pw.p[j] + o + 4 * i, pv);
+        for (int j = 0; j < kXWindow; ++j) {
+          if (a[j] == 0.f) continue;  // uniform over the workgroup
+          cpx<float> pv[4];
+          ld4(static_cast<const SP*>(pw.p[j]) + o + 4 * i, pv);
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          xv[k].re += a[j] * pv[k].re;
-          xv[k].im += a[j] * pv[k].im;
+          for (int k = 0; k < 4; ++k) {
+            xv[k].re += a[j] * pv[k].re;
+            xv[k].im += a[j] * pv[k].im;
+          }
         }
-      }
-      if (fold) {
+        if (fold) {
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          double2* xp = X + oX + 4 * i + k;
-          const double2 b = *xp;
-          *xp = make_double2(b.x + (double)xv[k].re, b.y + (double)xv[k].im);
-          xv[k] = {0.f, 0.f};
+          for (int k = 0; k < 4; ++k) {
+            double2* xp = X + oX + 4 * i + k;
+            const double2 b = *xp;
+            *xp = make_double2(b.x + (double)xv[k].re, b.y + (double)xv[k].im);
+            xv[k] = {0.f, 0.f};
+          }
         }
+        st4(x + ox + 4 * i, xv);
       }
-      st4(x + ox + 4 * i, xv);
+      return;
     }
-    return;
   }
   for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
-    float2 xv = x[ox + i];
+    cpx<A> xv = ld(x + ox + i);
 #pragma unroll
     for (int j = 0; j < kXWindow; ++j) {
-      if (a[j] == 0.f) continue;  // uniform over the workgroup
-      const auto pv = ld(pw.p[j] + o + i);
-      xv.x += a[j] * pv.re;
-      xv.y += a[j] * pv.im;
+      if (a[j] == (A)0) continue;  // uniform over the workgroup
+      const auto pv = ld(static_cast<const SP*>(pw.p[j]) + o + i);
+      xv.re += a[j] * (A)pv.re;
+      xv.im += a[j] * (A)pv.im;
     }
     if (fold) {
       const double2 b = X[oX + i];
-      X[oX + i] = make_double2(b.x + (double)xv.x, b.y + (double)xv.y);
-      xv = make_float2(0.f, 0.f);
+      X[oX + i] = make_double2(b.x + (double)xv.re, b.y + (double)xv.im);
+      xv = {(A)0, (A)0};
     }
-    x[ox + i] = xv;
+    st(x + ox + i, xv);
   }
 }
 
-// reliable update, step 1: fold the low-precision correction into x (FP64)
-__global__ void k_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, const CGState* cs) {
-  const int q = blockIdx.y;
-  if (ru_skip(cs[q])) return;
-  for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
-    float2 a = xl[(size_t)q * rsl + i];
-    double2 b = X[(size_t)q * rsX + i];
-    X[(size_t)q * rsX + i] = make_double2(b.x + (double)a.x, b.y + (double)a.y);
-    xl[(size_t)q * rsl + i] = make_float2(0.f, 0.f);
-  }
-}
-
-// (step 2, s = g5 (b - Dhat x) with its norm, is the last hop of that product)
+// (step 1, X += x, is part of the flush; step 2, s = g5 (b - Dhat x) with its
+// norm, is the last hop of that product)
 // step 3 (without FP32 operators): r_lo = (float) r_true
 __global__ void k_ru_copy(const double2* __restrict__ R, long rsR, float2* rl, long rsl, long n, const CGState* cs) {
   const int q = blockIdx.y;
@@ -498,11 +494,11 @@ hipError_t launch_cg_p(void* p, const void* r, int prec, long n, long rs, int nr
                        void* plo, int lo_prec, hipStream_t st, void* pnext) {
   dim3 grid(blas_nblocks(n), nrhs);
   if (prec == P_F64 && p)
-    k_cg_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)p, (const double2*)r, n,
-                                                           rs, s, (double2*)nullptr);
+    k_cg_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)(pnext ? pnext : p),
+                                                           (const double2*)r, n, rs, s, (double2*)nullptr);
   else if (prec == P_F32 && p && (plo == nullptr || lo_prec == P_F32))
-    k_cg_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n, rs, s,
-                                                        (float2*)plo);
+    k_cg_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)(pnext ? pnext : p),
+                                                        (const float2*)r, n, rs, s, (float2*)plo);
   else if (prec == P_F32 && p && plo && lo_prec == P_BF16)
     k_cg_p<float2, float2, bf16x2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n, rs, s,
                                                         (bf16x2*)plo);
@@ -524,12 +520,13 @@ hipError_t launch_cg_beta_p(void* p, const void* r, int prec, long n, long rs, i
   const int nbx = std::min(nb, std::max(256, nb / nrhs));
   dim3 grid(nbx, nrhs);
   if (prec == P_F64 && p)
-    k_cg_beta_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)p,
+    k_cg_beta_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)(pnext ? pnext : p),
                                                                 (const double2*)r, n, rs, s, (double2*)nullptr,
                                                                 partials, nparts);
   else if (prec == P_F32 && p && (plo == nullptr || lo_prec == P_F32))
-    k_cg_beta_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n,
-                                                             rs, s, (float2*)plo, partials, nparts);
+    k_cg_beta_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)(pnext ? pnext : p),
+                                                             (const float2*)r, n, rs, s, (float2*)plo, partials,
+                                                             nparts);
   else if (prec == P_F32 && p && plo && lo_prec == P_BF16)
     k_cg_beta_p<float2, float2, bf16x2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n,
                                                              rs, s, (bf16x2*)plo, partials, nparts);
@@ -542,19 +539,20 @@ hipError_t launch_cg_beta_p(void* p, const void* r, int prec, long n, long rs, i
   return hipGetLastError();
 }
 
-hipError_t launch_cg_xflush(float2* x, long rsx, const PWindow& pw, long n, long rs, int nrhs, const CGState* s,
-                            hipStream_t st, double2* X, long rsX) {
+hipError_t launch_cg_xflush(void* x, int xprec, long rsx, const PWindow& pw, int pprec, long n, long rs, int nrhs,
+                            const CGState* s, hipStream_t st, double2* X, long rsX) {
   dim3 grid(blas_nblocks(n), nrhs);
-  k_cg_xflush<<<grid, kB, 0, st>>>(x, rsx, pw, n, rs, s, X, rsX);
+  if (xprec == P_F64 && pprec == P_F64 && !X)
+    k_cg_xflush<double2, double2><<<grid, kB, 0, st>>>((double2*)x, rsx, pw, n, rs, s, X, rsX);
+  else if (xprec == P_F32 && pprec == P_F32)
+    k_cg_xflush<float2, float2><<<grid, kB, 0, st>>>((float2*)x, rsx, pw, n, rs, s, X, rsX);
+  else if (xprec == P_F32 && pprec == P_BF16)
+    k_cg_xflush<float2, bf16x2><<<grid, kB, 0, st>>>((float2*)x, rsx, pw, n, rs, s, X, rsX);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, int nrhs, const CGState* s,
-                          hipStream_t st) {
-  dim3 grid(blas_nblocks(n), nrhs);
-  k_ru_fold<<<grid, kB, 0, st>>>(X, rsX, xl, rsl, n, s);
-  return hipGetLastError();
-}
 hipError_t launch_ru_copy(const double2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
                           const CGState* s, hipStream_t st) {
   dim3 grid(blas_nblocks(n), nrhs);

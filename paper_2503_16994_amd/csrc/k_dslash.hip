@@ -700,10 +700,8 @@ __global__ __launch_bounds__(kHopBlock) void k_hop(const HopLaunch a) {
 
 // The last hop of a CG iteration fused with the vector update: with
 // Ap = g5 (A_ee q + 1/2 H t) computed in registers, every rhs that is not done
-// gets x += alpha p, r -= alpha Ap (x, r of type SV, p of the operator's
-// input type SI: the very vector the operator was applied to) and the
-// per-block |r|^2 partial.  Ap is never stored.  With x null the x update is
-// left to a later flush of the deferred updates.
+// gets r -= alpha Ap (r of type SV) and the per-block |r|^2 partial.  Ap is
+// never stored; x += alpha p is left to the flush of the deferred updates.
 template <typename SG, typename SI, typename SV, int NR, int RL, bool SPLIT, bool TM>
 __global__ __launch_bounds__(kHopBlock) void k_hop_xr(const HopLaunch a) {
   using A = typename StoreTraits<SG>::acc;
@@ -714,29 +712,15 @@ __global__ __launch_bounds__(kHopBlock) void k_hop_xr(const HopLaunch a) {
   ThreadSite ts;
   cpx<A> v[NR][12];
   if (!hop_thread<SG, SI, PRE_CLOV, POST_NONE, true, NR, RL, SPLIT, TM>(a, ts, v, xch)) return;
-  SV* xb = static_cast<SV*>(a.xr_x);
   SV* rb = static_cast<SV*>(a.xr_r);
-  const SI* pb = static_cast<const SI*>(a.xr_p);
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int q = ts.rhs0 + r;
     const CGState& cs = a.cg[q];
     double nrm = 0.0;
     if (ts.active && !cs.done) {
-      const double alpha_d = cs.alpha;
-      const AV alpha = (AV)alpha_d;
-      const size_t o = (size_t)q * a.xr_rs + tix(ts.s, 12) + ts.c0 * kTile,
-                   ox = (size_t)q * a.xr_xrs + tix(ts.s, 12) + ts.c0 * kTile;
-      if (xb) {  // uniform over the launch
-#pragma unroll
-        for (int k = 0; k < NC; ++k) {
-          auto pv = ld(pb + o + k * kTile);
-          auto xv = ld(xb + ox + k * kTile);
-          xv.re += (AV)alpha_d * pv.re;
-          xv.im += (AV)alpha_d * pv.im;
-          st(xb + ox + k * kTile, xv);
-        }
-      }
+      const AV alpha = (AV)cs.alpha;
+      const size_t o = (size_t)q * a.xr_rs + tix(ts.s, 12) + ts.c0 * kTile;
 #pragma unroll
       for (int k = 0; k < NC; ++k) {
         auto rv = ld(rb + o + k * kTile);
@@ -1040,22 +1024,13 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
     const size_t site = tix(s, 12) + (6 * b + col) * kTile;
     if constexpr (XR) {
       using AV = typename StoreTraits<SO>::acc;
-      SO* xb = static_cast<SO*>(a.xr_x);
       SO* rb = static_cast<SO*>(a.xr_r);
-      const SI* pb = static_cast<const SI*>(a.xr_p);
       const CGState& cs = a.cg[rhs];
       if (active && !cs.done) {
         const AV alpha = (AV)cs.alpha;
-        const size_t o = (size_t)rhs * a.xr_rs + site, ox = (size_t)rhs * a.xr_xrs + site;
+        const size_t o = (size_t)rhs * a.xr_rs + site;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-          if (xb) {
-            const auto pv = ld(pb + o + 3 * q * kTile);
-            auto xv = ld(xb + ox + 3 * q * kTile);
-            xv.re += alpha * pv.re;
-            xv.im += alpha * pv.im;
-            st(xb + ox + 3 * q * kTile, xv);
-          }
           auto rv = ld(rb + o + 3 * q * kTile);
           rv.re -= alpha * (AV)v[q].re;
           rv.im -= alpha * (AV)v[q].im;

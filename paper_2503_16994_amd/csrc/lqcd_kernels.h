@@ -73,14 +73,12 @@ struct HopLaunch {
   // filled in by the launcher
   int nbs;  // site blocks (both parities in `both` mode)
   int bpp;  // site blocks per (z, t) plane
-  // fused CG update (launch_hop_xr): x += alpha p, r -= alpha out for every
-  // rhs not done, |r|^2 partials into `partials`; out itself is not stored
-  void* xr_x;
+  // fused CG update (launch_hop_xr): r -= alpha out for every rhs not done,
+  // |r|^2 partials into `partials`; out itself is not stored (the x updates are
+  // deferred, see kXWindow)
   void* xr_r;
-  const void* xr_p;
-  int xr_prec;   // precision of x and r (p has the operator's input precision)
-  long xr_rs;    // rhs stride of r and p
-  long xr_xrs;   // rhs stride of x
+  int xr_prec;   // precision of r
+  long xr_rs;    // rhs stride of r
   const struct CGState* cg;
   // Residual in place of the result (FP64, PRE_CLOV): res - result, res like
   // out, then g5 if res_g5; written to out, or rounded to FP32 to out32, or (both
@@ -168,7 +166,7 @@ hipError_t launch_clover(const CloverLaunch& c, hipStream_t st);
 enum CGStatus { CG_RUNNING = 0, CG_CONVERGED = 1, CG_MAXITER = 2, CG_NONFINITE = 3, CG_STALLED = 4 };
 
 // CG control of one right-hand side (device memory)
-// Iterations whose x updates a BF16-operand recursion defers: their alpha
+// Iterations whose x updates an even-odd recursion defers: their alpha
 // (CGState::alpha_w) and search directions are kept, and one flush kernel
 // adds them to x at every reliable-update slot (every kXWindow-th iteration).
 constexpr int kXWindow = 5;
@@ -228,27 +226,25 @@ hipError_t launch_cg_beta(CGState* s, const double* partials, int nparts, int nr
 hipError_t launch_cg_xr(void* x, int xprec, long rsx, void* r, const void* p, const void* Ap,
                         int prec, long n, long rs, int nrhs, const CGState* s, double* partials,
                         hipStream_t st);
-// p = r + beta p, also written to p_lo (precision lo_prec) if given; with p
-// null the direction is kept in BF16 alone (r FP32): p_next = r + beta p_lo,
-// written to p_next (p_lo itself when p_next is null)
+// p_next = r + beta p (p itself when p_next is null), also written to p_lo
+// (precision lo_prec) if given; with p null the direction is kept in BF16 alone
+// (r FP32): p_next = r + beta p_lo (p_lo itself when p_next is null)
 hipError_t launch_cg_p(void* p, const void* r, int prec, long n, long rs, int nrhs,
                        const CGState* s, void* p_lo, int lo_prec, hipStream_t st, void* p_next = nullptr);
 // beta step and p update in one launch (nparts |r|^2 partials per rhs)
 hipError_t launch_cg_beta_p(void* p, const void* r, int prec, long n, long rs, int nrhs, CGState* s,
                             void* p_lo, int lo_prec, const double* partials, int nparts, hipStream_t st,
                             void* p_next = nullptr);
-// deferred x updates: x += sum_j alpha_w[j] p_j over the kXWindow BF16
-// directions p_j (slots with alpha_w[j] = 0 are not read); x FP32.  With X
-// (FP64) given, every rhs with a pending reliable update then also has x
-// folded into X and zeroed (the update's fold step).
+// deferred x updates: x += sum_j alpha_w[j] p_j over the kXWindow directions
+// p_j of precision pprec (slots with alpha_w[j] = 0 are not read).  With X
+// (FP64; x FP32) given, every rhs with a pending reliable update then also has
+// x folded into X and zeroed (the update's fold step).
 struct PWindow {
-  const bf16x2* p[kXWindow];
+  const void* p[kXWindow];
 };
-hipError_t launch_cg_xflush(float2* x, long rsx, const PWindow& pw, long n, long rs, int nrhs, const CGState* s,
-                            hipStream_t st, double2* X = nullptr, long rsX = 0);
+hipError_t launch_cg_xflush(void* x, int xprec, long rsx, const PWindow& pw, int pprec, long n, long rs, int nrhs,
+                            const CGState* s, hipStream_t st, double2* X = nullptr, long rsX = 0);
 // reliable-update kernels (each skips rhs without a pending update)
-hipError_t launch_ru_fold(double2* X, long rsX, float2* xl, long rsl, long n, int nrhs,
-                          const CGState* s, hipStream_t st);
 // rl = R (rounded to FP32) for every rhs with a pending reliable update
 hipError_t launch_ru_copy(const double2* R, long rsR, float2* rl, long rsl, long n, int nrhs,
                           const CGState* s, hipStream_t st);

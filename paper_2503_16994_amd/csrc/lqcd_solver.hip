@@ -9,9 +9,10 @@
 //   eta_hat = eta_e - D_eo A_oo^{-1} eta_o,   CG on Dhat^+ Dhat x = Dhat^+ eta_hat,
 //   psi_e = x,  psi_o = A_oo^{-1} (eta_o - D_oe psi_e),
 // and Dhat^+ = g5 Dhat g5.  One CG iteration is four hop launches (the g5 and
-// |Dhat p|^2 fused into the second), one alpha, the fused x/r update with
-// |r|^2, one beta and the p update.  All CG scalars stay on the device; the
-// host reads them once per chunk of iterations.
+// |Dhat p|^2 fused into the second, alpha into the third, r -= alpha Ap with
+// |r|^2 into the fourth) and beta with the p update; the x updates are deferred
+// over five iterations.  All CG scalars stay on the device; the host reads them
+// once per chunk of iterations.
 //
 // Stopping and reliable updates.  The target is the true relative residual
 // |eta - Dw psi|/|eta| <= tol.  The recursion runs in the inner precision.
@@ -183,10 +184,9 @@ hipError_t hop_oe_res(const Ctl& c, Vec z, Vec t_o, Vec b, Vec out, double* part
 }
 
 // fused last hop + CG update: Ap = g5 (A_ee q_e + 1/2 H t_o) in registers,
-// x += alpha p, r -= alpha Ap, |r|^2 partials (x and r in the recursion's
-// precision, p in the operator's input precision)
-hipError_t hop_oe_xr(const Ctl& c, int lprec, Vec q, Vec t_o, Vec x, Vec r, Vec p, double* partials,
-                     const CGState* cg, const int* done) {
+// r -= alpha Ap, |r|^2 partials (r in the recursion's precision)
+hipError_t hop_oe_xr(const Ctl& c, int lprec, Vec q, Vec t_o, Vec r, double* partials, const CGState* cg,
+                     const int* done) {
   HopLaunch h = mk(c, lprec);
   h.p_out = 0;
   h.in_prec = q.prec;
@@ -202,12 +202,9 @@ hipError_t hop_oe_xr(const Ctl& c, int lprec, Vec q, Vec t_o, Vec x, Vec r, Vec 
   h.g5 = true;
   h.partials = partials;
   h.done = done;
-  h.xr_x = x.p;
   h.xr_r = r.p;
-  h.xr_p = p.p;
   h.xr_prec = r.prec;
   h.xr_rs = r.rs;
-  h.xr_xrs = x.rs;
   h.cg = cg;
   return launch_hop_xr(h, c.st);
 }
@@ -461,8 +458,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   auto reliable_update = [&]() -> hipError_t {
     hipError_t e;
     if (eo) {
-      // (with deferred x updates the flush before the update has folded x)
-      if (lo && !lo16 && (e = launch_ru_fold(m.X, FRS, m.xl, HRS, 12 * V2, N, cg, st))) return e;
+      // (the flush before the update has folded a low-precision x into X)
       if ((e = hop_eo(c, P_F64, X, odd_part(TMP, V2), skip_ru, 0))) return e;
       if (lo && ru32) {
         // s rounded into FP32 scratch, Dhat^+ in the workspace's FP32 tuning,
@@ -501,43 +497,62 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   // eo: hop, hop (+g5, |Dhat p|^2), hop (+alpha), hop fused with the x/r
   // update (+|r|^2), then beta fused with the p update, or, every kRuStride-th
   // iteration, beta, the reliable-update group and the p update.
-  // With BF16 operands the x updates of kXWindow iterations are deferred: the
-  // search direction of iteration i lives in window buffer i mod kXWindow,
-  // the p update writes the next buffer, the alpha step records alpha in the
-  // same slot, and the flush before each reliable update adds all of them to
-  // x (chunks and phases start at multiples of kRuStride, so the slot of an
-  // iteration is fixed in a captured graph and every window is whole).
+  // eo: the x updates of kXWindow iterations are deferred: the search
+  // direction of iteration i lives in window buffer i mod kXWindow, the p
+  // update writes the next buffer, the alpha step records alpha in the same
+  // slot, and the flush before each reliable update adds all of them to x
+  // (chunks and phases start at multiples of kRuStride, so the slot of an
+  // iteration is fixed in a captured graph and every window is whole).  The
+  // same operations in the same order as an update in every iteration, at 1.4
+  // instead of 3 vector passes: 24^3x48 FP32 propagator 313 -> 293 ms, 12^3x24
+  // FP64 with 12 rhs 46.8 -> 44.2 ms, 16^3x32 FP64 12.6 -> 12.4 ms.
   constexpr int kRuStride = 5;
   static_assert(kRuStride == kXWindow, "x window = reliable-update stride");
   Vec pwin[kXWindow];
   PWindow pw{};
-  if (mixed && ip == LQCD_BF16 && eo) {
-    // the FP32 p and q vectors are not used by BF16-operand iterations; each
-    // holds two BF16 vectors of the same rhs stride
-    bf16x2* spare[4] = {(bf16x2*)m.pl, (bf16x2*)m.pl + (size_t)N * HRS, (bf16x2*)m.ql,
-                        (bf16x2*)m.ql + (size_t)N * HRS};
-    pwin[0] = Vec{m.pb, P_BF16, HRS};
-    for (int j = 1; j < kXWindow; ++j) pwin[j] = Vec{spare[j - 1], P_BF16, HRS};
-    for (int j = 0; j < kXWindow; ++j) pw.p[j] = (const bf16x2*)pwin[j].p;
-    // rhs that finish early leave their later slots unwritten; zeros keep the
-    // hops of partly finished rhs tiles finite
-    LQCD_HIP(launch_fill_zero(m.pl, (size_t)N * HRS * 8, st));
-    LQCD_HIP(launch_fill_zero(m.ql, (size_t)N * HRS * 8, st));
-  }
+  // The window buffers of the selected phase (slot 0 is the phase's own p),
+  // cleared: rhs that finish early leave their later slots unwritten, and
+  // zeros keep the hops of partly finished rhs tiles finite.
+  auto open_window = [&]() -> hipError_t {
+    if (!eo) return hipSuccess;
+    hipError_t e = hipSuccess;
+    pwin[0] = pin;
+    if (lo16) {
+      // the FP32 p and q vectors are not used by BF16-operand iterations; each
+      // holds two BF16 vectors of the same rhs stride
+      bf16x2* spare[4] = {(bf16x2*)m.pl, (bf16x2*)m.pl + (size_t)N * HRS, (bf16x2*)m.ql,
+                          (bf16x2*)m.ql + (size_t)N * HRS};
+      for (int j = 1; j < kXWindow; ++j) pwin[j] = Vec{spare[j - 1], P_BF16, HRS};
+      e = launch_fill_zero(m.pl, (size_t)N * HRS * 8, st);
+      if (e == hipSuccess) e = launch_fill_zero(m.ql, (size_t)N * HRS * 8, st);
+    } else if (lo) {
+      // the FP64 p is not used before the FP64 continuation, which clears it; it
+      // holds four FP32 vectors of the FP32 rhs stride
+      for (int j = 1; j < kXWindow; ++j) pwin[j] = Vec{(float2*)m.P + (size_t)(j - 1) * N * HRS, P_F32, HRS};
+      e = launch_fill_zero(m.P, full_bytes, st);
+    } else {
+      // the odd halves of the FP64 p, q, r and Ap
+      const Vec spare[4] = {P, Q, R, AP};
+      for (int j = 1; j < kXWindow; ++j) {
+        pwin[j] = odd_part(spare[j - 1], V2);
+        if (e == hipSuccess) e = launch_fill_zero_rhs((double2*)pwin[j].p, HRS, FRS, N, st);
+      }
+    }
+    for (int j = 0; j < kXWindow; ++j) pw.p[j] = pwin[j].p;
+    return e;
+  };
+  LQCD_HIP(open_window());
   auto iteration = [&](int i) -> hipError_t {
     hipError_t e;
     int nb_r;  // |r|^2 partials per rhs
     const int slot = i % kXWindow;
-    const bool win = lo16 && eo;  // deferred x updates
-    if (win) pin = pwin[slot];
     if (eo) {
+      pin = pwin[slot];
       const int nb_it = iter_parts(c, lprec);
       if ((e = hop_eo(c, lprec, pin, tin, done, nr_tile))) return e;
       if ((e = hop_oe(c, lprec, pin, tin, qin, true, parts, done, nr_tile))) return e;
-      if ((e = hop_eo(dg(c), lprec, qin, tin, done, nr_tile, cg, parts, nb_it, win ? slot : -1)))
-        return e;  // + alpha
-      if ((e = hop_oe_xr(dg(c), lprec, qin, tin, win ? Vec{nullptr, P_F32, HRS} : xi, ri, pin, parts, cg, done)))
-        return e;
+      if ((e = hop_eo(dg(c), lprec, qin, tin, done, nr_tile, cg, parts, nb_it, slot))) return e;  // + alpha
+      if ((e = hop_oe_xr(dg(c), lprec, qin, tin, ri, parts, cg, done))) return e;
       nb_r = nb_it;
     } else {
       if ((e = dw_full(c, (const double2*)pin.p, (double2*)qin.p, true, parts, done))) return e;
@@ -550,14 +565,16 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     }
     // with BF16 operands the search direction is kept in BF16 alone: the
     // recursion then updates x with the very vector the operator saw
-    void* p = lo16 ? nullptr : pi.p;
+    void* p = lo16 ? nullptr : pin.p;
     void* plo = lo16 ? pin.p : nullptr;
-    void* pnext = win ? pwin[(slot + 1) % kXWindow].p : nullptr;
+    void* pnext = eo ? pwin[(slot + 1) % kXWindow].p : nullptr;
     const int plo_prec = lo16 ? P_BF16 : P_F32;
     if ((i + 1) % kRuStride != 0)
       return launch_cg_beta_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, parts, nb_r, st, pnext);
     if ((e = launch_cg_beta(cg, parts, nb_r, N, st))) return e;
-    if (win && (e = launch_cg_xflush(m.xl, HRS, pw, n_vec, HRS, N, cg, st, m.X, FRS))) return e;
+    if (eo && (e = launch_cg_xflush(xi.p, xi.prec, xi.rs, pw, pin.prec, n_vec, pin.rs, N, cg, st, lo ? m.X : nullptr,
+                                    FRS)))
+      return e;
     if ((e = reliable_update())) return e;
     return launch_cg_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, st, pnext);
   };
@@ -668,6 +685,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     LQCD_HIP(launch_fill_zero(m.P, full_bytes, st));
     LQCD_HIP(launch_cg_escalate(cg, N, st));
     select(false);
+    LQCD_HIP(open_window());
     LQCD_HIP(reliable_update());
     LQCD_HIP(launch_cg_p(m.P, m.R, P_F64, n_vec, FRS, N, cg, nullptr, P_F32, st));
     rc = run_phase(stalled);
