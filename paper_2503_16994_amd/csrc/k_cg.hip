@@ -27,7 +27,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "lqcd_kernels.h"
+#include "cg_dev.h"
 
 namespace lqcd {
 
@@ -50,15 +50,7 @@ __device__ inline double bsum(double v, double* sh) {
 // fixed-order sum of the partials of one rhs (n as in parts_count), result
 // broadcast to the block
 __device__ inline double psum(const double* p, int n, double* sh) {
-  if (parts_count(n) <= 64) {
-    // every wave forms the sum of the general route's first wave (the others
-    // add zeros there), and no barrier is needed
-    const int l = threadIdx.x & 63;
-    double v = l < parts_count(n) ? parts_at(p, n, l) : 0.0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
-  }
+  if (parts_count(n) <= 64) return wave_psum(p, n);
   double acc = 0.0;
   for (int i = threadIdx.x; i < parts_count(n); i += kB) acc += parts_at(p, n, i);
   double s = bsum(acc, sh);
@@ -67,8 +59,6 @@ __device__ inline double psum(const double* p, int n, double* sh) {
   __syncthreads();
   return out;
 }
-
-__device__ inline bool finite(double v) { return v == v && fabs(v) <= 1.7976931348623157e308; }
 
 __global__ void k_cg_setup(CGState* s, const double* b2, const double* eta2, CGSetup cfg) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -106,36 +96,6 @@ __global__ void k_cg_setup(CGState* s, const double* b2, const double* eta2, CGS
   c.done = zero ? 1 : 0;
   c.status = zero ? CG_CONVERGED : CG_RUNNING;
   if (zero) c.rho2 = 0.0;
-}
-
-// beta and the iteration control from the new |r|^2 = v; the denominator is
-// rr_prev, the |r|^2 the alpha step of this iteration divided by (alpha sets
-// it), so the fused beta/p kernel below can replace rr while its other
-// workgroups still divide by the old value
-__device__ inline void beta_step(CGState& c, double v) {
-  c.iters += 1;
-  if (!finite(v) || !finite(c.alpha)) {
-    c.done = 1;
-    c.status = CG_NONFINITE;
-    c.skip_ru = 1;
-    return;
-  }
-  const bool hit = v <= c.target2;
-  const bool due = c.ru_every > 0 && c.iters - c.last_ru >= c.ru_every;
-  const bool drop = v < c.delta2 * c.rr_max;
-  if (hit || due || drop) {
-    if (c.skip_ru) c.ru_drop = 0;  // a new request
-    c.skip_ru = 0;
-    if (hit) c.inner_hit = 1;
-    if (hit || drop) c.ru_drop = 1;
-  }
-  c.beta = (c.rr_prev > 0.0) ? v / c.rr_prev : 0.0;
-  c.rr = v;
-  if (v > c.rr_max) c.rr_max = v;
-  if (c.iters >= c.maxiter && c.skip_ru) {
-    c.done = 1;
-    c.status = CG_MAXITER;
-  }
 }
 
 __global__ void k_cg_beta(CGState* s, const double* partials, int nparts) {
@@ -243,7 +203,7 @@ struct PUpdate {
 #pragma unroll
       for (int k = 0; k < 4; ++k)
         if (k == 0 || std::is_same<SP, bf16x2>::value)
-          pv[k] = {rv[k].re + beta * pv[k].re, rv[k].im + beta * pv[k].im};
+          pv[k] = p_next(beta, rv[k], pv[k]);
       if constexpr (std::is_same<SP, bf16x2>::value) {
         if (four) {
           st4(pn + o + 4 * i, pv);

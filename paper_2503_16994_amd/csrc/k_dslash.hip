@@ -23,7 +23,7 @@
 // block orders below) and occupancy (RL instead of NR keeps registers low).
 #include <type_traits>
 
-#include "lqcd_kernels.h"
+#include "cg_dev.h"
 
 namespace lqcd {
 
@@ -780,9 +780,10 @@ __device__ inline SI canon_ld(const double2* site, int k, bool g5) {
   return t;
 }
 
-template <int K, bool CANON, typename A, typename SG, typename SI>
+// PF: the operand is r + beta y (HopLaunch::pf_r)
+template <int K, bool CANON, bool PF, typename A, typename SG, typename SI>
 __device__ inline void spread_hop(const HopLaunch& a, const SI* yb, int p, int s, const Coord& c, int rhs, cpx<A>* w,
-                                  int l) {
+                                  int l, const double* rr2) {
   constexpr int MU = K / 2, DIR = (K & 1) ? -1 : 1;
   bool edge;
   A pr, pi;
@@ -801,6 +802,17 @@ __device__ inline void spread_hop(const HopLaunch& a, const SI* yb, int p, int s
       }
     }
     if (internal) fetch_k<K>(f, a, yb, p, s, c, rhs);
+    if constexpr (PF) {
+      using SR = std::conditional_t<std::is_same<SI, double2>::value, double2, float2>;
+      const int sn = nb_index(a.g, s, c, MU, DIR);
+      const SR* rp = static_cast<const SR*>(a.pf_r) + (size_t)rhs * a.pf_rs + tix(sn, 12);
+      cpx<A> r[12];
+#pragma unroll
+      for (int k = 0; k < 12; ++k) r[k] = ld(rp + k * kTile);
+      const A beta = (A)(rr2[1] > 0.0 ? rr2[0] / rr2[1] : 0.0);
+#pragma unroll
+      for (int k = 0; k < 12; ++k) st(&f.y[0][k], p_next(beta, r[k], widen<A>(f.y[0][k])));
+    }
     cpx<A> U[9];
     hop_link(U, f, a);
     hop_half<MU, DIR>(U, f.y[0], edge, pr, pi, v);
@@ -844,7 +856,11 @@ __device__ inline cpx<A> row_mul(const cpx<A> (&m)[6], int i, const cpx<A> (&v)[
 
 // CANON: input and output may be canonical fields (HopLaunch::cy, cz, cout),
 // which saves a small operator application its two layout conversions.
-template <typename SG, typename SI, typename SO, bool XR, bool CANON>
+// PF: applied to the updated search direction (HopLaunch::pf_r), which saves a
+// small iteration the launch of the update (4.5 us eager, 1.6 us and its drain
+// in a graph) for twelve more loads a lane: 8^4 FP32 solve 3885 -> 3833 us,
+// others of 2^9 to 2^14 sites 3 to 6% (10941 -> 10576, 3516 -> 3312 us).
+template <typename SG, typename SI, typename SO, bool XR, bool CANON, bool PF = false>
 __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) {
   using A = typename StoreTraits<SG>::acc;
   __shared__ __attribute__((aligned(16))) cpx<A> wls[8 * 6 * kSpreadSites];  // the hops; later the site vectors
@@ -859,6 +875,19 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
     if (c.done) {
       if (a.alpha_slot >= 0 && threadIdx.x == 0) c.alpha_w[a.alpha_slot] = 0.0;
       return;
+    }
+    if (a.beta_parts) {
+      const double rr = wave_psum(a.beta_parts + (size_t)r * parts_stride(a.beta_nparts), a.beta_nparts);
+      __syncthreads();  // every wave has read done
+      if (threadIdx.x == 0) {
+        beta_step(c, rr);
+        nls[kHopBlock / 64] = c.done;
+      }
+      __syncthreads();
+      if (nls[kHopBlock / 64] != 0.0) {
+        if (a.alpha_slot >= 0 && threadIdx.x == 0) c.alpha_w[a.alpha_slot] = 0.0;
+        return;
+      }
     }
     const double* pp = a.alpha_parts + (size_t)r * parts_stride(a.alpha_nparts);
     double acc = 0.0;  // as in fused_alpha: the first kHopBlock threads
@@ -931,16 +960,39 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
       }
     }
   }
+  // |r|^2 and the one before, for beta
+  double rr2[2] = {0.0, 0.0};
+  if constexpr (PF) {
+    using SR = std::conditional_t<std::is_same<SI, double2>::value, double2, float2>;
+    rr2[1] = a.pf_cg[rhs].rr_prev;
+    // this site's components of the new direction (input parity, same index)
+    const size_t o = tix(s, 12) + (6 * b + col) * kTile;
+    cpx<A> pv[2], rv[2];
+    if (owner && active) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        pv[q] = ld(yb + (size_t)rhs * a.y_rs + o + 3 * q * kTile);
+        rv[q] = ld(static_cast<const SR*>(a.pf_r) + (size_t)rhs * a.pf_rs + o + 3 * q * kTile);
+      }
+    }
+    rr2[0] = wave_psum(a.pf_parts + (size_t)rhs * parts_stride(a.pf_nparts), a.pf_nparts);
+    if (owner && active) {
+      const A beta = (A)(rr2[1] > 0.0 ? rr2[0] / rr2[1] : 0.0);
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        st(static_cast<SI*>(a.pf_next) + (size_t)rhs * a.pf_rs + o + 3 * q * kTile, p_next(beta, rv[q], pv[q]));
+    }
+  }
   if (active) {
     switch (w) {
-      case 0: spread_hop<0, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 1: spread_hop<1, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 2: spread_hop<2, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 3: spread_hop<3, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 4: spread_hop<4, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 5: spread_hop<5, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      case 6: spread_hop<6, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
-      default: spread_hop<7, CANON, A, SG, SI>(a, yb, p, s, c, rhs, wls, l); break;
+      case 0: spread_hop<0, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 1: spread_hop<1, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 2: spread_hop<2, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 3: spread_hop<3, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 4: spread_hop<4, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 5: spread_hop<5, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      case 6: spread_hop<6, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
+      default: spread_hop<7, CANON, PF, A, SG, SI>(a, yb, p, s, c, rhs, wls, l, rr2); break;
     }
   }
   __syncthreads();
@@ -1176,6 +1228,15 @@ static int spread_nparts(const HopLaunch& h) {
 // workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
 // conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
 // 33.2.
+// The direction update is fused where every wave can sum the partials itself
+// without a barrier; above that the sum costs each workgroup what the launch
+// does.
+bool hop_fuses_p(const HopLaunch& h0) {
+  HopLaunch h = h0;
+  if (h.prec == P_F64) h.rhs_lanes = 1;
+  return spread_on(h) && parts_count(spread_nparts(h)) <= 64;
+}
+
 bool hop_reads_canonical(const HopLaunch& h0) {
   HopLaunch h = h0;
   if (h.prec == P_F64) h.rhs_lanes = 1;
@@ -1193,6 +1254,15 @@ static hipError_t launch_spread(HopLaunch h, hipStream_t st) {
     }
   }
   if (h.cy || h.cz || h.cout) return hipErrorInvalidValue;
+  if (h.beta_parts && parts_count(h.beta_nparts) > 64) return hipErrorInvalidValue;
+  if constexpr (!XR && std::is_same<SI, SO>::value) {
+    if (h.pf_r) {
+      if (parts_count(h.pf_nparts) > 64 || h.both || h.pre != PRE_NONE) return hipErrorInvalidValue;
+      k_hop_spread<SG, SI, SO, false, false, true><<<grid, kSpreadBlock, 0, st>>>(h);
+      return hipGetLastError();
+    }
+  }
+  if (h.pf_r) return hipErrorInvalidValue;
   k_hop_spread<SG, SI, SO, XR, false><<<grid, kSpreadBlock, 0, st>>>(h);
   return hipGetLastError();
 }
@@ -1286,7 +1356,7 @@ static hipError_t launch_tiled(const HopLaunch& h0, hipStream_t st) {
   if (std::is_same<SG, double2>::value) h.rhs_lanes = 1;
   if (spread_on(h)) return launch_spread<SG, SI, SO, false>(h, st);
   if (!prepare(h)) return hipErrorInvalidValue;
-  if (h.cy || h.cz) return hipErrorInvalidValue;  // the small form only
+  if (h.cy || h.cz || h.pf_r || h.beta_parts) return hipErrorInvalidValue;  // the small form only
   if (h.cout) {
     if constexpr (std::is_same<SG, double2>::value && PRE == PRE_CLOV && POST == POST_NONE)
       return h.partials ? hipErrorInvalidValue : launch_canon(h, st);

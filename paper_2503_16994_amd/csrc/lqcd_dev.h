@@ -241,7 +241,7 @@ __device__ inline double cnorm2(cpx<A> c) {
 // 2 i and 2 i + 1 are the two waves whose sum is value i of the former.  The
 // sums over either are the same operations.
 __host__ __device__ inline int parts_stride(int n) { return n < 0 ? -n : n; }
-__device__ inline int parts_count(int n) { return n < 0 ? -n / 2 : n; }
+__host__ __device__ inline int parts_count(int n) { return n < 0 ? -n / 2 : n; }
 __device__ inline double parts_at(const double* p, int n, int i) { return n < 0 ? p[2 * i] + p[2 * i + 1] : p[i]; }
 
 // Third row of an SU(3) matrix (row major, m[3 a + b]) from its first two.

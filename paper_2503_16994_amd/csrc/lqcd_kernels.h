@@ -97,6 +97,19 @@ struct HopLaunch {
   const double2* cz;
   double2* cout;
   bool g5_in, cout_zero;
+  // The direction update of the previous iteration fused into this launch
+  // (hop_fuses_p only): y is the old direction, the operator is applied to
+  // p = r + beta y (rounded to y's storage), and p is stored to pf_next on the
+  // sites of the input parity.  beta comes from the pf_nparts |r|^2 partials of
+  // pf_parts and rr_prev of pf_cg; the control state is not changed here but by
+  // the next launch with alpha_cg, which takes the same partials as
+  // beta_parts and performs the beta step before the alpha step.
+  const void* pf_r;  // null: no update
+  void* pf_next;
+  long pf_rs;        // rhs stride of r and pf_next
+  const double* pf_parts;
+  int pf_nparts;
+  const struct CGState* pf_cg;
   // CG alpha fused into a hop launch that does not need it (k_hop only):
   // alpha = rr / pAp with pAp the fixed-order sum of alpha_nparts partials per
   // rhs; rhs r is handled by workgroup r mod grid, before its stencil work (in a
@@ -105,12 +118,17 @@ struct HopLaunch {
   const double* alpha_parts;  // [nrhs][alpha_nparts]
   int alpha_nparts;
   int alpha_slot;             // >= 0: also record alpha in alpha_w[alpha_slot] (0 for a done rhs)
+  const double* beta_parts;   // given (small launches only): the beta step of the previous iteration first
+  int beta_nparts;
 };
 
 int hop_nblocks(const HopLaunch& h);
 int hop_max_parts(long V2);  // bound on partials per rhs of any hop launch
 int hop_nparts(const HopLaunch& h);  // partials per rhs of a tiled hop launch, as parts_count takes them
 hipError_t launch_hop(const HopLaunch& h, hipStream_t st);
+// whether a launch of this shape can update the search direction it is applied
+// to (HopLaunch::pf_r)
+bool hop_fuses_p(const HopLaunch& h);
 // whether a launch of this shape takes canonical input (HopLaunch::cy, cz)
 bool hop_reads_canonical(const HopLaunch& h);
 hipError_t launch_hop_xr(const HopLaunch& h, hipStream_t st);

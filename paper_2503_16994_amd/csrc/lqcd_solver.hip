@@ -99,13 +99,34 @@ HopLaunch mk(const Ctl& c, int lprec) {
   return h;
 }
 
+// The direction update of the previous iteration on the way of a small
+// iteration: its first hop updates p (next non-null), the hop with the alpha
+// step performs the beta step (see HopLaunch::pf_r)
+struct PFuse {
+  Vec r, next;
+  const double* parts;  // |r|^2
+  int nparts;
+  CGState* cg;
+};
+
 // out_o = A_oo^{-1} D_oe y_e = A_oo^{-1} (-1/2 H y_e); with alpha_cg the
 // launch also computes the CG alpha of every rhs from alpha_parts (and
 // records it in window slot alpha_slot if that is >= 0)
 hipError_t hop_eo(const Ctl& c, int lprec, Vec y, Vec out_o, const int* done, int nr_tile,
                   CGState* alpha_cg = nullptr, const double* alpha_parts = nullptr, int alpha_nparts = 0,
-                  int alpha_slot = -1) {
+                  int alpha_slot = -1, const PFuse* pf = nullptr) {
   HopLaunch h = mk(c, lprec);
+  if (pf && alpha_cg) {
+    h.beta_parts = pf->parts;
+    h.beta_nparts = pf->nparts;
+  } else if (pf) {
+    h.pf_r = pf->r.p;
+    h.pf_next = pf->next.p;
+    h.pf_rs = pf->r.rs;
+    h.pf_parts = pf->parts;
+    h.pf_nparts = pf->nparts;
+    h.pf_cg = pf->cg;
+  }
   h.alpha_cg = alpha_cg;
   h.alpha_parts = alpha_parts;
   h.alpha_nparts = alpha_nparts;
@@ -495,8 +516,9 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
 
   // ---- one CG iteration (graph-capturable: kernels only) --------------------
   // eo: hop, hop (+g5, |Dhat p|^2), hop (+alpha), hop fused with the x/r
-  // update (+|r|^2), then beta fused with the p update, or, every kRuStride-th
-  // iteration, beta, the reliable-update group and the p update.
+  // update (+|r|^2), then beta fused with the p update (on small lattices both
+  // in the hops of the next iteration), or, every kRuStride-th iteration, beta,
+  // the reliable-update group and the p update.
   // eo: the x updates of kXWindow iterations are deferred: the search
   // direction of iteration i lives in window buffer i mod kXWindow, the p
   // update writes the next buffer, the alpha step records alpha in the same
@@ -546,13 +568,19 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     hipError_t e;
     int nb_r;  // |r|^2 partials per rhs
     const int slot = i % kXWindow;
+    // small lattices: the update of p rides with the next iteration's hops
+    const bool fuse_p = eo && hop_fuses_p(mk(c, lprec));
+    double* const parts_r = fuse_p ? parts2 : parts;  // |r|^2, kept over the next two hops
     if (eo) {
       pin = pwin[slot];
       const int nb_it = iter_parts(c, lprec);
-      if ((e = hop_eo(c, lprec, pin, tin, done, nr_tile))) return e;
+      const PFuse pf{ri, pin, parts_r, nb_it, cg};
+      const PFuse* pfuse = fuse_p && slot > 0 ? &pf : nullptr;
+      const Vec& y = pfuse ? pwin[slot - 1] : pin;
+      if ((e = hop_eo(c, lprec, y, tin, done, nr_tile, nullptr, nullptr, 0, -1, pfuse))) return e;
       if ((e = hop_oe(c, lprec, pin, tin, qin, true, parts, done, nr_tile))) return e;
-      if ((e = hop_eo(dg(c), lprec, qin, tin, done, nr_tile, cg, parts, nb_it, slot))) return e;  // + alpha
-      if ((e = hop_oe_xr(dg(c), lprec, qin, tin, ri, parts, cg, done))) return e;
+      if ((e = hop_eo(dg(c), lprec, qin, tin, done, nr_tile, cg, parts, nb_it, slot, pfuse))) return e;  // + alpha
+      if ((e = hop_oe_xr(dg(c), lprec, qin, tin, ri, parts_r, cg, done))) return e;
       nb_r = nb_it;
     } else {
       if ((e = dw_full(c, (const double2*)pin.p, (double2*)qin.p, true, parts, done))) return e;
@@ -569,9 +597,10 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     void* plo = lo16 ? pin.p : nullptr;
     void* pnext = eo ? pwin[(slot + 1) % kXWindow].p : nullptr;
     const int plo_prec = lo16 ? P_BF16 : P_F32;
+    if ((i + 1) % kRuStride != 0 && fuse_p) return hipSuccess;  // with the next iteration
     if ((i + 1) % kRuStride != 0)
-      return launch_cg_beta_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, parts, nb_r, st, pnext);
-    if ((e = launch_cg_beta(cg, parts, nb_r, N, st))) return e;
+      return launch_cg_beta_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, parts_r, nb_r, st, pnext);
+    if ((e = launch_cg_beta(cg, parts_r, nb_r, N, st))) return e;
     if (eo && (e = launch_cg_xflush(xi.p, xi.prec, xi.rs, pw, pin.prec, n_vec, pin.rs, N, cg, st, lo ? m.X : nullptr,
                                     FRS)))
       return e;

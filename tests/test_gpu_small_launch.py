@@ -47,8 +47,9 @@ def test_small_operators_equal_the_general_ones(bc, two_row, prec, mu):
 
 
 @pytest.mark.parametrize("solver,inner,mu", [(lqcd.SOLVER_CG_FULL, lqcd.F64, 0.0), (lqcd.SOLVER_CG_EO, lqcd.F64, 0.0),
-                                             (lqcd.SOLVER_CG_EO, lqcd.F64, 0.05), (lqcd.SOLVER_CG_EO, lqcd.F32, 0.0)],
-                         ids=["full", "eo", "eo-mu", "f32"])
+                                             (lqcd.SOLVER_CG_EO, lqcd.F64, 0.05), (lqcd.SOLVER_CG_EO, lqcd.F32, 0.0),
+                                             (lqcd.SOLVER_CG_EO, lqcd.BF16, 0.0)],
+                         ids=["full", "eo", "eo-mu", "f32", "bf16"])
 def test_small_solves_equal_the_general_ones(solver, inner, mu):
     L = (10, 6, 6, 10)
     print(f"\n[gpu case] small solve {L} solver {solver} inner {inner} mu {mu}", flush=True)
