@@ -129,20 +129,28 @@ struct HopSpec {
 //    launch, so ordinary loads beat non-temporal ones; one rhs of a larger
 //    lattice streams them once and keeps the non-temporal ones.
 //  * rhs per thread: one while the launch needs its threads to hide latency,
-//    two (or three for a multiple of three, or an odd n) once there are enough.
-//  * From 10^6 sites on, z-slabs per XCD.
+//    two (or three for an odd n, in FP32 for any multiple of three) once there
+//    are enough.
+//  * From 10^6 sites on, z-slabs per XCD; in FP64 with several rhs from 10^6
+//    sites times rhs on.
 // Measured, us per pair of hops, non-temporal loads and one rhs per thread
 // against this choice: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
-// 4 rhs 136 / 98, 12 rhs 391 / 299, 24^3x48 12 rhs 2632 / 1707, 32^3x64 1 rhs
-// 753 / 645, 12 rhs 7936 / 4119; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
+// 4 rhs 136 / 98, 12 rhs 391 / 295, 24^3x48 12 rhs 2632 / 1701, 32^3x64 1 rhs
+// 753 / 645, 12 rhs 7936 / 4379; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
 // / 113, 32^3x64 12 rhs 4076 / 2395; BF16 32^3x64 12 rhs 1533 / 1188.
+// The slabs and tiles of FP64 batches, us per canonical Dw / per four hops of the
+// Schur normal operator, plain order against slabs at two rhs per thread:
+// 16^3x32 4 rhs 154 / 275 and 150 / 285, 8 rhs 281 / 526 and 273 / 511, 12 rhs
+// 410 / 762 and 389 / 732; 32^3x64 12 rhs, slabs at three and two rhs per thread:
+// 7194 / 11236 and 6937 / 10882.
 inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
   constexpr int kCached = LQCD_TUNE_NT_STORE | LQCD_TUNE_CACHED_GAUGE, kStream = LQCD_TUNE_NT_STORE;
   const int64_t vn = V * n, large = 1000000;
   lqcd_tuning t = {1, 1, 1, 0};
   if (V >= large) {
     t.block_order = 2;
-    if (n > 1) t.nr_tile = (n % 3 == 0 && prec != LQCD_BF16) || n == 3 ? 3 : 2;
+    const bool three = n % 3 == 0 && (prec == LQCD_F32 || (prec == LQCD_F64 && n % 2 != 0));
+    if (n > 1) t.nr_tile = three || n == 3 ? 3 : 2;
   }
   if (prec == LQCD_BF16) {
     if (n >= 4 && vn >= 390000) t.nr_tile = 2;
@@ -152,7 +160,10 @@ inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
     if (!fits && n > 1) t.nr_tile = n;
   } else {
     t.flags = kCached;
-    if (V < large && vn >= (prec == LQCD_F64 ? 1200000 : 360000)) t.nr_tile = 2;
+    if (V < large && vn >= (prec == LQCD_F64 ? large : 360000)) {
+      t.nr_tile = 2;
+      if (prec == LQCD_F64) t.block_order = 2;
+    }
   }
   return t;
 }
