@@ -15,16 +15,22 @@
 // (clover_inv.h); a block that is singular to working precision is reported
 // as a numerical error.
 //
-// Work decomposition: a workgroup of six waves owns the 64 sites of one
-// layout tile.  Wave p computes the field strength of plane p (a lane per
-// site) and leaves its nine independent reals in LDS; then wave b < 2
-// assembles, stores and inverts the blocks of chirality b.  One thread per
-// site doing all of it keeps six 3x3 matrices, four leaves and two 6x6 blocks
-// alive: that needed 9 KB of scratch per lane and took 9.2 ms at 32^3x64 (3.26
-// ms at 24^3x48, three precisions stored); this takes 1.88 ms (0.69 ms).
-// Bound: the links through L2 (twelve per plane and site) and FP64 issue.
-// Three waves per SIMD (two workgroups per CU) at the price of 28 spilled
-// registers measure 687 us at 24^3x48, two waves without spills 711 us.
+// Work decomposition: a workgroup of W waves owns the 64 sites of one layout
+// tile.  Each wave computes the field strength of 6/W planes, one after the
+// other (a lane per site), and leaves the nine independent reals of each in LDS;
+// then wave b < 2 assembles, stores and inverts the blocks of chirality b.  One
+// thread per site doing all of it keeps six 3x3 matrices, four leaves and two
+// 6x6 blocks alive: that needed 9 KB of scratch per lane and took 3.26 ms at
+// 24^3x48 with three precisions stored.
+// Bound: the links through L2 (twelve per plane and site), and their latency:
+// with W = 6 four of six waves end at the barrier while the last two hold the
+// workgroup's place, and only 1.5 waves per SIMD are resident on average.  W = 2
+// keeps every wave to the end: 24^3x48 (two rows, FP64 stored) 664 -> 538 us, and
+// with the tile order below and stores past L2 455.  W = 6 is the shorter chain
+// while the chip is not full: a changed operator and its Dw at 12x10x8x14 (210
+// workgroups) 53 us with W = 6, 58 with 2; 12^3x24 (648) 93 and 86; 32^3x64 2707
+// and 2172.  Two waves per SIMD: at three, 25 to 36 registers spill (W = 2: 598
+// against 495 us).
 #include "clover_inv.h"
 #include "lqcd_kernels.h"
 
@@ -32,7 +38,18 @@ namespace lqcd {
 
 using cd = cpx<double>;
 
-constexpr int kCloverPlanes = 6;  // xy, xz, xt, yz, yt, zt: one wave each
+constexpr int kCloverPlanes = 6;  // xy, xz, xt, yz, yt, zt
+constexpr int kCloverWide = 512;  // from this many workgroups on, two waves each
+
+// Tile order.  In site order every XCD walks whole time slices, and from some
+// 10^4 sites a slice its t neighbours have left its L2 when it returns to them.
+// Here a time slice is a row of tiles (about: tiles may straddle slices, which
+// only costs locality), cut into column groups of at most kGroupTiles tiles, a
+// multiple of eight groups; an XCD walks one group through all rows, then the
+// next.  24^3x48 538 -> 495 us; a changed operator and its Dw at 32^3x64 2314 ->
+// 2172 us, 16^3x32 166 both; groups of 8, 16 and 32 tiles 503, 471 and 476 us.
+constexpr int kRowTiles = 32;  // tiles per slice from which the order is used
+constexpr int kGroupTiles = 16;
 
 struct M3 {
   cd m[9];
@@ -122,32 +139,20 @@ __device__ inline M3 field_strength(const KGeom& g, const double2* U, const Coor
     return x == 0 ? last * stride : -stride;
   };
   const int fm = step(mu, 1), bm = step(mu, -1), fn = step(nu, 1), bn = step(nu, -1);
-  // The fence keeps the scheduler from hoisting every load to the front: all
-  // twelve links would be live at once and spill.
 #define LNK(off, par, d) load_link<TWO_ROW>(g, U, lex + (off), (par), (d))
-#define FENCE __builtin_amdgcn_sched_barrier(0)
   const M3 Un_x = LNK(0, p, nu);
   M3 A = m3_mul_nd(LNK(fm, 1 - p, nu), LNK(fn, 1 - p, mu));
-  FENCE;
   A = m3_mul_nd(A, Un_x);
   M3 B = m3_mul_dn(LNK(bn, 1 - p, nu), LNK(bn, 1 - p, mu));
-  FENCE;
   B = m3_mul(B, LNK(fm + bn, p, nu));
-  FENCE;
   A = m3_mul(LNK(0, p, mu), m3_sub_dag(A, B));
-  FENCE;
   B = m3_mul_nd(Un_x, LNK(bm + fn, p, mu));
-  FENCE;
   M3 C = m3_mul_nd(B, LNK(bm, 1 - p, nu));
-  FENCE;
   B = m3_mul(LNK(bm + bn, p, mu), LNK(bn, 1 - p, nu));
-  FENCE;
   B = m3_mul_dn(B, LNK(bm + bn, p, nu));
 #pragma unroll
   for (int e = 0; e < 9; ++e) C.m[e] = csub(C.m[e], B.m[e]);
-  FENCE;
   C = m3_mul(C, LNK(bm, 1 - p, mu));
-#undef FENCE
 #undef LNK
   M3 F;
 #pragma unroll
@@ -215,35 +220,50 @@ __device__ inline void make_block(const AH3& E1, const AH3& E2, const AH3& E3, d
 template <typename S>
 __device__ inline void store_packed(S* field, size_t s, int c0, const cd (&B)[6][6]) {
   S* base = field + tix(s, 36) + c0 * kTile;
-  st(base + 0 * kTile, cd{B[0][0].re, B[1][1].re});
-  st(base + 1 * kTile, cd{B[2][2].re, B[3][3].re});
-  st(base + 2 * kTile, cd{B[4][4].re, B[5][5].re});
+  st_nt(base + 0 * kTile, cd{B[0][0].re, B[1][1].re});
+  st_nt(base + 1 * kTile, cd{B[2][2].re, B[3][3].re});
+  st_nt(base + 2 * kTile, cd{B[4][4].re, B[5][5].re});
 #pragma unroll
   for (int i = 1; i < 6; ++i)
 #pragma unroll
-    for (int j = 0; j < i; ++j) st(base + tri_index(i, j) * kTile, B[i][j]);
+    for (int j = 0; j < i; ++j) st_nt(base + tri_index(i, j) * kTile, B[i][j]);
 }
 
-template <bool TWO_ROW>
-__global__ __launch_bounds__(64 * kCloverPlanes, 3) void k_clover(const CloverLaunch c) {
+template <bool TWO_ROW, int W>
+__global__ __launch_bounds__(64 * W, 2) void k_clover(const CloverLaunch c) {
   __shared__ double sh[kCloverPlanes][9][kTile];
   const KGeom& g = c.g;
-  // the two parities of a tile side by side, each XCD a contiguous range
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int p = blk & 1, l = threadIdx.x & 63;
+  // the two parities of a tile side by side
+  int tile, p;
+  if (c.groups > 0) {
+    const int j = (int)(blockIdx.x >> 3), per = 2 * c.rows * c.cols;  // workgroups of a group
+    const int grp = (int)(blockIdx.x & 7) + 8 * (j / per), i = (j % per) >> 1;
+    const int col = (int)((long)grp * c.row_tiles / c.groups) + i % c.cols;
+    if (col >= (int)((long)(grp + 1) * c.row_tiles / c.groups)) return;
+    tile = i / c.cols * c.row_tiles + col;
+    p = j & 1;
+  } else {
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    tile = blk >> 1;
+    p = blk & 1;
+  }
+  const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int s = (blk >> 1) * kTile + l;
+  const int s = tile * kTile + l;
   const Coord co = site_coord(g, s < g.V2 ? s : 0, p);
   if (s < g.V2) {
-    const int mu = w < 3 ? 0 : (w < 5 ? 1 : 2);
-    const int nu = w < 3 ? w + 1 : (w < 5 ? w - 1 : 3);
-    const M3 F = field_strength<TWO_ROW>(g, c.U64, co, 2 * s + (co.x & 1), p, mu, nu);
+#pragma unroll 1
+    for (int q = w * (kCloverPlanes / W); q < (w + 1) * (kCloverPlanes / W); ++q) {
+      const int mu = q < 3 ? 0 : (q < 5 ? 1 : 2);
+      const int nu = q < 3 ? q + 1 : (q < 5 ? q - 1 : 3);
+      const M3 F = field_strength<TWO_ROW>(g, c.U64, co, 2 * s + (co.x & 1), p, mu, nu);
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      sh[w][i][l] = F.m[4 * i].im;
-      const cd v = F.m[i == 0 ? 3 : 5 + i];  // (1,0), (2,0), (2,1)
-      sh[w][3 + 2 * i][l] = v.re;
-      sh[w][4 + 2 * i][l] = v.im;
+      for (int i = 0; i < 3; ++i) {
+        sh[q][i][l] = F.m[4 * i].im;
+        const cd v = F.m[i == 0 ? 3 : 5 + i];  // (1,0), (2,0), (2,1)
+        sh[q][3 + 2 * i][l] = v.re;
+        sh[q][4 + 2 * i][l] = v.im;
+      }
     }
   }
   __syncthreads();
@@ -310,9 +330,9 @@ __global__ __launch_bounds__(64 * kCloverPlanes, 3) void k_clover(const CloverLa
   blk6::NormBound rb;
   const size_t base = tix((size_t)s, 36) + 18 * b * kTile;
   auto put = [&](int e, cd v) {
-    st(c.Ci64 + base + e * kTile, v);
-    if (c.Ci32) st(c.Ci32 + base + e * kTile, v);
-    if (c.Ci16) st(c.Ci16 + base + e * kTile, v);
+    st_nt(c.Ci64 + base + e * kTile, v);
+    if (c.Ci32) st_nt(c.Ci32 + base + e * kTile, v);
+    if (c.Ci16) st_nt(c.Ci16 + base + e * kTile, v);
   };
   double diag[6];
   const bool ldl = blk6::inverse_ldl_each(B, [&](int i, int j, cd v) {
@@ -333,12 +353,30 @@ __global__ __launch_bounds__(64 * kCloverPlanes, 3) void k_clover(const CloverLa
   }
 }
 
-hipError_t launch_clover(const CloverLaunch& c, hipStream_t st) {
-  const unsigned grid = 2u * (unsigned)((c.g.V2 + kTile - 1) / kTile);
+template <int W>
+static void launch_clover_w(const CloverLaunch& c, unsigned grid, hipStream_t st) {
   if (c.two_row)
-    k_clover<true><<<grid, 64 * kCloverPlanes, 0, st>>>(c);
+    k_clover<true, W><<<grid, 64 * W, 0, st>>>(c);
   else
-    k_clover<false><<<grid, 64 * kCloverPlanes, 0, st>>>(c);
+    k_clover<false, W><<<grid, 64 * W, 0, st>>>(c);
+}
+
+hipError_t launch_clover(const CloverLaunch& c0, hipStream_t st) {
+  CloverLaunch c = c0;
+  const int tiles = (int)((c.g.V2 + kTile - 1) / kTile);
+  unsigned grid = 2u * (unsigned)tiles;
+  c.row_tiles = (int)((c.g.V2 / c.g.L[3] + kTile - 1) / kTile);
+  c.groups = 0;
+  if (c.row_tiles >= kRowTiles) {
+    c.groups = 8 * ((c.row_tiles + 8 * kGroupTiles - 1) / (8 * kGroupTiles));
+    c.rows = (tiles + c.row_tiles - 1) / c.row_tiles;
+    c.cols = (c.row_tiles + c.groups - 1) / c.groups;
+    grid = (unsigned)c.groups * 2u * (unsigned)c.rows * (unsigned)c.cols;
+  }
+  if (2 * tiles < kCloverWide)
+    launch_clover_w<6>(c, grid, st);
+  else
+    launch_clover_w<2>(c, grid, st);
   return hipGetLastError();
 }
 

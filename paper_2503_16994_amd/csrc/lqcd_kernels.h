@@ -175,6 +175,9 @@ struct CloverLaunch {
   bf16x2* C16;
   bf16x2* Ci16;
   int* err_flag;
+  // set by launch_clover: rows of row_tiles tiles, cut into column groups of at
+  // most cols tiles (groups 0: the tiles in order)
+  int row_tiles, groups, rows, cols;
 };
 hipError_t launch_clover(const CloverLaunch& c, hipStream_t st);
 

@@ -1,6 +1,8 @@
 """GPU parity on lattices smaller than, or not a multiple of, the 64-site pieces
 that the import, clover and hop kernels work in: extents of 2 (both neighbours
-of a site in a direction are the same site), V = 32, 48, 240 and 720.
+of a site in a direction are the same site), V = 32, 48, 240 and 720.  The last
+two have time slices of 38.5 and 137.3 pieces, which the clover kernel's tile
+order cuts into 8 and 16 column groups of unequal width (two waves a piece).
 
 FP64 operators against the oracle, relative 2-norm <= 1e-12: a few hundred
 roundings of 2^-53 per component, the bound of the other operator tests.
@@ -15,7 +17,8 @@ from paper_2503_16994_amd import inputs, lqcd
 pytestmark = pytest.mark.gpu
 
 P, SF, OPEN = 0, 1, 2
-CASES = [((2, 2, 2, 4), P), ((2, 2, 2, 6), OPEN), ((6, 2, 2, 10), SF), ((10, 6, 2, 6), P)]
+CASES = [((2, 2, 2, 4), P), ((2, 2, 2, 6), OPEN), ((6, 2, 2, 10), SF), ((10, 6, 2, 6), P),
+         ((22, 14, 16, 8), P), ((26, 26, 26, 4), OPEN)]
 
 
 @pytest.mark.parametrize("mu", [0.0, 0.07], ids=["mu0", "mu"])
