@@ -1228,9 +1228,8 @@ static int spread_nparts(const HopLaunch& h) {
 // workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
 // conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
 // 33.2.
-// The direction update is fused where every wave can sum the partials itself
-// without a barrier; above that the sum costs each workgroup what the launch
-// does.
+// The direction update is fused where a launch is small (spread_on) and every
+// wave can sum the partials itself without a barrier (at most 64, 2^14 sites).
 bool hop_fuses_p(const HopLaunch& h0) {
   HopLaunch h = h0;
   if (h.prec == P_F64) h.rhs_lanes = 1;
