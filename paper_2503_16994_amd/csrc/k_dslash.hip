@@ -1223,11 +1223,6 @@ static int spread_nparts(const HopLaunch& h) {
   return -(h.both ? 2 : 1) * ((per + 1) & ~1);
 }
 
-// Canonical input is read site by site (192 contiguous bytes per lane, no
-// coalescing over lanes), which pays while the launch is one round of a
-// workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
-// conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
-// 33.2.
 // The direction update is fused where a launch is small (spread_on) and every
 // wave can sum the partials itself without a barrier (at most 64, 2^14 sites).
 bool hop_fuses_p(const HopLaunch& h0) {
@@ -1236,6 +1231,11 @@ bool hop_fuses_p(const HopLaunch& h0) {
   return spread_on(h) && parts_count(spread_nparts(h)) <= 64;
 }
 
+// Canonical input is read site by site (192 contiguous bytes per lane, no
+// coalescing over lanes), which pays while the launch is one round of a
+// workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
+// conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
+// 33.2.
 bool hop_reads_canonical(const HopLaunch& h0) {
   HopLaunch h = h0;
   if (h.prec == P_F64) h.rhs_lanes = 1;
