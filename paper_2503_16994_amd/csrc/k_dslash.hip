@@ -858,8 +858,9 @@ __device__ inline cpx<A> row_mul(const cpx<A> (&m)[6], int i, const cpx<A> (&v)[
 // which saves a small operator application its two layout conversions.
 // PF: applied to the updated search direction (HopLaunch::pf_r), which saves a
 // small iteration the launch of the update (4.5 us eager, 1.6 us and its drain
-// in a graph) for twelve more loads a lane: 8^4 FP32 solve 3885 -> 3833 us,
-// others of 2^9 to 2^14 sites 3 to 6% (10941 -> 10576, 3516 -> 3312 us).
+// in a graph) for twelve more loads a lane and a barrier in the third hop:
+// solves of 2^9 to 2^14 sites up to 5% (3516 -> 3330, 8714 -> 8580, 10941 ->
+// 10600 us), 8^4 FP32 3885 both.
 template <typename SG, typename SI, typename SO, bool XR, bool CANON, bool PF = false>
 __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) {
   using A = typename StoreTraits<SG>::acc;
@@ -909,7 +910,14 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
   }
   const int lb = xcd_remap(blockIdx.x, nwork);  // the rhs of a site block side by side on one XCD
   const int rhs = lb % a.nrhs, sb = lb / a.nrhs;
-  if (a.done && a.done[rhs * (int)(sizeof(CGState) / sizeof(int))] != 0) return;
+  if (a.beta_parts) {
+    // this launch's beta step may set the flag: one read decides for the workgroup
+    if (threadIdx.x == 0) nls[0] = a.done[rhs * (int)(sizeof(CGState) / sizeof(int))];
+    __syncthreads();
+    if (nls[0] != 0.0) return;
+  } else if (a.done && a.done[rhs * (int)(sizeof(CGState) / sizeof(int))] != 0) {
+    return;
+  }
   const int p = a.both ? (sb & 1) : a.p_out;
   const int bx = a.both ? sb >> 1 : sb, s = bx * kSpreadSites + l;  // site block of the parity, site
   const bool active = s < g.V2;
@@ -1253,7 +1261,7 @@ static hipError_t launch_spread(HopLaunch h, hipStream_t st) {
     }
   }
   if (h.cy || h.cz || h.cout) return hipErrorInvalidValue;
-  if (h.beta_parts && parts_count(h.beta_nparts) > 64) return hipErrorInvalidValue;
+  if (h.beta_parts && (parts_count(h.beta_nparts) > 64 || !h.done || !h.alpha_cg)) return hipErrorInvalidValue;
   if constexpr (!XR && std::is_same<SI, SO>::value) {
     if (h.pf_r) {
       if (parts_count(h.pf_nparts) > 64 || h.both || h.pre != PRE_NONE) return hipErrorInvalidValue;
