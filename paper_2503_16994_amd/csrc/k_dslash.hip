@@ -1179,19 +1179,23 @@ static bool split_on(const HopLaunch& h) { return h.dir_split && h.nr_tile == 1 
 // the library set nr_tile = rhs_lanes = 1 whenever mu != 0)
 static bool tm_on(const HopLaunch& h) { return h.tm_post != 0 || h.tm_mu != 0.0; }
 
-// Launches of k_hop_spread: those with too few threads in flight otherwise (a
-// site and rhs is one thread of k_hop).  Measured with k_hop against
-// k_hop_spread, us per hop: output sites x rhs = 2048: FP64 10.1 / 5.9, FP32 9.5 / 5.5,
-// BF16 7.6 / 4.7; 16384: 14.4 / 9.4, 11.5 / 6.4, 7.6 / 4.8; 31104: 15.3 / 14.4,
-// 11.4 / 8.9, 8.1 / 6.7; 32768: 16.5 / 17.3, 12.7 / 9.9, 7.8 / 6.2; 41472:
-// 18.9 / 19.4, 13.2 / 12.3, 9.1 / 8.4; 65536: 24.4 / 30.9, 15.4 / 16.6, 10.2 /
-// 11.9.  FP64 has one workgroup per CU (183 registers), FP32 and BF16 two.
+// Launches of k_hop_spread (a site and rhs is one thread of k_hop): those whose
+// workgroups are all resident at once, one per CU in FP64 (183 registers), two in
+// FP32 and BF16.  One more starts a second round that few CUs take part in.
+// Measured as time of k_hop over time of k_hop_spread, by output sites x rhs:
+// even-odd solves, one field / with a twisted mass: FP64 16384 1.32 / 1.34, 18432
+// 0.97 / 0.95, 28672 0.93 / 0.92; FP32 32768 1.15 / 1.17, 36864 0.99 / 0.98, 45056
+// 0.98 / 0.98; BF16 20480 1.13 / 1.14, 32768 1.13 / 1.14, 36864 0.96 / 0.94, 40960
+// 0.95 / 0.91; twelve fields: FP64 30720 0.95, FP32 43008 0.92, BF16 30720 1.14,
+// 43008 0.98; full-lattice solves 20480 0.96; Dw 20480 0.93.
 // The caller's direction split sums in another order and keeps its own kernel.
-constexpr long kSpreadMax64 = 30 * 1024, kSpreadMax32 = 44 * 1024;
-// output sites times rhs of a launch
-static long launch_sites(const HopLaunch& h) { return (h.both ? 2L : 1L) * h.g.V2 * h.nrhs; }
+constexpr long kCUs = 256;
+static int spread_nblocks(const HopLaunch& h) {
+  return (h.both ? 2 : 1) * ((h.g.V2 + kSpreadSites - 1) / kSpreadSites);
+}
+static long spread_workgroups(const HopLaunch& h) { return (long)spread_nblocks(h) * h.nrhs; }
 static bool spread_on(const HopLaunch& h) {
-  return h.hop && !split_on(h) && launch_sites(h) <= (h.prec == P_F64 ? kSpreadMax64 : kSpreadMax32);
+  return h.hop && !split_on(h) && spread_workgroups(h) <= (h.prec == P_F64 ? 1 : 2) * kCUs;
 }
 
 // Unused dynamic LDS that caps the workgroups resident per CU (160 KiB of LDS
@@ -1221,10 +1225,7 @@ int hop_nblocks(const HopLaunch& h) {
   return h.both ? 2 * nb : nb;
 }
 
-static int spread_nblocks(const HopLaunch& h) {
-  return (h.both ? 2 : 1) * ((h.g.V2 + kSpreadSites - 1) / kSpreadSites);
-}
-// its partial sums per rhs, as a count of half sums (see parts_count): whole
+// partial sums per rhs of a small launch, as a count of half sums (see parts_count): whole
 // pairs for each parity
 static int spread_nparts(const HopLaunch& h) {
   const int per = (h.g.V2 + kSpreadSites - 1) / kSpreadSites;
@@ -1241,13 +1242,13 @@ bool hop_fuses_p(const HopLaunch& h0) {
 
 // Canonical input is read site by site (192 contiguous bytes per lane, no
 // coalescing over lanes), which pays while the launch is one round of a
-// workgroup per CU: Dw of 8^3x12 (12288 sites and fields) 11.7 us with the
-// conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2, and D^+ D there 31.5 and
-// 33.2.
+// workgroup per CU (every small FP64 launch): Dw of 8^3x12 (12288 sites and
+// fields) 11.7 us with the conversion, 9.8 without; 12^4 (20736) 19.7 and 19.2,
+// and D^+ D there 31.5 and 33.2.
 bool hop_reads_canonical(const HopLaunch& h0) {
   HopLaunch h = h0;
   if (h.prec == P_F64) h.rhs_lanes = 1;
-  return spread_on(h) && launch_sites(h) <= 256 * kSpreadSites;
+  return spread_on(h) && spread_workgroups(h) <= kCUs;
 }
 
 template <typename SG, typename SI, typename SO, bool XR>

@@ -1,0 +1,62 @@
+// Host check of the rules by which the library chooses its launches, linked
+// against the built library (no device work).  Each check is named on the
+// command line; a failure prints what differs and ends with status 1.
+#include <stdio.h>
+#include <string.h>
+
+#include "../paper_2503_16994_amd/csrc/lqcd_internal.h"
+
+using namespace lqcd;
+
+static int failures = 0;
+#define CHECK(cond, ...)                  \
+  do {                                    \
+    if (!(cond)) {                        \
+      printf("%s: ", #cond);              \
+      printf(__VA_ARGS__);                \
+      printf("\n");                       \
+      ++failures;                         \
+    }                                     \
+  } while (0)
+
+static HopLaunch hop(int prec, long V2, int nrhs, bool both, double mu) {
+  HopLaunch h;
+  memset(&h, 0, sizeof(h));
+  h.g.V2 = (int)V2;
+  h.prec = prec;
+  h.nrhs = nrhs;
+  h.hop = true;
+  h.both = both;
+  h.tm_mu = mu;
+  h.tm_post = mu != 0.0;
+  apply_tuning(h, lqcd_tuning{1, 1, 1, 0});
+  return h;
+}
+
+// A small launch (negative partial counts) is one whose 64-site workgroups are
+// resident together: 256 in FP64, 512 in FP32 and BF16.
+static void small_launches() {
+  for (int prec = P_F64; prec <= P_BF16; ++prec) {
+    const long line = 256 * (prec == P_F64 ? 1 : 2);
+    for (int nrhs : {1, 4, 12})
+      for (int both = 0; both < 2; ++both)
+        for (double mu : {0.0, 0.01})
+          for (long V2 = 16; V2 * nrhs < 64 * 2 * line; V2 += 16) {
+            const bool small = hop_nparts(hop(prec, V2, nrhs, both != 0, mu)) < 0;
+            const long n = (both ? 2 : 1) * ((V2 + 63) / 64) * nrhs;
+            CHECK(small == (n <= line), "prec %d nrhs %d both %d mu %g workgroups %ld", prec, nrhs, both, mu, n);
+            if (failures > 10) return;
+          }
+  }
+}
+
+int main(int argc, char** argv) {
+  for (int i = 1; i < argc; ++i) {
+    if (!strcmp(argv[i], "small_launches")) small_launches();
+    else {
+      printf("unknown check %s\n", argv[i]);
+      return 2;
+    }
+  }
+  return failures ? 1 : 0;
+}
