@@ -60,6 +60,17 @@ __device__ inline double psum(const double* p, int n, double* sh) {
   return out;
 }
 
+// A decision on flags that the launch itself may change meanwhile (beta_step and
+// the update's finish set them), taken by one thread for its whole workgroup: read
+// by every wave for itself, waves of one workgroup could part before a barrier.
+template <typename F>
+__device__ inline bool wg_once(F&& flag) {
+  __shared__ int v;
+  if (threadIdx.x == 0) v = flag() ? 1 : 0;
+  __syncthreads();
+  return v != 0;
+}
+
 __global__ void k_cg_setup(CGState* s, const double* b2, const double* eta2, CGSetup cfg) {
   const int r = blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= cfg.nrhs) return;
@@ -101,7 +112,7 @@ __global__ void k_cg_setup(CGState* s, const double* b2, const double* eta2, CGS
 __global__ void k_cg_beta(CGState* s, const double* partials, int nparts) {
   __shared__ double sh[4];
   const int r = blockIdx.x;
-  if (s[r].done) return;
+  if (wg_once([&] { return s[r].done != 0; })) return;
   const double v = psum(partials + (size_t)r * parts_stride(nparts), nparts, sh);
   if (threadIdx.x == 0) beta_step(s[r], v);
 }
@@ -231,8 +242,8 @@ __global__ void k_cg_p(const SP* p, SP* pn, const S* __restrict__ r, long n, lon
 // every workgroup sums the |r|^2 partials in the same fixed order, so all
 // agree on beta bit for bit; workgroup 0 alone updates the control state.
 // A rhs that workgroup 0 marks done meanwhile may see p updated by only some
-// workgroups, which is harmless: done is final here (only the reliable
-// update's finish kernel sets the resumable CG_STALLED).
+// workgroups (each as a whole), which is harmless: done is final here (only the
+// reliable update's finish kernel sets the resumable CG_STALLED).
 template <typename S, typename SP, typename SL>
 __global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, CGState* cs, SL* plo,
                             const double* partials, int nparts) {
@@ -242,7 +253,7 @@ __global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n
   PUpdate<S, SP, SL> u(p, pn, r, plo, (size_t)q * rs, n);
   u.load();
   const double rr0 = c.rr_prev;
-  if (c.done) return;
+  if (wg_once([&] { return c.done != 0; })) return;
   const double v = psum(partials + (size_t)q * parts_stride(nparts), nparts, sh);
   if (blockIdx.x == 0 && threadIdx.x == 0) beta_step(c, v);
   if (!finite(v)) return;
@@ -340,7 +351,7 @@ __global__ void k_ru_finish(CGState* s, const double* part_res, int n_res, const
                             int n_r) {
   __shared__ double sh[4];
   const int r = blockIdx.x;
-  if (ru_skip(s[r])) return;
+  if (wg_once([&] { return ru_skip(s[r]); })) return;
   const double res2 = psum(part_res + (size_t)r * parts_stride(n_res), n_res, sh);
   const double rr = psum(part_r + (size_t)r * parts_stride(n_r), n_r, sh);
   if (threadIdx.x != 0) return;
