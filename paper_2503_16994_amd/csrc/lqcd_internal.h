@@ -124,20 +124,35 @@ struct HopSpec {
 
 // Launch configuration of a workspace that nobody tuned, by sites V, storage
 // precision and rhs count n (no configuration changes a result).
-//  * Links and clover blocks: with several rhs per site they are re-read, and
-//    up to a few 10^5 sites they stay in the last-level cache from launch to
-//    launch, so ordinary loads beat non-temporal ones; one rhs of a larger
-//    lattice streams them once and keeps the non-temporal ones.
+//  * Links and clover blocks in FP64 and FP32: with several rhs per site they are
+//    re-read, and up to a few 10^5 sites they stay in the last-level cache from
+//    launch to launch, so ordinary loads beat non-temporal ones; one rhs (or two,
+//    and in FP32 three) of a larger lattice streams them once and keeps the
+//    non-temporal ones.  In BF16 the two are the same to 1%: non-temporal.
 //  * rhs per thread: one while the launch needs its threads to hide latency,
 //    two (or three for an odd n, in FP32 for any multiple of three) once there
 //    are enough.
 //  * From 10^6 sites on, z-slabs per XCD; in FP64 with several rhs from 10^6
 //    sites times rhs on.
-// Measured, us per pair of hops, non-temporal loads and one rhs per thread
-// against this choice: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
+// Against non-temporal loads and one rhs per thread everywhere, us per pair of
+// hops on fields of zeros: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
 // 4 rhs 136 / 98, 12 rhs 391 / 295, 24^3x48 12 rhs 2632 / 1701, 32^3x64 1 rhs
 // 753 / 645, 12 rhs 7936 / 4379; FP32 16^3x32 12 rhs 216 / 147, 24^3x48 1 rhs 127
 // / 113, 32^3x64 12 rhs 4076 / 2395; BF16 32^3x64 12 rhs 1533 / 1188.
+// The lines, ms of even-odd solves of 40 iterations from noise sources:
+//   cached / non-temporal loads: FP32 1 rhs 524288 sites 10.6 / 11.1, 663552 13.8 /
+//   13.8, 786432 16.4 / 15.8, 983040 20.2 / 19.2, 2 rhs (one / two a thread) 262144
+//   8.4 / 8.8, 663552 22.2 / 21.1, 3 rhs 262144 11.9 / 11.7, 393216 18.1 / 18.4, 663552
+//   31.0 / 29.1; FP64 1 rhs 212992 7.86 / 8.00, 221184 8.34 / 8.50, 245760 8.93 / 8.55,
+//   2 rhs 212992 11.95 / 11.99, 245760 13.45 / 13.21, 3 rhs (one / three a thread)
+//   245760 18.6 / 19.1, 524288 39.6 / 40.7;
+//   one / two rhs a thread, by sites times rhs: BF16 393216 4.76 / 4.80, 524288 5.29 /
+//   5.44, 786432 7.27 / 7.10, 1048576 9.12 / 9.33, 1327104 12.05 / 12.24, 1572864
+//   12.92 / 12.76, 2654208 23.2 / 22.3; FP32 327680 5.46 / 5.55, 360448 5.95 / 5.75,
+//   497664 7.58 / 7.07; FP64 497664 10.80 / 10.91, 786432 17.7 / 17.3, 1048576 23.1 /
+//   23.0, and 22.3 with slabs;
+//   plain order / slabs, 1 rhs: FP64 524288 17.4 / 17.7, 983040 32.9 / 31.5, 1048576
+//   34.5 / 33.1; FP32 1048576 20.1 / 19.8; BF16 983040 11.3 / 11.0.
 // The slabs and tiles of FP64 batches, us per canonical Dw / per four hops of the
 // Schur normal operator, plain order against slabs at two rhs per thread:
 // 16^3x32 4 rhs 154 / 275 and 150 / 285, 8 rhs 281 / 526 and 273 / 511, 12 rhs
@@ -153,9 +168,9 @@ inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
     if (n > 1) t.nr_tile = three || n == 3 ? 3 : 2;
   }
   if (prec == LQCD_BF16) {
-    if (n >= 4 && vn >= 390000) t.nr_tile = 2;
+    if (n >= 4 && vn >= 1400000) t.nr_tile = 2;
   } else if (n < 4) {
-    const bool fits = V <= (prec == LQCD_F64 ? 250000 : large);
+    const bool fits = V <= (prec == LQCD_F32 ? 600000 : n < 3 ? 230000 : large);
     t.flags = fits ? kCached : kStream;
     if (!fits && n > 1) t.nr_tile = n;
   } else {

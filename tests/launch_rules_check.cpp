@@ -50,9 +50,36 @@ static void small_launches() {
   }
 }
 
+// The configuration of a workspace nobody tuned, at measured points on both
+// sides of its lines (the faster of the two is the one expected).
+static void own_configurations() {
+  struct {
+    int prec;
+    int64_t V;
+    int n, tile;
+    bool cached;
+  } const want[] = {
+      {LQCD_F32, 524288, 1, 1, true},  {LQCD_F32, 786432, 1, 1, false}, {LQCD_F32, 983040, 1, 1, false},
+      {LQCD_F32, 262144, 2, 1, true},  {LQCD_F32, 663552, 2, 2, false}, {LQCD_F32, 393216, 3, 1, true},
+      {LQCD_F32, 663552, 3, 3, false}, {LQCD_F64, 221184, 1, 1, true},  {LQCD_F64, 245760, 1, 1, false},
+      {LQCD_F64, 212992, 2, 1, true},  {LQCD_F64, 245760, 2, 2, false}, {LQCD_F64, 245760, 3, 1, true},
+      {LQCD_F64, 524288, 3, 1, true},  {LQCD_BF16, 131072, 4, 1, false}, {LQCD_BF16, 131072, 8, 1, false},
+      {LQCD_BF16, 331776, 4, 1, false}, {LQCD_BF16, 131072, 12, 2, false}, {LQCD_BF16, 663552, 4, 2, false},
+      {LQCD_F32, 81920, 4, 1, true},   {LQCD_F32, 90112, 4, 2, true},   {LQCD_F64, 41472, 12, 1, true},
+      {LQCD_F64, 131072, 8, 2, true},
+  };
+  for (const auto& w : want) {
+    const lqcd_tuning t = own_tuning(w.V, w.prec, w.n);
+    CHECK(t.nr_tile == w.tile, "prec %d V %ld n %d: tile %d", w.prec, (long)w.V, w.n, t.nr_tile);
+    CHECK(((t.flags & LQCD_TUNE_CACHED_GAUGE) != 0) == w.cached, "prec %d V %ld n %d: flags %d", w.prec, (long)w.V,
+          w.n, t.flags);
+  }
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!strcmp(argv[i], "small_launches")) small_launches();
+    else if (!strcmp(argv[i], "own_configurations")) own_configurations();
     else {
       printf("unknown check %s\n", argv[i]);
       return 2;
