@@ -373,7 +373,7 @@ static const void* cloi_of(const lqcd_ws* w, int prec) {
 
 // dag: the launch belongs to the adjoint operator g5 D(-mu) g5 (twisted
 // mass -mu, adjoint odd-site inverse); no difference for mu = 0
-static HopLaunch base_launch(const OpCtx& c, bool dag) {
+static HopLaunch base_launch(const OpCtx& c, bool dag, bool both = false) {
   HopLaunch h;
   memset(&h, 0, sizeof(h));
   h.g = c.w->g->kg;
@@ -384,7 +384,8 @@ static HopLaunch base_launch(const OpCtx& c, bool dag) {
   h.hop = true;
   h.tm_mu = dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
-  apply_tuning(h, tuning_of(c.w, c.prec, c.nrhs));
+  h.both = both;
+  apply_tuning(h, tuning_of(c.w, c.prec, c.nrhs, both));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
 }
@@ -410,8 +411,7 @@ struct CanonIO {
 static hipError_t apply_dw_full(const OpCtx& c, const void* y, void* out, bool g5, bool dag = false,
                                 const CanonIO& io = {}) {
   const lqcd_geom_t* g = c.w->g;
-  HopLaunch h = base_launch(c, dag);
-  h.both = true;
+  HopLaunch h = base_launch(c, dag, true);
   h.par_stride = par_off(g);
   h.cpre_par = 36L * g->V2p;
   h.y = y;
@@ -503,8 +503,7 @@ extern "C" int lqcd_dw_apply(const lqcd_gauge_t* u, const lqcd_dirac* d, int op,
   const bool canon = (layout == LQCD_LAYOUT_CANON);
   const bool g5in = (op == LQCD_OP_DW_DAG || op == LQCD_OP_SCHUR_DAG);
   const bool dag = g5in;
-  HopLaunch shape = base_launch(c, false);
-  shape.both = op <= LQCD_OP_DWDAGDW;
+  const HopLaunch shape = base_launch(c, false, op <= LQCD_OP_DWDAGDW);
   const bool small = canon && hop_reads_canonical(shape);
   const bool write = canon && (small || (prec == P_F64 && op != LQCD_OP_HOP_EO));
   const size_t full_bytes = (size_t)nrhs * 24 * g->V2p * elem_bytes(prec);

@@ -129,6 +129,8 @@ struct HopSpec {
 //    launch to launch, so ordinary loads beat non-temporal ones; one rhs (or two,
 //    and in FP32 three) of a larger lattice streams them once and keeps the
 //    non-temporal ones.  In BF16 the two are the same to 1%: non-temporal.
+//    A launch over both parities (`both`) reads every link twice, so in FP32 it
+//    keeps the ordinary loads to 10^6 sites.
 //  * rhs per thread: one while the launch needs its threads to hide latency,
 //    two (or three for an odd n, in FP32 for any multiple of three) once there
 //    are enough.
@@ -146,6 +148,8 @@ struct HopSpec {
 //   31.0 / 29.1; FP64 1 rhs 212992 7.86 / 8.00, 221184 8.34 / 8.50, 245760 8.93 / 8.55,
 //   2 rhs 212992 11.95 / 11.99, 245760 13.45 / 13.21, 3 rhs (one / three a thread)
 //   245760 18.6 / 19.1, 524288 39.6 / 40.7;
+//   the same, us per internal Dw of 1 rhs: FP32 331776 52.2 / 60.6, 663552 108.7 /
+//   115.2; FP64 229376 76.8 / 77.4, 331776 120.4 / 116.4;
 //   one / two rhs a thread, by sites times rhs: BF16 393216 4.76 / 4.80, 524288 5.29 /
 //   5.44, 786432 7.27 / 7.10, 1048576 9.12 / 9.33, 1327104 12.05 / 12.24, 1572864
 //   12.92 / 12.76, 2654208 23.2 / 22.3; FP32 327680 5.46 / 5.55, 360448 5.95 / 5.75,
@@ -158,7 +162,7 @@ struct HopSpec {
 // 16^3x32 4 rhs 154 / 275 and 150 / 285, 8 rhs 281 / 526 and 273 / 511, 12 rhs
 // 410 / 762 and 389 / 732; 32^3x64 12 rhs, slabs at three and two rhs per thread:
 // 7194 / 11236 and 6937 / 10882.
-inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
+inline lqcd_tuning own_tuning(int64_t V, int prec, int n, bool both = false) {
   constexpr int kCached = LQCD_TUNE_NT_STORE | LQCD_TUNE_CACHED_GAUGE, kStream = LQCD_TUNE_NT_STORE;
   const int64_t vn = V * n, large = 1000000;
   lqcd_tuning t = {1, 1, 1, 0};
@@ -170,7 +174,8 @@ inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
   if (prec == LQCD_BF16) {
     if (n >= 4 && vn >= 1400000) t.nr_tile = 2;
   } else if (n < 4) {
-    const bool fits = V <= (prec == LQCD_F32 ? 600000 : n < 3 ? 230000 : large);
+    const int64_t line = prec == LQCD_F32 ? (both ? large : 600000) : n == 3 ? large : both ? 250000 : 230000;
+    const bool fits = V <= line;
     t.flags = fits ? kCached : kStream;
     if (!fits && n > 1) t.nr_tile = n;
   } else {
@@ -183,8 +188,8 @@ inline lqcd_tuning own_tuning(int64_t V, int prec, int n) {
   return t;
 }
 // the configuration of launches over n rhs in precision prec
-inline lqcd_tuning tuning_of(const lqcd_ws* w, int prec, int n) {
-  return w->tune_set[prec] ? w->tune[prec] : own_tuning(w->g->V, prec, n);
+inline lqcd_tuning tuning_of(const lqcd_ws* w, int prec, int n, bool both = false) {
+  return w->tune_set[prec] ? w->tune[prec] : own_tuning(w->g->V, prec, n, both);
 }
 
 // rhs tiling of a launch over nrhs fields: rhs_lanes lanes per site, each

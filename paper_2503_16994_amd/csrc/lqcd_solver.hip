@@ -83,7 +83,7 @@ Vec odd_part(const Vec& v, long V2) {
   return Vec{(char*)v.p + (size_t)12 * V2 * elem_bytes(v.prec), v.prec, v.rs};
 }
 
-HopLaunch mk(const Ctl& c, int lprec) {
+HopLaunch mk(const Ctl& c, int lprec, bool both = false) {
   HopLaunch h;
   memset(&h, 0, sizeof(h));
   h.g = c.g->kg;
@@ -94,7 +94,8 @@ HopLaunch mk(const Ctl& c, int lprec) {
   h.hop = true;
   h.tm_mu = c.dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
-  apply_tuning(h, tuning_of(c.w, lprec, c.nrhs));
+  h.both = both;
+  apply_tuning(h, tuning_of(c.w, lprec, c.nrhs, both));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
 }
@@ -234,11 +235,7 @@ hipError_t hop_oe_xr(const Ctl& c, int lprec, Vec q, Vec t_o, Vec r, double* par
 int iter_parts(const Ctl& c, int lprec) { return hop_nparts(mk(c, lprec)); }
 
 // the launch shape of dw_full (both parities, the FP64 tuning)
-HopLaunch dw_full_launch(const Ctl& c) {
-  HopLaunch h = mk(c, P_F64);
-  h.both = true;
-  return h;
-}
+HopLaunch dw_full_launch(const Ctl& c) { return mk(c, P_F64, true); }
 // partial sums per rhs that a dw_full launch writes (its own site blocks:
 // the tuned rhs tile and direction split decide the block size)
 int full_parts(const Ctl& c) { return hop_nparts(dw_full_launch(c)); }

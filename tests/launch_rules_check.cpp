@@ -57,7 +57,7 @@ static void own_configurations() {
     int prec;
     int64_t V;
     int n, tile;
-    bool cached;
+    bool cached, both = false;
   } const want[] = {
       {LQCD_F32, 524288, 1, 1, true},  {LQCD_F32, 786432, 1, 1, false}, {LQCD_F32, 983040, 1, 1, false},
       {LQCD_F32, 262144, 2, 1, true},  {LQCD_F32, 663552, 2, 2, false}, {LQCD_F32, 393216, 3, 1, true},
@@ -67,9 +67,11 @@ static void own_configurations() {
       {LQCD_BF16, 331776, 4, 1, false}, {LQCD_BF16, 131072, 12, 2, false}, {LQCD_BF16, 663552, 4, 2, false},
       {LQCD_F32, 81920, 4, 1, true},   {LQCD_F32, 90112, 4, 2, true},   {LQCD_F64, 41472, 12, 1, true},
       {LQCD_F64, 131072, 8, 2, true},
+      // launches over both parities
+      {LQCD_F32, 663552, 1, 1, true, true}, {LQCD_F64, 229376, 1, 1, true, true}, {LQCD_F64, 331776, 1, 1, false, true},
   };
   for (const auto& w : want) {
-    const lqcd_tuning t = own_tuning(w.V, w.prec, w.n);
+    const lqcd_tuning t = own_tuning(w.V, w.prec, w.n, w.both);
     CHECK(t.nr_tile == w.tile, "prec %d V %ld n %d: tile %d", w.prec, (long)w.V, w.n, t.nr_tile);
     CHECK(((t.flags & LQCD_TUNE_CACHED_GAUGE) != 0) == w.cached, "prec %d V %ld n %d: flags %d", w.prec, (long)w.V,
           w.n, t.flags);
