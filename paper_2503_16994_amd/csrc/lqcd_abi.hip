@@ -359,6 +359,8 @@ struct OpCtx {
   int nrhs;
   hipStream_t st;
   double mu;  // twisted mass
+  // canonical operator that ends in a layout conversion (see own_tuning_converted)
+  bool converted = false, one_hop = false;
 };
 
 static const void* links_of(const lqcd_gauge* u, int prec) {
@@ -385,7 +387,9 @@ static HopLaunch base_launch(const OpCtx& c, bool dag, bool both = false) {
   h.tm_mu = dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
   h.both = both;
-  apply_tuning(h, tuning_of(c.w, c.prec, c.nrhs, both));
+  apply_tuning(h, c.converted && !c.w->tune_set[c.prec]
+                      ? own_tuning_converted(c.w->g->V, c.prec, c.nrhs, both, c.one_hop, c.u->two_row != 0)
+                      : tuning_of(c.w, c.prec, c.nrhs, both));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
 }
@@ -506,6 +510,8 @@ extern "C" int lqcd_dw_apply(const lqcd_gauge_t* u, const lqcd_dirac* d, int op,
   const HopLaunch shape = base_launch(c, false, op <= LQCD_OP_DWDAGDW);
   const bool small = canon && hop_reads_canonical(shape);
   const bool write = canon && (small || (prec == P_F64 && op != LQCD_OP_HOP_EO));
+  c.converted = canon && !write;
+  c.one_hop = op == LQCD_OP_HOP_EO || op == LQCD_OP_HOP_OE;
   const size_t full_bytes = (size_t)nrhs * 24 * g->V2p * elem_bytes(prec);
   void* tmp = w->m.R;  // scratch full vectors
   void* tmp2 = w->m.P;

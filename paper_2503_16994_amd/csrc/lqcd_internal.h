@@ -192,6 +192,29 @@ inline lqcd_tuning tuning_of(const lqcd_ws* w, int prec, int n, bool both = fals
   return w->tune_set[prec] ? w->tune[prec] : own_tuning(w->g->V, prec, n, both);
 }
 
+// The same for an operator on canonical fields whose result the layout conversion
+// reads next (one_hop: a single launch over one parity).
+//  * Up to 8 MB of (sites x rhs x element) the conversion finds the result in the
+//    last-level cache, so it is stored the ordinary way.
+//  * The conversions before and after sweep that cache: links and clover blocks of
+//    few rhs stay in it from call to call only if everything the call moves fits
+//    its 256 MB.
+// us per call of FP32 HOP_EO, stores and loads ordinary / non-temporal stores and
+// ordinary loads / this choice: 16^3x32 1 rhs 36.6 / 37.2 / 36.6, 4 rhs 111 / 117 /
+// 110; 24^4 1 rhs 88.5 / 90.2 / 84.8, with a twisted mass 101 / 104 / 92, 4 rhs 279 /
+// 274 / 274; 24^3x48 1 rhs 168 / 169 / 163.  FP64 16^3x32 49.6 / 50.6 / 49.6, 24^4 136 /
+// 139 / 125.  BF16 the same to 1% in every form.
+inline lqcd_tuning own_tuning_converted(int64_t V, int prec, int n, bool both, bool one_hop, bool two_row) {
+  lqcd_tuning t = own_tuning(V, prec, n, both);
+  const int64_t e = (int64_t)elem_bytes(prec);
+  if (prec == LQCD_BF16 || V * n * e > 8000000) return t;
+  t.flags &= ~LQCD_TUNE_NT_STORE;
+  // links of both parities and clover blocks of one; canonical and internal fields
+  const int64_t bytes = V * (((two_row ? 24 : 36) + 18) * e + n * 24 * (16 + e));
+  if (!both && (n < 4 || one_hop) && bytes > 256000000) t.flags &= ~LQCD_TUNE_CACHED_GAUGE;
+  return t;
+}
+
 // rhs tiling of a launch over nrhs fields: rhs_lanes lanes per site, each
 // with nr_tile rhs; both are reduced until their product divides nrhs
 inline void apply_tuning(HopLaunch& h, const lqcd_tuning& t) {

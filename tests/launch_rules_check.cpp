@@ -78,10 +78,35 @@ static void own_configurations() {
   }
 }
 
+// The same where a layout conversion reads the result next (canonical FP32
+// operators, FP64 HOP_EO).
+static void converted_configurations() {
+  constexpr int N = LQCD_TUNE_NT_STORE, C = LQCD_TUNE_CACHED_GAUGE;
+  struct {
+    int prec;
+    int64_t V;
+    int n;
+    bool both, one_hop;
+    int flags;
+  } const want[] = {
+      {LQCD_F32, 131072, 1, false, true, C},  {LQCD_F32, 331776, 1, false, true, 0}, {LQCD_F32, 663552, 1, false, true, 0},
+      {LQCD_F32, 331776, 1, false, false, 0}, {LQCD_F32, 331776, 1, true, false, C}, {LQCD_F32, 131072, 4, false, true, 0},
+      {LQCD_F32, 131072, 4, false, false, C}, {LQCD_F32, 331776, 4, false, true, N | C},
+      {LQCD_F64, 131072, 1, false, true, C},  {LQCD_F64, 331776, 1, false, true, 0}, {LQCD_F64, 663552, 1, false, true, N},
+      {LQCD_BF16, 331776, 1, false, true, 0},
+  };
+  for (const auto& w : want) {
+    const int flags = own_tuning_converted(w.V, w.prec, w.n, w.both, w.one_hop, true).flags;
+    CHECK(flags == w.flags, "prec %d V %ld n %d both %d one hop %d: flags %d", w.prec, (long)w.V, w.n, w.both, w.one_hop,
+          flags);
+  }
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!strcmp(argv[i], "small_launches")) small_launches();
     else if (!strcmp(argv[i], "own_configurations")) own_configurations();
+    else if (!strcmp(argv[i], "converted_configurations")) converted_configurations();
     else {
       printf("unknown check %s\n", argv[i]);
       return 2;
