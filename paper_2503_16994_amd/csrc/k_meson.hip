@@ -15,26 +15,36 @@
 //
 // As a matrix product, G_t = Z Z^H with Z[(al, be)][(x, a, c)] the 16 x 9 V3
 // matrix of slice t, so it runs on the FP64 matrix cores: with Z = Zr + i Zi,
-//   Re G = Zr Zr^T + Zi Zi^T,   Im G = X - X^T,   X = Zi Zr^T,
-// three real 16x16 products instead of the four of a general complex one
-// (G is Hermitian).
+//   Re G = Zr Zr^T + Zi Zi^T,   Im G = Zi Zr^T - Zr Zi^T.
+// An entry of G may be far smaller than the terms it is summed from (columns that
+// differ by nearly a phase: Im, or Re for spins tied by a factor i), so the two
+// products of Re and of Im go into one accumulator each, term by term.  (Im G as
+// X - X^T of one product is a product less, and the error of such an entry grew a
+// thousandfold against sums of its own terms.)
 //
 // Kernel 1 (k_meson_partial): workgroup (b, t) takes one chunk of slice t,
 // each of its four waves every fourth group of four sites.  In
 // v_mfma_f64_16x16x4 lane l holds row l % 16 and inner index l / 16 of both
 // operands, so the lane that loads component (al, a) of column (be, c) at
 // site l / 16 of the group holds one entry of the left and of the right
-// operand at once: nine 16-byte loads and 27 matrix instructions per four
+// operand at once: nine 16-byte loads and 36 matrix instructions per four
 // sites, no LDS and no barrier inside the loop, and the next group's loads in
-// flight meanwhile.  The waves' sums are added in wave order.
+// flight meanwhile.  v_permlane16_swap first puts the two terms of a site next to
+// each other along the inner index (re of two sites in one register, im of them
+// in the other), so that they meet in the sum before the next site's do.  Every
+// four groups (288 terms) the sums are added to a second pair, which keeps the
+// chains of a sum as short as its error wants them.  The waves' sums are added
+// in wave order.
 // Kernel 2 (k_meson_reduce): workgroup t sums the chunk partials of every
-// entry in chunk order, forms G and contracts with the requested Gamma pairs
-// (a fixed-order block sum).  FP64 throughout; deterministic, no atomics.
+// entry in chunk order, forms G (Im antisymmetrised) and contracts with the
+// requested Gamma pairs (a fixed-order block sum).  FP64 throughout;
+// deterministic, no atomics.
 //
-// Bound: HBM, 2304 B per site read once.  At 32^3x64 the call takes 870 us
-// (5.6 TB/s, against 6.0 TB/s of a plain read-only sum on the same card);
-// staged in LDS 16 sites at a time and accumulated with vector FMAs, 168
-// registers and two barriers per 16 sites, it took 1578 us.
+// Bound: HBM, 2304 B per site read once.  At 32^3x64 the call takes 885 us
+// (5.5 TB/s, against 6.0 TB/s of a plain read-only sum on the same card), with Im G
+// from X - X^T 863 (and at four waves per SIMD, 931); staged in LDS 16 sites at a
+// time and accumulated with vector FMAs, 168 registers and two barriers per 16
+// sites, it took 1578 us.
 #include "lqcd_kernels.h"
 
 namespace lqcd {
@@ -47,6 +57,16 @@ constexpr long kMesonGrid = 2048;    // workgroups wanted: eight per CU, two rou
 
 using cd = cpx<double>;
 typedef double d4 __attribute__((ext_vector_type(4)));
+
+// exchanges the odd 16-lane rows of a with the even ones of b
+__device__ inline void swap_rows(double& a, double& b) {
+  typedef unsigned u2 __attribute__((ext_vector_type(2)));
+  u2 av = __builtin_bit_cast(u2, a), bv = __builtin_bit_cast(u2, b);
+  const auto lo = __builtin_amdgcn_permlane16_swap(av.x, bv.x, false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(av.y, bv.y, false, false);
+  a = __builtin_bit_cast(double, u2{lo[0], hi[0]});
+  b = __builtin_bit_cast(double, u2{lo[1], hi[1]});
+}
 
 __global__ __launch_bounds__(kMesonBlock) void k_meson_partial(const double2* __restrict__ psi, long V, long V3,
                                                                int chunk, int nchunk, double2* partials) {
@@ -67,24 +87,37 @@ __global__ __launch_bounds__(kMesonBlock) void k_meson_partial(const double2* __
     x += kStep;
     p += kStep * 12;
   };
-  d4 rr = {0.0, 0.0, 0.0, 0.0}, ii = rr, xx = rr;
+  const d4 zero = {0.0, 0.0, 0.0, 0.0};
+  d4 re = zero, im = zero, re_sum = zero, im_sum = zero;
   const int steps = (int)((s_end - ((long)t * V3 + (long)b * chunk) + kStep - 1) / kStep);  // uniform
   load(z);
   for (int k = 0; k < steps; ++k) {
     load(zn);  // past the chunk: zeros, nothing read
 #pragma unroll
     for (int e = 0; e < 9; ++e) {
-      rr = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].x, z[e].x, rr, 0, 0, 0);
-      ii = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].y, z[e].y, ii, 0, 0, 0);
-      xx = __builtin_amdgcn_mfma_f64_16x16x4f64(z[e].y, z[e].x, xx, 0, 0, 0);
+      // inner index 0..3: re, im of sites 0 and 2, then of sites 1 and 3
+      double p0 = z[e].x, p1 = z[e].y, n0 = z[e].y, n1 = -z[e].x;
+      swap_rows(p0, p1);
+      swap_rows(n0, n1);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(p0, p0, re, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f64_16x16x4f64(p1, p1, re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(n0, p0, im, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f64_16x16x4f64(n1, p1, im, 0, 0, 0);
+    }
+    if ((k & 3) == 3) {
+      re_sum += re;
+      im_sum += im;
+      re = im = zero;
     }
 #pragma unroll
     for (int e = 0; e < 9; ++e) z[e] = zn[e];
   }
+  re_sum += re;
+  im_sum += im;
   // result element r of lane l: row l / 16 + 4 r, column l % 16
   __shared__ double2 red[kMesonBlock / 64][256];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) red[w][((l >> 4) + 4 * r) * 16 + row] = make_double2(rr[r] + ii[r], xx[r]);
+  for (int r = 0; r < 4; ++r) red[w][((l >> 4) + 4 * r) * 16 + row] = make_double2(re_sum[r], im_sum[r]);
   __syncthreads();
   double2 s = make_double2(0.0, 0.0);
 #pragma unroll
@@ -92,7 +125,7 @@ __global__ __launch_bounds__(kMesonBlock) void k_meson_partial(const double2* __
     s.x += red[ww][tid].x;
     s.y += red[ww][tid].y;
   }
-  partials[((size_t)t * nchunk + b) * 256 + tid] = s;  // (Re G, X) of entry (tid / 16, tid % 16)
+  partials[((size_t)t * nchunk + b) * 256 + tid] = s;  // entry (tid / 16, tid % 16)
 }
 
 // chiral-basis gamma matrices g_x, g_y, g_z, g_t (mu = 0..3): each has one
@@ -158,7 +191,7 @@ __global__ __launch_bounds__(256) void k_meson_reduce(const double2* __restrict_
   }
   xs[i] = g.y;
   __syncthreads();
-  g.y -= xs[(i & 15) * 16 + (i >> 4)];  // Im G = X - X^T
+  g.y = 0.5 * (g.y - xs[(i & 15) * 16 + (i >> 4)]);  // G is Hermitian
   if (G) G[(size_t)t * 256 + i] = g;
   // entry i = G[al][be][de][ga]
   const int al = i >> 6, be = (i >> 4) & 3, de = (i >> 2) & 3, ga = i & 3;

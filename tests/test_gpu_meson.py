@@ -5,6 +5,8 @@ Tolerance: relative 1e-12 (max-norm over the tensor, resp. over each
 correlator): both sides sum the same FP64 products, in different orders,
 over at most a few thousand sites per slice.
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -113,3 +115,40 @@ def test_meson_full_size_sampled_slices():
         assert abs(Cg[0, t] - orc.meson_correlator(G_ref[None], 15, 15)[0]) < 1e-12 * abs(Cg[0, t])
     del psi
     torch.cuda.empty_cache()
+
+
+# Columns that differ by a phase that barely varies, or by that and a factor i
+# (spins tied by a gamma matrix): every entry of G has one large part and one
+# that all but cancels.  That part is held to the rounding of its own terms:
+# 9 V3 pairs of products |z_i z_j| ~ 1, a rounding of u = 2^-53 of each pair's
+# size, adding up like a random walk, times 8.  (A sum of one product over the
+# slice, subtracted from its transpose afterwards, is off by the rounding of that
+# sum, which is as large as the other part.)  16^3: 64-site chunks, summed by the
+# second kernel; 8^3: one chunk a slice, summed in the first.
+@pytest.mark.parametrize("L", [(16, 16, 16, 4), (8, 8, 8, 2048)], ids=lambda L: "x".join(map(str, L)))
+def test_meson_parts_that_cancel(L):
+    print(f"\n[gpu case] meson cancelling parts {L}", flush=True)
+    T, V3 = L[3], L[0] * L[1] * L[2]
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    ph = torch.randn((12, T, V3, 4, 3), generator=gen, dtype=torch.float64, device="cuda").mul_(0.05).add_(0.7)
+    spin = torch.arange(4, device="cuda")
+    col = torch.arange(12, device="cuda") // 3
+    ph += (math.pi / 2) * ((col[:, None] + spin[None, :]) % 2)[:, None, None, :, None]
+    psi = torch.polar(1 + 0.3 * torch.rand(ph.shape, generator=gen, dtype=torch.float64, device="cuda"), ph)
+    del ph
+    lat = lqcd.Lattice(L, lqcd.BC_PERIODIC, (1, 1, 1, -1))
+    _, G = lqcd.meson(lat, psi.reshape(12, T, L[2], L[1], L[0], 4, 3), [], lqcd.Workspace(lat, lqcd.PM_F64, 1))
+    G = G.cpu().numpy()
+    par = (np.arange(4)[:, None] + np.arange(4)[None, :]) % 2  # [al][be]
+    for t in {0, T // 2, T - 1}:
+        z = psi[:, t].cpu().numpy().reshape(4, 3, V3, 4, 3).transpose(3, 0, 2, 4, 1).reshape(16, -1)  # [(al, be)][x, a, c]
+        zr, zi = z.real.astype(np.longdouble), z.imag.astype(np.longdouble)
+        # term by term, in 64-bit mantissas (products summed one by one would cancel here too)
+        re = np.stack([(zr[i] * zr + zi[i] * zi).sum(axis=1) for i in range(16)])
+        im = np.stack([(zi[i] * zr - zr[i] * zi).sum(axis=1) for i in range(16)])
+        small = (par.reshape(-1)[:, None] != par.reshape(-1)[None, :])  # Re is the small part
+        g = G[t].reshape(16, 16)
+        err = np.where(small, np.abs(g.real - re), np.abs(g.imag - im)).astype(np.float64)
+        tol = 8 * 2.0 ** -53 * math.sqrt(9 * V3) * 1.3 ** 2
+        assert err.max() <= tol, (t, err.max(), tol)
+        assert rel_max(g, (re + 1j * im).astype(np.complex128)) < 1e-12
