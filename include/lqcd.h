@@ -261,10 +261,11 @@ typedef struct lqcd_tuning {
 enum { LQCD_TUNE_NT_STORE = 1, LQCD_TUNE_CACHED_GAUGE = 2, LQCD_TUNE_OCC_SHIFT = 2,
        LQCD_TUNE_DIR_SPLIT = 16 };
 
-/* Hop-kernel configuration used by a workspace for precision `prec`
- * (default: nr_tile 1, block_order 1, rhs_lanes 1, as lqcd_ws_get_tuning
- * returns it; until a configuration is set or autotuned, launches choose
- * theirs by lattice size, precision and rhs count).  A launch over n rhs uses
+/* Hop-kernel configuration used by a workspace for precision `prec`.  The
+ * default, nr_tile 1, block_order 1, rhs_lanes 1, no flags, leaves it to the
+ * launches, which choose by lattice size, precision and rhs count; setting it
+ * gives the choice back to them (so that get, set another, set the first back
+ * restores a workspace).  A launch over n rhs uses
  * the largest rhs_lanes and nr_tile not above these whose product divides n.
  * EINVAL for values out of range.  None of these changes the arithmetic of
  * any rhs, except LQCD_TUNE_DIR_SPLIT: with it the eight hop terms of a site

@@ -653,7 +653,7 @@ extern "C" int lqcd_ws_set_tuning(lqcd_ws_t* w, int prec, const lqcd_tuning* t) 
                      LQCD_TUNE_DIR_SPLIT)))
     return fail(LQCD_EINVAL, "lqcd_ws_set_tuning: value out of range");
   w->tune[prec] = *t;
-  w->tune_set[prec] = true;
+  w->tune_set[prec] = !same_tuning(*t, kDefaultTuning);  // the default: the launches choose
   return LQCD_OK;
 }
 

@@ -70,6 +70,10 @@ inline bool same_tuning(const lqcd_tuning& a, const lqcd_tuning& b) {
          a.flags == b.flags;
 }
 
+// the configuration of a workspace nobody tuned (nr, order, lanes, flags): it
+// stands for own_tuning, and setting it gives the choice back to the launches
+constexpr lqcd_tuning kDefaultTuning = {1, 1, 1, 0};
+
 struct lqcd_ws {
   const lqcd_geom_t* g;
   int pmask;
@@ -81,8 +85,8 @@ struct lqcd_ws {
   double kappa = 0, csw = 0, cF = 0, mu = 0;
   int clover_pmask = 0;
   std::vector<GraphEntry> graphs;
-  lqcd_tuning tune[3] = {{1, 1, 1, 0}, {1, 1, 1, 0}, {1, 1, 1, 0}};  // nr, order, lanes, flags
-  bool tune_set[3] = {false, false, false};  // set by the caller or the autotuner (else: own_tuning)
+  lqcd_tuning tune[3] = {kDefaultTuning, kDefaultTuning, kDefaultTuning};
+  bool tune_set[3] = {false, false, false};  // not the default (else: own_tuning)
 };
 
 namespace lqcd {

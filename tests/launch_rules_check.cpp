@@ -102,10 +102,51 @@ static void converted_configurations() {
   }
 }
 
+// Setting what lqcd_ws_get_tuning returned for a workspace nobody tuned changes
+// nothing: at once, and after another setting it gives the choice back to the
+// launches.
+static void tuning_round_trip() {
+  for (int prec = LQCD_F64; prec <= LQCD_BF16; ++prec)
+    for (int nrhs : {1, 3, 4, 12})
+      for (int T : {8, 32, 256}) {
+        lqcd_geom_desc d;
+        memset(&d, 0, sizeof(d));
+        for (int mu = 0; mu < 4; ++mu) {
+          d.L[mu] = mu == 3 ? T : 16;
+          d.theta_re[mu] = 1.0;
+        }
+        lqcd_geom_t* g = nullptr;
+        lqcd_ws_t* w = nullptr;
+        CHECK(lqcd_geom(&d, &g) == LQCD_OK, "geometry");
+        // only recorded, never dereferenced here
+        CHECK(lqcd_ws_create(g, 7, nrhs, (void*)(uintptr_t)(1 << 20), ~size_t(0), &w) == LQCD_OK, "workspace");
+        const auto untouched = [&](const char* when) {
+          for (int n : {1, nrhs})
+            CHECK(same_tuning(tuning_of(w, prec, n), own_tuning(w->g->V, prec, n)), "prec %d nrhs %d T %d n %d: %s", prec,
+                  nrhs, T, n, when);
+        };
+        lqcd_tuning first;
+        CHECK(lqcd_ws_get_tuning(w, prec, &first) == LQCD_OK, "get");
+        CHECK(same_tuning(first, lqcd_tuning{1, 1, 1, 0}), "prec %d: the documented default", prec);
+        CHECK(lqcd_ws_set_tuning(w, prec, &first) == LQCD_OK, "set");
+        untouched("set(get())");
+        lqcd_tuning other = first;  // one field changed
+        other.flags |= LQCD_TUNE_DIR_SPLIT;
+        lqcd_tuning back;
+        CHECK(lqcd_ws_set_tuning(w, prec, &other) == LQCD_OK && lqcd_ws_get_tuning(w, prec, &back) == LQCD_OK, "set");
+        CHECK(same_tuning(back, other) && same_tuning(tuning_of(w, prec, 1), other), "a set configuration is used");
+        CHECK(lqcd_ws_set_tuning(w, prec, &first) == LQCD_OK, "set");
+        untouched("restored");
+        lqcd_ws_free(w);
+        lqcd_geom_free(g);
+      }
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!strcmp(argv[i], "small_launches")) small_launches();
     else if (!strcmp(argv[i], "own_configurations")) own_configurations();
+    else if (!strcmp(argv[i], "tuning_round_trip")) tuning_round_trip();
     else if (!strcmp(argv[i], "converted_configurations")) converted_configurations();
     else {
       printf("unknown check %s\n", argv[i]);
