@@ -275,12 +275,14 @@ enum { LQCD_TUNE_NT_STORE = 1, LQCD_TUNE_CACHED_GAUGE = 2, LQCD_TUNE_OCC_SHIFT =
 int lqcd_ws_set_tuning(lqcd_ws_t *w, int prec, const lqcd_tuning *t);
 int lqcd_ws_get_tuning(const lqcd_ws_t *w, int prec, lqcd_tuning *t);
 
-/* Autotuner: times every candidate configuration (nr_tile x rhs_lanes
- * dividing nrhs, block_order, flags) of one Schur-operator application (both hop kernels)
- * in precision `prec` on nrhs fields of the workspace, with HIP events on
- * `stream`, at the workspace's real lattice shape; stores the fastest in the
- * workspace and in the process-wide tuning cache (below), and returns it with
- * its time in microseconds.  The
+/* Autotuner: times the default and every candidate configuration (nr_tile x
+ * rhs_lanes dividing nrhs, block_order, flags) of one Schur-operator application
+ * (both hop kernels) in precision `prec` on nrhs fields of the workspace, with HIP
+ * events on `stream`, at the workspace's real lattice shape; stores the fastest in
+ * the workspace and in the process-wide tuning cache (below), and returns it with
+ * its time in microseconds.  Hops of small lattices run in a form that takes no
+ * configuration: where both do, an application over both parities is timed
+ * instead, and where that does too the default is the result.  The
  * LQCD_TUNE_DIR_SPLIT bit is the caller's choice and is kept as set in the
  * workspace; with it set only nr_tile = rhs_lanes = 1 (the shape it applies
  * to) is searched, so autotuning never changes a result.  Overwrites the

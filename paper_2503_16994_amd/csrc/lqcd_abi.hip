@@ -683,7 +683,6 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
   LQCD_HIP(hipEventCreate(&e1));
   const lqcd_tuning saved = w->tune[prec];
   const bool saved_set = w->tune_set[prec];
-  w->tune_set[prec] = true;  // the trials set it
   const int keep = saved.flags & LQCD_TUNE_DIR_SPLIT;  // the caller's choice
   double best_t = 1e300;
   lqcd_tuning best_cfg = saved;
@@ -692,9 +691,17 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
   // LQCD_TUNE_LOG=1: every candidate's time on stderr (diagnostics)
   const char* log_env = getenv("LQCD_TUNE_LOG");
   const bool log_trials = log_env && log_env[0] == '1';
-  // times the workspace's current tuning; keeps it if it is the fastest so far
-  auto trial = [&]() {
+  // What is timed: the two hops of a Schur-operator application, or where those are
+  // small launches (which take no configuration) a launch over both parities.
+  // Where that is small too, nothing takes one: only the default is timed.
+  const bool hops_small = hop_nparts(base_launch(c, false)) < 0;
+  const bool all_small = hops_small && hop_nparts(base_launch(c, false, true)) < 0;
+  // times configuration t; keeps it if it is the fastest so far
+  auto trial = [&](const lqcd_tuning& t) {
+    w->tune[prec] = t;
+    w->tune_set[prec] = !same_tuning(t, kDefaultTuning);
     auto once = [&]() -> hipError_t {
+      if (hops_small) return apply_dw_full(c, w->m.X, w->m.TMP, false);
       hipError_t e = apply_hop_eo(c, w->m.X, w->m.R);
       if (e == hipSuccess) e = apply_hop_oe(c, w->m.X, w->m.R, w->m.TMP, false);
       return e;
@@ -713,17 +720,17 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
       if (err == hipSuccess && 1e3 * ms < us) us = 1e3 * ms;
     }
     if (err == hipSuccess && log_trials) {
-      const lqcd_tuning& t = w->tune[prec];
       fprintf(stderr, "lqcd_autotune V=%lld prec=%d nrhs=%d nr_tile=%d rhs_lanes=%d order=%d flags=%d us=%.2f\n",
               (long long)w->g->V, prec, nrhs, t.nr_tile, t.rhs_lanes, t.block_order, t.flags, us);
     }
     if (err == hipSuccess && us < best_t) {
       best_t = us;
-      best_cfg = w->tune[prec];
+      best_cfg = t;
     }
   };
+  if (!keep) trial(kDefaultTuning);  // what the launches choose themselves
   // pass 1: rhs lanes, rhs tile, block order, store and load kinds
-  for (int rl = 1; rl <= 4 && err == hipSuccess; rl *= 2) {
+  for (int rl = 1; rl <= 4 && err == hipSuccess && !all_small; rl *= 2) {
     if (nrhs % rl || (prec == P_F64 && rl > 1)) continue;
     for (int nr = 1; nr <= 3 && err == hipSuccess; ++nr) {
       if (nrhs % (nr * rl)) continue;
@@ -731,17 +738,18 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
       for (int cfg = 0; cfg < 28 && err == hipSuccess; ++cfg) {
         const int order = cfg >> 2;
         const int flags = ((cfg & 1) ? LQCD_TUNE_NT_STORE : 0) | ((cfg & 2) ? LQCD_TUNE_CACHED_GAUGE : 0) | keep;
-        w->tune[prec] = lqcd_tuning{nr, order, rl, flags};
-        trial();
+        const lqcd_tuning t = {nr, order, rl, flags};
+        if (!same_tuning(t, kDefaultTuning)) trial(t);
       }
     }
   }
   // pass 2: occupancy caps on the best configuration
-  const lqcd_tuning base = best_cfg;
-  for (int level = 1; level <= 3 && err == hipSuccess; ++level) {
-    w->tune[prec] = base;
-    w->tune[prec].flags = (base.flags & ~(3 << LQCD_TUNE_OCC_SHIFT)) | (level << LQCD_TUNE_OCC_SHIFT);
-    trial();
+  lqcd_tuning base = best_cfg;
+  if (same_tuning(base, kDefaultTuning)) base = own_tuning(w->g->V, prec, nrhs);
+  for (int level = 1; level <= 3 && err == hipSuccess && !all_small; ++level) {
+    lqcd_tuning t = base;
+    t.flags = (base.flags & ~(3 << LQCD_TUNE_OCC_SHIFT)) | (level << LQCD_TUNE_OCC_SHIFT);
+    trial(t);
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
@@ -751,6 +759,7 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
     return hip_status(err, "lqcd_autotune");
   }
   w->tune[prec] = best_cfg;
+  w->tune_set[prec] = !same_tuning(best_cfg, kDefaultTuning);
   tune_cache_put(u, prec, nrhs, d->mu != 0.0, best_cfg, best_t);
   if (best) *best = best_cfg;
   if (best_us) *best_us = best_t;

@@ -70,3 +70,31 @@ def test_small_solves_equal_the_general_ones(solver, inner, mu):
         for j, one in alone.items():
             assert one.info[0]["iters"] == batch.info[j]["iters"], (tune, j)
             assert torch.equal(one.psi[0], batch.psi[j]), (tune, j)
+
+
+def test_autotuning_leaves_small_lattices_to_the_default():
+    """8^4: every FP32 launch of one field is small and takes no configuration, so
+    there is nothing to choose (a choice would be noise, and would apply to this
+    workspace's and the cache's other launches); with 12 fields the launch over both
+    parities is general and takes what was timed on it."""
+    L = (8, 8, 8, 8)
+    print(f"\n[gpu case] autotune {L}", flush=True)
+    lat, g = system(L, P, True)
+    d = lqcd.dirac(0.123, 1.7)
+    default = dict(nr_tile=1, block_order=1, rhs_lanes=1, nt_store=False, cached_gauge=False, occ_cap=0, dir_split=False)
+    lqcd.tune_cache_clear()
+    try:
+        ws = lqcd.Workspace(lat, PM, 1)
+        for prec in (lqcd.F64, lqcd.F32, lqcd.BF16):
+            for _ in range(3):
+                best, us = lqcd.autotune(g, d, prec, 1, ws)
+                assert best == default and us > 0
+                assert lqcd.get_tuning(ws, prec) == default and lqcd.tune_cache_find(g, prec, 1) == default
+        many = lqcd.Workspace(lat, PM, 12)
+        x = torch.from_numpy(np.stack([inputs.gaussian_spinor(L, k, P) for k in range(12)])).cuda()
+        before = lqcd.dw_apply(g, d, x, op=lqcd.OP_DW, prec=lqcd.F32, ws=many)
+        best, us = lqcd.autotune(g, d, lqcd.F32, 12, many)
+        assert us > 0 and lqcd.get_tuning(many, lqcd.F32) == best == lqcd.tune_cache_find(g, lqcd.F32, 12)
+        assert torch.equal(lqcd.dw_apply(g, d, x, op=lqcd.OP_DW, prec=lqcd.F32, ws=many), before)
+    finally:
+        lqcd.tune_cache_clear()
