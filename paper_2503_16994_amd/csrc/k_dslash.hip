@@ -1284,6 +1284,17 @@ int hop_nparts(const HopLaunch& h0) {
   return hop_nblocks(h);
 }
 
+// the block order that a launch of this shape runs: the slab orders need whole
+// workgroups per (z, t) plane and a whole number of slabs
+int hop_order(const HopLaunch& h) {
+  const bool slab_ok =
+      (h.g.L[2] % 8) == 0 && ((long)h.g.Lxh * h.g.L[1]) % sites_per_block(h.rhs_lanes, split_on(h)) == 0;
+  if ((h.order == 2 || h.order == 5) && !slab_ok) return 1;
+  if (h.order == 6 && !(slab_ok && (h.g.L[2] % 16) == 0)) return 1;
+  if (h.order == 4 && !slab_ok) return 3;
+  return h.order < 0 || h.order > 6 ? 1 : h.order;
+}
+
 // fill in nbs/bpp and validate the block order for this launch
 static bool prepare(HopLaunch& h) {
   if (h.rhs_lanes != 1 && h.rhs_lanes != 2 && h.rhs_lanes != 4) return false;
@@ -1291,14 +1302,8 @@ static bool prepare(HopLaunch& h) {
   if (h.nrhs % (h.nr_tile * h.rhs_lanes) != 0) return false;
   h.nbs = hop_nblocks(h);
   h.lds_cap = lds_cap_bytes(h.occ_cap);
-  const int spb = sites_per_block(h.rhs_lanes, split_on(h));
-  const long P = (long)h.g.Lxh * h.g.L[1];
-  h.bpp = (int)(P / spb);
-  const bool slab_ok = (h.g.L[2] % 8) == 0 && (P % spb) == 0;
-  if ((h.order == 2 || h.order == 5) && !slab_ok) h.order = 1;
-  if (h.order == 6 && !(slab_ok && (h.g.L[2] % 16) == 0)) h.order = 1;
-  if (h.order == 4 && !slab_ok) h.order = 3;
-  if (h.order < 0 || h.order > 6) h.order = 1;
+  h.bpp = (int)((long)h.g.Lxh * h.g.L[1] / sites_per_block(h.rhs_lanes, split_on(h)));
+  h.order = hop_order(h);
   return true;
 }
 

@@ -728,6 +728,13 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
       best_cfg = t;
     }
   };
+  // the block order that the timed launches run under configuration t
+  auto order_run = [&](const lqcd_tuning& t) {
+    HopLaunch h = base_launch(c, false, hops_small);
+    apply_tuning(h, t);
+    if (c.mu != 0.0) single_tile(h);
+    return hop_order(h);
+  };
   if (!keep) trial(kDefaultTuning);  // what the launches choose themselves
   // pass 1: rhs lanes, rhs tile, block order, store and load kinds
   for (int rl = 1; rl <= 4 && err == hipSuccess && !all_small; rl *= 2) {
@@ -739,13 +746,17 @@ extern "C" int lqcd_autotune(const lqcd_gauge_t* u, const lqcd_dirac* d, int pre
         const int order = cfg >> 2;
         const int flags = ((cfg & 1) ? LQCD_TUNE_NT_STORE : 0) | ((cfg & 2) ? LQCD_TUNE_CACHED_GAUGE : 0) | keep;
         const lqcd_tuning t = {nr, order, rl, flags};
-        if (!same_tuning(t, kDefaultTuning)) trial(t);
+        if (same_tuning(t, kDefaultTuning)) continue;
+        if (order_run(t) == order) trial(t);  // else another candidate under its name
       }
     }
   }
   // pass 2: occupancy caps on the best configuration
   lqcd_tuning base = best_cfg;
-  if (same_tuning(base, kDefaultTuning)) base = own_tuning(w->g->V, prec, nrhs);
+  if (same_tuning(base, kDefaultTuning)) {
+    base = own_tuning(w->g->V, prec, nrhs, hops_small);
+    base.block_order = order_run(base);
+  }
   for (int level = 1; level <= 3 && err == hipSuccess && !all_small; ++level) {
     lqcd_tuning t = base;
     t.flags = (base.flags & ~(3 << LQCD_TUNE_OCC_SHIFT)) | (level << LQCD_TUNE_OCC_SHIFT);

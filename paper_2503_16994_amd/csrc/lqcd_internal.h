@@ -139,7 +139,7 @@ struct HopSpec {
 //    two (or three for an odd n, in FP32 for any multiple of three) once there
 //    are enough.
 //  * From 10^6 sites on, z-slabs per XCD; in FP64 with several rhs from 10^6
-//    sites times rhs on.
+//    sites times rhs on (plain order where planes do not divide, see hop_order).
 // Against non-temporal loads and one rhs per thread everywhere, us per pair of
 // hops on fields of zeros: FP64 12^3x24 12 rhs 123 / 89, 16^3x32 1 rhs 47.5 / 43.1,
 // 4 rhs 136 / 98, 12 rhs 391 / 295, 24^3x48 12 rhs 2632 / 1701, 32^3x64 1 rhs

@@ -98,3 +98,22 @@ def test_autotuning_leaves_small_lattices_to_the_default():
         assert torch.equal(lqcd.dw_apply(g, d, x, op=lqcd.OP_DW, prec=lqcd.F32, ws=many), before)
     finally:
         lqcd.tune_cache_clear()
+
+
+@pytest.mark.parametrize("L,orders", [((12, 12, 8, 8), {0, 1, 3}), ((16, 16, 16, 4), {0, 1, 2, 3, 4, 5, 6})],
+                         ids=["72-site planes", "128-site planes"])
+def test_autotuning_tries_the_orders_that_run(L, orders, monkeypatch, capfd):
+    """Slab orders need whole 128-site workgroups per (z, t) plane; where they do
+    not have them they run as order 1 or 3, and are not tried under their name."""
+    print(f"\n[gpu case] autotune orders {L}", flush=True)
+    lat, g = system(L, P, True)
+    monkeypatch.setenv("LQCD_TUNE_LOG", "1")
+    capfd.readouterr()
+    lqcd.tune_cache_clear()
+    try:
+        best, _ = lqcd.autotune(g, lqcd.dirac(0.123, 1.7), lqcd.F32, 12, lqcd.Workspace(lat, PM, 12))
+    finally:
+        lqcd.tune_cache_clear()
+    log = [ln for ln in capfd.readouterr().err.splitlines() if ln.startswith("lqcd_autotune")]
+    tried = {int(dict(f.split("=") for f in ln.split()[1:])["order"]) for ln in log}
+    assert tried == orders and best["block_order"] in orders
