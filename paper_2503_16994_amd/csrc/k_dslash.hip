@@ -1211,11 +1211,12 @@ static unsigned lds_cap_bytes(int level) {
   }
 }
 
-// most partial sums per rhs any hop launch writes on V2 sites per parity:
-// 4 rhs lanes (fewest sites per workgroup), or both parities split
+// most partial sums per rhs a launch of k_hop writes on V2 sites per parity: 4 rhs
+// lanes (fewest sites per workgroup), or both parities split (a small launch
+// writes at most 514: 512 workgroups, whole pairs per parity)
 int hop_max_parts(long V2) {
   const long one = (V2 + sites_per_block(4) - 1) / sites_per_block(4);
-  const long both = 2 * ((V2 + sites_per_block(1, true) - 1) / sites_per_block(1, true) + 1);  // whole pairs
+  const long both = 2 * ((V2 + sites_per_block(1, true) - 1) / sites_per_block(1, true));
   return (int)(one > both ? one : both);
 }
 

@@ -236,7 +236,7 @@ WsLayout plan_ws(const lqcd_geom_t* g, int pmask, int nrhs, char* base) {
     m.tb = (bf16x2*)take(half16);
   }
   const int hop_parts = hop_max_parts(g->V2);
-  m.max_parts = hop_parts > 2048 ? hop_parts : 2048;
+  m.max_parts = hop_parts > 2048 ? hop_parts : 2048;  // 2048: the vector kernels' sums; small hop launches have fewer
   m.partials = (double*)take((size_t)nrhs * m.max_parts * sizeof(double));
   m.partials2 = (double*)take((size_t)nrhs * m.max_parts * sizeof(double));
   m.cg = (CGState*)take((size_t)nrhs * sizeof(CGState));

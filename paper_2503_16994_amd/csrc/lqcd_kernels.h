@@ -124,7 +124,7 @@ struct HopLaunch {
 
 int hop_nblocks(const HopLaunch& h);
 int hop_order(const HopLaunch& h);  // block order it runs (slab orders fall back where planes do not divide)
-int hop_max_parts(long V2);  // bound on partials per rhs of any hop launch
+int hop_max_parts(long V2);  // bound on partials per rhs of a hop launch that is not small
 int hop_nparts(const HopLaunch& h);  // partials per rhs of a tiled hop launch, as parts_count takes them
 hipError_t launch_hop(const HopLaunch& h, hipStream_t st);
 // whether a launch of this shape can update the search direction it is applied

@@ -142,10 +142,43 @@ static void tuning_round_trip() {
       }
 }
 
+// Workspaces keep their size, and hold the partial sums of every launch form.
+static void workspace_bytes() {
+  const struct {
+    int L[4];
+    size_t one, twelve;  // FP64 for one rhs; every precision for twelve
+  } want[] = {{{16, 16, 16, 32}, 314606336, 3180727808}, {{24, 24, 24, 48}, 1592691456, 16102419968},
+              {{32, 32, 32, 64}, 5033689856, 50891591168}, {{26, 26, 26, 30}, 1265796864, 12797448704},
+              {{32, 32, 32, 32}, 2516845312, 25445797376}};
+  for (const auto& w : want) {
+    lqcd_geom_desc d;
+    memset(&d, 0, sizeof(d));
+    for (int mu = 0; mu < 4; ++mu) {
+      d.L[mu] = w.L[mu];
+      d.theta_re[mu] = 1.0;
+    }
+    lqcd_geom_t* g = nullptr;
+    CHECK(lqcd_geom(&d, &g) == LQCD_OK, "geometry");
+    CHECK(lqcd_ws_bytes(g, LQCD_PM_F64, 1) == w.one, "T %d: %zu", w.L[3], lqcd_ws_bytes(g, LQCD_PM_F64, 1));
+    CHECK(lqcd_ws_bytes(g, 7, 12) == w.twelve, "T %d: %zu", w.L[3], lqcd_ws_bytes(g, 7, 12));
+    lqcd_geom_free(g);
+  }
+  for (int prec = P_F64; prec <= P_BF16; ++prec)
+    for (int nrhs : {1, 2, 4, 12})
+      for (int both = 0; both < 2; ++both)
+        for (long V2 = 16; V2 < 40000; V2 += 8) {
+          const int n = parts_stride(hop_nparts(hop(prec, V2, nrhs, both != 0, 0.0)));
+          const int max = hop_max_parts(V2) > 2048 ? hop_max_parts(V2) : 2048;
+          CHECK(n <= max, "prec %d nrhs %d both %d V2 %ld: %d partials", prec, nrhs, both, V2, n);
+          if (failures > 10) return;
+        }
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!strcmp(argv[i], "small_launches")) small_launches();
     else if (!strcmp(argv[i], "own_configurations")) own_configurations();
+    else if (!strcmp(argv[i], "workspace_bytes")) workspace_bytes();
     else if (!strcmp(argv[i], "tuning_round_trip")) tuning_round_trip();
     else if (!strcmp(argv[i], "converted_configurations")) converted_configurations();
     else {

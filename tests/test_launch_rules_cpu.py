@@ -25,7 +25,8 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["small_launches", "own_configurations", "converted_configurations", "tuning_round_trip"])
+@pytest.mark.parametrize("check", ["small_launches", "own_configurations", "converted_configurations", "tuning_round_trip",
+                                   "workspace_bytes"])
 def test_rule(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
