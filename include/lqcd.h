@@ -222,9 +222,10 @@ int lqcd_meson(const lqcd_geom_t *g, const void *psi, int npairs, const int32_t 
 size_t lqcd_noalloc_scratch_bytes(void);
 
 /* lqcd_meson without a workspace: same arguments, results and errors, and
- * the same kernels, with the T x ceil(Lx Ly Lz / 256) x 256 complex128
- * partials in the fixed array instead of the workspace (32^3x64 needs all
- * 32 MiB).  EINVAL, without device work, for a lattice whose partials exceed
+ * the same kernels, with their partial sums (4 KiB each, at most
+ * max(T x ceil(Lx Ly Lz / 256), 4096) of them; 8 MiB at 32^3x64) in the fixed
+ * array instead of the workspace.  EINVAL, without device work, for a lattice
+ * with T x ceil(Lx Ly Lz / 256) x 4 KiB above
  * LQCD_NOALLOC_SCRATCH_BYTES.  Calls no allocating routine; the first call
  * on a device looks up the array's address there (EDEVICE if that fails). */
 int lqcd_meson_noalloc(const lqcd_geom_t *g, const void *psi, int npairs, const int32_t *pairs, void *C,

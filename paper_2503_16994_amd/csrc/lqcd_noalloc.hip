@@ -14,7 +14,7 @@ using namespace lqcd;
 
 namespace {
 
-// meson partials of the largest supported lattice (see lqcd.h)
+// meson partials of any lattice within the size limit (see lqcd.h)
 static __device__ __align__(256) double2 scratch[LQCD_NOALLOC_SCRATCH_BYTES / sizeof(double2)];
 
 constexpr int kMaxDevices = 64;
@@ -55,7 +55,8 @@ extern "C" int lqcd_meson_noalloc(const lqcd_geom_t* g, const void* psi, int npa
                                   void* G, void* stream) {
   const int rc = meson_check("lqcd_meson_noalloc", g, psi, npairs, pairs, C, G);
   if (rc) return rc;
-  // the documented bound; the launch itself never needs more than this or 16 MiB
+  // the documented limit; the launch itself needs at most this or 16 MiB
+  static_assert(LQCD_NOALLOC_SCRATCH_BYTES >= (16u << 20), "the launch's own bound");
   const size_t V3 = (size_t)g->desc.L[0] * g->desc.L[1] * g->desc.L[2];
   const size_t need = (size_t)g->desc.L[3] * ((V3 + 255) / 256) * 256 * sizeof(double2);
   if (need > (size_t)LQCD_NOALLOC_SCRATCH_BYTES)

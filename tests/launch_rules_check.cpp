@@ -174,11 +174,30 @@ static void workspace_bytes() {
         }
 }
 
+// Partial sums of the meson contraction: within the bound the header gives, hence
+// within the fixed array for every lattice that lqcd_meson_noalloc accepts, and
+// within the smallest workspace.
+static void meson_scratch() {
+  constexpr size_t kPartial = 256 * 2 * sizeof(double);
+  CHECK(64 * meson_nchunk(32 * 32 * 32, 64) * kPartial == 8u << 20, "32^3x64: %d", meson_nchunk(32 * 32 * 32, 64));
+  for (int T = 4; T <= 4096; T += T < 128 ? 2 : 62)
+    for (long V3 = 8; V3 <= 262144; V3 += V3 < 4096 ? 8 : V3 / 64 * 4) {
+      const size_t limit = (size_t)T * ((V3 + 255) / 256), n = (size_t)T * meson_nchunk(V3, T);
+      CHECK(n <= (limit > 4096 ? limit : 4096), "T %d V3 %ld: %zu partials", T, V3, n);
+      if (limit * kPartial <= LQCD_NOALLOC_SCRATCH_BYTES)
+        CHECK(n * kPartial <= LQCD_NOALLOC_SCRATCH_BYTES, "T %d V3 %ld: %zu partials", T, V3, n);
+      const size_t ws = (size_t)8 * 24 * padded_sites(V3 * T / 2) * 16;  // the FP64 vectors of one rhs
+      CHECK(n * kPartial <= ws, "T %d V3 %ld: %zu partials, workspace %zu", T, V3, n, ws);
+      if (failures > 10) return;
+    }
+}
+
 int main(int argc, char** argv) {
   for (int i = 1; i < argc; ++i) {
     if (!strcmp(argv[i], "small_launches")) small_launches();
     else if (!strcmp(argv[i], "own_configurations")) own_configurations();
     else if (!strcmp(argv[i], "workspace_bytes")) workspace_bytes();
+    else if (!strcmp(argv[i], "meson_scratch")) meson_scratch();
     else if (!strcmp(argv[i], "tuning_round_trip")) tuning_round_trip();
     else if (!strcmp(argv[i], "converted_configurations")) converted_configurations();
     else {

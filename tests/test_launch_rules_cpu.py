@@ -26,7 +26,7 @@ def program(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["small_launches", "own_configurations", "converted_configurations", "tuning_round_trip",
-                                   "workspace_bytes"])
+                                   "workspace_bytes", "meson_scratch"])
 def test_rule(program, check):
     r = subprocess.run([program, check], capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
