@@ -117,31 +117,27 @@ __global__ void k_cg_beta(CGState* s, const double* partials, int nparts) {
   if (threadIdx.x == 0) beta_step(s[r], v);
 }
 
-// x += alpha p ; r -= alpha Ap ; |r|^2 partials   (x may be wider than r)
-template <typename SX, typename S>
-__global__ void k_cg_xr(SX* x, S* r, const S* __restrict__ p, const S* __restrict__ Ap, long n,
+// x += alpha p ; r -= alpha Ap ; |r|^2 partials (the full-lattice solver, FP64)
+__global__ void k_cg_xr(double2* x, double2* r, const double2* __restrict__ p, const double2* __restrict__ Ap, long n,
                         long rsx, long rs, const CGState* cs, double* partials) {
   __shared__ double sh[4];
   const int q = blockIdx.y;
   if (cs[q].done) return;
-  using A = typename StoreTraits<S>::acc;
-  const double alpha_d = cs[q].alpha;
-  const A alpha = (A)alpha_d;
+  const double alpha = cs[q].alpha;
   const size_t o = (size_t)q * rs, ox = (size_t)q * rsx;
   double acc = 0.0;
   for (long i = (long)blockIdx.x * kB + threadIdx.x; i < n; i += (long)gridDim.x * kB) {
-    auto pv = ld(p + o + i);
-    auto av = ld(Ap + o + i);
+    const auto pv = ld(p + o + i);
+    const auto av = ld(Ap + o + i);
     auto xv = ld(x + ox + i);
     auto rv = ld(r + o + i);
-    using AX = decltype(xv.re);
-    xv.re += (AX)alpha_d * (AX)pv.re;
-    xv.im += (AX)alpha_d * (AX)pv.im;
+    xv.re += alpha * pv.re;
+    xv.im += alpha * pv.im;
     rv.re -= alpha * av.re;
     rv.im -= alpha * av.im;
     st(x + ox + i, xv);
     st(r + o + i, rv);
-    acc += (double)rv.re * (double)rv.re + (double)rv.im * (double)rv.im;
+    acc += rv.re * rv.re + rv.im * rv.im;
   }
   double b = bsum(acc, sh);
   if (threadIdx.x == 0) partials[(size_t)q * gridDim.x + blockIdx.x] = b;
@@ -172,24 +168,23 @@ __device__ inline void st4(float2* p, const cpx<float> (&v)[4]) {
   *reinterpret_cast<float4*>(p + 2) = make_float4(v[2].re, v[2].im, v[3].re, v[3].im);
 }
 
-// pn = r + beta p over the n elements of one rhs (offset o), and plo = pn if
-// given; p and pn may be the same vector.  load() fetches this thread's first
+// pn = r + beta p over the n elements of one rhs (offset o); p and pn may be the
+// same vector.  load() fetches this thread's first
 // elements, so that a small launch has them in flight while beta is formed;
-// run() does the update.  BF16-only directions move four elements a lane.
-template <typename S, typename SP, typename SL>
+// run() does the update.  BF16 directions move four elements a lane.
+template <typename S, typename SP>
 struct PUpdate {
   using A = typename StoreTraits<S>::acc;
   const SP* p;
   SP* pn;
   const S* r;
-  SL* plo;
   size_t o;
   long n;
   bool four;
   cpx<A> pv[4], rv[4];
-  __device__ inline PUpdate(const SP* p_, SP* pn_, const S* r_, SL* plo_, size_t o_, long n_)
-      : p(p_), pn(pn_), r(r_), plo(plo_), o(o_), n(n_) {
-    four = std::is_same<SP, bf16x2>::value && plo == nullptr && (n & 3) == 0 && (o & 3) == 0;
+  __device__ inline PUpdate(const SP* p_, SP* pn_, const S* r_, size_t o_, long n_)
+      : p(p_), pn(pn_), r(r_), o(o_), n(n_) {
+    four = std::is_same<SP, bf16x2>::value && (n & 3) == 0 && (o & 3) == 0;
   }
   __device__ inline long first() const { return (long)blockIdx.x * kB + threadIdx.x; }
   __device__ inline long count() const { return four ? n >> 2 : n; }
@@ -222,16 +217,15 @@ struct PUpdate {
         }
       }
       st(pn + o + i, pv[0]);
-      if (plo) st(plo + o + i, pv[0]);
     }
   }
 };
 
-// p = r + beta p ; optional low-precision copy of p
-template <typename S, typename SP, typename SL>
-__global__ void k_cg_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, const CGState* cs, SL* plo) {
+// pn = r + beta p
+template <typename S, typename SP>
+__global__ void k_cg_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, const CGState* cs) {
   const int q = blockIdx.y;
-  PUpdate<S, SP, SL> u(p, pn, r, plo, (size_t)q * rs, n);
+  PUpdate<S, SP> u(p, pn, r, (size_t)q * rs, n);
   u.load();
   if (cs[q].done) return;
   using A = typename StoreTraits<S>::acc;
@@ -244,13 +238,13 @@ __global__ void k_cg_p(const SP* p, SP* pn, const S* __restrict__ r, long n, lon
 // A rhs that workgroup 0 marks done meanwhile may see p updated by only some
 // workgroups (each as a whole), which is harmless: done is final here (only the
 // reliable update's finish kernel sets the resumable CG_STALLED).
-template <typename S, typename SP, typename SL>
-__global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, CGState* cs, SL* plo,
+template <typename S, typename SP>
+__global__ void k_cg_beta_p(const SP* p, SP* pn, const S* __restrict__ r, long n, long rs, CGState* cs,
                             const double* partials, int nparts) {
   __shared__ double sh[4];
   const int q = blockIdx.y;
   CGState& c = cs[q];
-  PUpdate<S, SP, SL> u(p, pn, r, plo, (size_t)q * rs, n);
+  PUpdate<S, SP> u(p, pn, r, (size_t)q * rs, n);
   u.load();
   const double rr0 = c.rr_prev;
   if (wg_once([&] { return c.done != 0; })) return;
@@ -447,64 +441,42 @@ hipError_t launch_cg_beta(CGState* s, const double* partials, int nparts, int nr
   return hipGetLastError();
 }
 
-hipError_t launch_cg_xr(void* x, int xprec, long rsx, void* r, const void* p, const void* Ap, int prec,
-                        long n, long rs, int nrhs, const CGState* s, double* partials, hipStream_t st) {
+hipError_t launch_cg_xr(double2* x, long rsx, double2* r, const double2* p, const double2* Ap, long n, long rs, int nrhs,
+                        const CGState* s, double* partials, hipStream_t st) {
+  k_cg_xr<<<dim3(blas_nblocks(n), nrhs), kB, 0, st>>>(x, r, p, Ap, n, rsx, rs, s, partials);
+  return hipGetLastError();
+}
+
+hipError_t launch_cg_p(void* p, int pprec, const void* r, int rprec, long n, long rs, int nrhs, const CGState* s,
+                       hipStream_t st, void* p_next) {
   dim3 grid(blas_nblocks(n), nrhs);
-  if (prec == P_F64 && xprec == P_F64)
-    k_cg_xr<double2, double2><<<grid, kB, 0, st>>>((double2*)x, (double2*)r, (const double2*)p,
-                                                   (const double2*)Ap, n, rsx, rs, s, partials);
-  else if (prec == P_F32 && xprec == P_F32)
-    k_cg_xr<float2, float2><<<grid, kB, 0, st>>>((float2*)x, (float2*)r, (const float2*)p,
-                                                 (const float2*)Ap, n, rsx, rs, s, partials);
+  void* pn = p_next ? p_next : p;
+  if (rprec == P_F64 && pprec == P_F64)
+    k_cg_p<<<grid, kB, 0, st>>>((const double2*)p, (double2*)pn, (const double2*)r, n, rs, s);
+  else if (rprec == P_F32 && pprec == P_F32)
+    k_cg_p<<<grid, kB, 0, st>>>((const float2*)p, (float2*)pn, (const float2*)r, n, rs, s);
+  else if (rprec == P_F32 && pprec == P_BF16)
+    k_cg_p<<<grid, kB, 0, st>>>((const bf16x2*)p, (bf16x2*)pn, (const float2*)r, n, rs, s);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
-hipError_t launch_cg_p(void* p, const void* r, int prec, long n, long rs, int nrhs, const CGState* s,
-                       void* plo, int lo_prec, hipStream_t st, void* pnext) {
-  dim3 grid(blas_nblocks(n), nrhs);
-  if (prec == P_F64 && p)
-    k_cg_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)(pnext ? pnext : p),
-                                                           (const double2*)r, n, rs, s, (double2*)nullptr);
-  else if (prec == P_F32 && p && (plo == nullptr || lo_prec == P_F32))
-    k_cg_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)(pnext ? pnext : p),
-                                                        (const float2*)r, n, rs, s, (float2*)plo);
-  else if (prec == P_F32 && p && plo && lo_prec == P_BF16)
-    k_cg_p<float2, float2, bf16x2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n, rs, s,
-                                                        (bf16x2*)plo);
-  else if (prec == P_F32 && !p && plo && lo_prec == P_BF16)  // the direction lives in BF16 only
-    k_cg_p<float2, bf16x2, bf16x2><<<grid, kB, 0, st>>>((const bf16x2*)plo, (bf16x2*)(pnext ? pnext : plo),
-                                                        (const float2*)r, n, rs, s, (bf16x2*)nullptr);
-  else
-    return hipErrorInvalidValue;
-  return hipGetLastError();
-}
-
-hipError_t launch_cg_beta_p(void* p, const void* r, int prec, long n, long rs, int nrhs, CGState* s,
-                            void* plo, int lo_prec, const double* partials, int nparts, hipStream_t st,
-                            void* pnext) {
+hipError_t launch_cg_beta_p(void* p, int pprec, const void* r, int rprec, long n, long rs, int nrhs, CGState* s,
+                            const double* partials, int nparts, hipStream_t st, void* p_next) {
   // every workgroup re-sums its rhs's partials before streaming p: with many
   // rhs, fewer workgroups per rhs (at least 256, each streaming more) keep
   // that repeated sum small while the whole grid stays as large
   const int nb = blas_nblocks(n);
   const int nbx = std::min(nb, std::max(256, nb / nrhs));
   dim3 grid(nbx, nrhs);
-  if (prec == P_F64 && p)
-    k_cg_beta_p<double2, double2, double2><<<grid, kB, 0, st>>>((const double2*)p, (double2*)(pnext ? pnext : p),
-                                                                (const double2*)r, n, rs, s, (double2*)nullptr,
-                                                                partials, nparts);
-  else if (prec == P_F32 && p && (plo == nullptr || lo_prec == P_F32))
-    k_cg_beta_p<float2, float2, float2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)(pnext ? pnext : p),
-                                                             (const float2*)r, n, rs, s, (float2*)plo, partials,
-                                                             nparts);
-  else if (prec == P_F32 && p && plo && lo_prec == P_BF16)
-    k_cg_beta_p<float2, float2, bf16x2><<<grid, kB, 0, st>>>((const float2*)p, (float2*)p, (const float2*)r, n,
-                                                             rs, s, (bf16x2*)plo, partials, nparts);
-  else if (prec == P_F32 && !p && plo && lo_prec == P_BF16)  // the direction lives in BF16 only
-    k_cg_beta_p<float2, bf16x2, bf16x2><<<grid, kB, 0, st>>>((const bf16x2*)plo,
-                                                             (bf16x2*)(pnext ? pnext : plo), (const float2*)r,
-                                                             n, rs, s, (bf16x2*)nullptr, partials, nparts);
+  void* pn = p_next ? p_next : p;
+  if (rprec == P_F64 && pprec == P_F64)
+    k_cg_beta_p<<<grid, kB, 0, st>>>((const double2*)p, (double2*)pn, (const double2*)r, n, rs, s, partials, nparts);
+  else if (rprec == P_F32 && pprec == P_F32)
+    k_cg_beta_p<<<grid, kB, 0, st>>>((const float2*)p, (float2*)pn, (const float2*)r, n, rs, s, partials, nparts);
+  else if (rprec == P_F32 && pprec == P_BF16)
+    k_cg_beta_p<<<grid, kB, 0, st>>>((const bf16x2*)p, (bf16x2*)pn, (const float2*)r, n, rs, s, partials, nparts);
   else
     return hipErrorInvalidValue;
   return hipGetLastError();

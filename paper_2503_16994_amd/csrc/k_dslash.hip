@@ -1498,8 +1498,6 @@ hipError_t launch_hop(const HopLaunch& h, hipStream_t st) {
     return dispatch_mode<float2, float2, float2>(h, st);
   if (h.prec == P_BF16 && h.in_prec == P_BF16 && h.out_prec == P_BF16)
     return dispatch_mode<bf16x2, bf16x2, bf16x2>(h, st);
-  if (h.prec == P_BF16 && h.in_prec == P_BF16 && h.out_prec == P_F32)
-    return dispatch_mode<bf16x2, bf16x2, float2>(h, st);
   return hipErrorInvalidValue;
 }
 

@@ -245,18 +245,16 @@ hipError_t launch_cg_setup(CGState* s, const double* b2, const double* eta2, con
                            hipStream_t st);
 hipError_t launch_cg_beta(CGState* s, const double* partials, int nparts, int nrhs,
                           hipStream_t st);
-hipError_t launch_cg_xr(void* x, int xprec, long rsx, void* r, const void* p, const void* Ap,
-                        int prec, long n, long rs, int nrhs, const CGState* s, double* partials,
-                        hipStream_t st);
-// p_next = r + beta p (p itself when p_next is null), also written to p_lo
-// (precision lo_prec) if given; with p null the direction is kept in BF16 alone
-// (r FP32): p_next = r + beta p_lo (p_lo itself when p_next is null)
-hipError_t launch_cg_p(void* p, const void* r, int prec, long n, long rs, int nrhs,
-                       const CGState* s, void* p_lo, int lo_prec, hipStream_t st, void* p_next = nullptr);
+// x += alpha p, r -= alpha Ap, |r|^2 partials (FP64)
+hipError_t launch_cg_xr(double2* x, long rsx, double2* r, const double2* p, const double2* Ap, long n, long rs, int nrhs,
+                        const CGState* s, double* partials, hipStream_t st);
+// p_next = r + beta p (p itself when p_next is null), p and p_next of precision
+// pprec: that of r, or BF16 with r FP32
+hipError_t launch_cg_p(void* p, int pprec, const void* r, int rprec, long n, long rs, int nrhs, const CGState* s,
+                       hipStream_t st, void* p_next = nullptr);
 // beta step and p update in one launch (nparts |r|^2 partials per rhs)
-hipError_t launch_cg_beta_p(void* p, const void* r, int prec, long n, long rs, int nrhs, CGState* s,
-                            void* p_lo, int lo_prec, const double* partials, int nparts, hipStream_t st,
-                            void* p_next = nullptr);
+hipError_t launch_cg_beta_p(void* p, int pprec, const void* r, int rprec, long n, long rs, int nrhs, CGState* s,
+                            const double* partials, int nparts, hipStream_t st, void* p_next = nullptr);
 // deferred x updates: x += sum_j alpha_w[j] p_j over the kXWindow directions
 // p_j of precision pprec (slots with alpha_w[j] = 0 are not read).  With X
 // (FP64; x FP32) given, every rhs with a pending reliable update then also has

@@ -427,7 +427,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   // inner operands of a phase: the low-precision recursion (mixed solves) or
   // FP64 (plain solves, and the continuation of stalled mixed rhs)
   bool lo = false, lo16 = false;  // phase in low precision; BF16 operator operands
-  Vec xi, ri, pi, qi, api, ti, pin, qin, tin;
+  Vec xi, ri, pin, qin, tin;
   const long n_vec = eo ? 12 * V2 : 24 * V2;  // complex elements per rhs of one inner vector
   int lprec = P_F64, nb_blas = blas_nblocks(n_vec);
   auto select = [&](bool low) {
@@ -435,15 +435,13 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     lo16 = low && ip == LQCD_BF16;
     lprec = low ? ip : P_F64;
     if (!low) {
-      xi = X; ri = R; pi = P; qi = Q; api = AP; ti = odd_part(TMP, V2);
-      pin = pi; qin = qi; tin = ti;
+      xi = X; ri = R; pin = P; qin = Q; tin = odd_part(TMP, V2);
     } else {
-      xi = Vec{m.xl, P_F32, HRS}; ri = Vec{m.rl, P_F32, HRS}; pi = Vec{m.pl, P_F32, HRS};
-      qi = Vec{m.ql, P_F32, HRS}; api = Vec{m.apl, P_F32, HRS}; ti = Vec{m.tl, P_F32, HRS};
+      xi = Vec{m.xl, P_F32, HRS}; ri = Vec{m.rl, P_F32, HRS};
       if (lo16) {
         pin = Vec{m.pb, P_BF16, HRS}; qin = Vec{m.qb, P_BF16, HRS}; tin = Vec{m.tb, P_BF16, HRS};
       } else {
-        pin = pi; qin = qi; tin = ti;
+        pin = Vec{m.pl, P_F32, HRS}; qin = Vec{m.ql, P_F32, HRS}; tin = Vec{m.tl, P_F32, HRS};
       }
     }
   };
@@ -507,8 +505,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
   if (x0) {
     LQCD_HIP(launch_cg_force_ru(cg, N, st));
     LQCD_HIP(reliable_update());
-    LQCD_HIP(launch_cg_p(lo16 ? nullptr : pi.p, ri.p, pi.prec, n_vec, pi.rs, N, cg, lo16 ? pin.p : nullptr,
-                         lo16 ? P_BF16 : P_F32, st));
+    LQCD_HIP(launch_cg_p(pin.p, pin.prec, ri.p, ri.prec, n_vec, pin.rs, N, cg, st));
   }
 
   // ---- one CG iteration (graph-capturable: kernels only) --------------------
@@ -581,28 +578,23 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
       nb_r = nb_it;
     } else {
       if ((e = dw_full(c, (const double2*)pin.p, (double2*)qin.p, true, parts, done))) return e;
-      if ((e = dw_full(dg(c), (const double2*)qin.p, (double2*)api.p, true, nullptr, done, cg, parts, nb_op)))
+      if ((e = dw_full(dg(c), (const double2*)qin.p, m.AP, true, nullptr, done, cg, parts, nb_op)))
         return e;  // + alpha
-      if ((e = launch_cg_xr(xi.p, xi.prec, xi.rs, ri.p, pi.p, api.p, ri.prec, n_vec, ri.rs, N, cg, parts,
-                            st)))
-        return e;
+      if ((e = launch_cg_xr(m.X, FRS, m.R, m.P, m.AP, n_vec, FRS, N, cg, parts, st))) return e;
       nb_r = nb_blas;
     }
     // with BF16 operands the search direction is kept in BF16 alone: the
     // recursion then updates x with the very vector the operator saw
-    void* p = lo16 ? nullptr : pin.p;
-    void* plo = lo16 ? pin.p : nullptr;
     void* pnext = eo ? pwin[(slot + 1) % kXWindow].p : nullptr;
-    const int plo_prec = lo16 ? P_BF16 : P_F32;
     if ((i + 1) % kRuStride != 0 && fuse_p) return hipSuccess;  // with the next iteration
     if ((i + 1) % kRuStride != 0)
-      return launch_cg_beta_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, parts_r, nb_r, st, pnext);
+      return launch_cg_beta_p(pin.p, pin.prec, ri.p, ri.prec, n_vec, pin.rs, N, cg, parts_r, nb_r, st, pnext);
     if ((e = launch_cg_beta(cg, parts_r, nb_r, N, st))) return e;
     if (eo && (e = launch_cg_xflush(xi.p, xi.prec, xi.rs, pw, pin.prec, n_vec, pin.rs, N, cg, st, lo ? m.X : nullptr,
                                     FRS)))
       return e;
     if ((e = reliable_update())) return e;
-    return launch_cg_p(p, ri.p, pi.prec, n_vec, pi.rs, N, cg, plo, plo_prec, st, pnext);
+    return launch_cg_p(pin.p, pin.prec, ri.p, ri.prec, n_vec, pin.rs, N, cg, st, pnext);
   };
   constexpr int K = 10 * kRuStride;      // iterations per chunk (host poll / graph)
   constexpr int K_TAIL = 2 * kRuStride;  // chunk length near convergence
@@ -713,7 +705,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     select(false);
     LQCD_HIP(open_window());
     LQCD_HIP(reliable_update());
-    LQCD_HIP(launch_cg_p(m.P, m.R, P_F64, n_vec, FRS, N, cg, nullptr, P_F32, st));
+    LQCD_HIP(launch_cg_p(m.P, P_F64, m.R, P_F64, n_vec, FRS, N, cg, st));
     rc = run_phase(stalled);
     if (rc) return rc;
   }
