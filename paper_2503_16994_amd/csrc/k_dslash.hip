@@ -870,6 +870,7 @@ __global__ __launch_bounds__(kSpreadBlock) void k_hop_spread(const HopLaunch a) 
   const int l = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int nwork = a.nbs * a.nrhs;
+  if (nwork == 0) return;  // launch_hop_place
   if ((int)blockIdx.x >= nwork) {  // the extra workgroups: alpha of one rhs each (see HopLaunch::alpha_cg)
     const int r = blockIdx.x - nwork;
     CGState& c = a.alpha_cg[r];
@@ -1188,14 +1189,16 @@ static bool tm_on(const HopLaunch& h) { return h.tm_post != 0 || h.tm_mu != 0.0;
 // 0.98 / 0.98; BF16 20480 1.13 / 1.14, 32768 1.13 / 1.14, 36864 0.96 / 0.94, 40960
 // 0.95 / 0.91; twelve fields: FP64 30720 0.95, FP32 43008 0.92, BF16 30720 1.14,
 // 43008 0.98; full-lattice solves 20480 0.96; Dw 20480 0.93.
-// The caller's direction split sums in another order and keeps its own kernel.
+// The caller's direction split sums in another order and keeps its own kernel, and
+// so does a launch that asks for the general form: a workgroup of eight waves finds
+// no place on a GPU that another stream's launches keep full.
 constexpr long kCUs = 256;
 static int spread_nblocks(const HopLaunch& h) {
   return (h.both ? 2 : 1) * ((h.g.V2 + kSpreadSites - 1) / kSpreadSites);
 }
 static long spread_workgroups(const HopLaunch& h) { return (long)spread_nblocks(h) * h.nrhs; }
 static bool spread_on(const HopLaunch& h) {
-  return h.hop && !split_on(h) && spread_workgroups(h) <= (h.prec == P_F64 ? 1 : 2) * kCUs;
+  return h.hop && !h.general && !split_on(h) && spread_workgroups(h) <= (h.prec == P_F64 ? 1 : 2) * kCUs;
 }
 
 // Unused dynamic LDS that caps the workgroups resident per CU (160 KiB of LDS
@@ -1273,6 +1276,14 @@ static hipError_t launch_spread(HopLaunch h, hipStream_t st) {
   }
   if (h.pf_r) return hipErrorInvalidValue;
   k_hop_spread<SG, SI, SO, XR, false><<<grid, kSpreadBlock, 0, st>>>(h);
+  return hipGetLastError();
+}
+
+hipError_t launch_hop_place(int prec, hipStream_t st) {
+  HopLaunch h{};  // no site blocks: every workgroup ends at once
+  if (prec == P_F64) k_hop_spread<double2, double2, double2, false, false><<<32, kSpreadBlock, 0, st>>>(h);
+  else if (prec == P_F32) k_hop_spread<float2, float2, float2, false, false><<<32, kSpreadBlock, 0, st>>>(h);
+  else k_hop_spread<bf16x2, bf16x2, bf16x2, false, false><<<32, kSpreadBlock, 0, st>>>(h);
   return hipGetLastError();
 }
 

@@ -278,6 +278,8 @@ extern "C" void lqcd_ws_free(lqcd_ws_t* w) {
     if (e.exec) (void)hipGraphExecDestroy(e.exec);
     if (e.graph) (void)hipGraphDestroy(e.graph);
   }
+  for (hipEvent_t e : w->probe)
+    if (e) (void)hipEventDestroy(e);
   delete w;
 }
 

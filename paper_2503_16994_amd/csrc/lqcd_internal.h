@@ -60,6 +60,7 @@ struct GraphEntry {
   uint64_t gauge_uid;
   int solver, inner_prec, nrhs, chunk;
   double mu;  // twisted mass (a kernel argument of the captured launches)
+  bool shared;  // general hop launches only
   lqcd_tuning tune_inner, tune_f64, tune_f32;
   hipGraph_t graph;
   hipGraphExec_t exec;
@@ -85,6 +86,7 @@ struct lqcd_ws {
   double kappa = 0, csw = 0, cF = 0, mu = 0;
   int clover_pmask = 0;
   std::vector<GraphEntry> graphs;
+  hipEvent_t probe[2] = {nullptr, nullptr};  // around the look for a place of a small solve
   lqcd_tuning tune[3] = {kDefaultTuning, kDefaultTuning, kDefaultTuning};
   bool tune_set[3] = {false, false, false};  // not the default (else: own_tuning)
 };

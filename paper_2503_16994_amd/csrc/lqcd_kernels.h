@@ -69,6 +69,7 @@ struct HopLaunch {
   double tm_mu;
   int tm_post;
   const void* Ctm;  // clover blocks A of the output parity (tm_post only)
+  bool general;      // not the small form, whatever the size (see hop_nparts)
   unsigned lds_cap;  // dynamic LDS bytes of the launch (set by the launcher)
   // filled in by the launcher
   int nbs;  // site blocks (both parities in `both` mode)
@@ -133,6 +134,9 @@ bool hop_fuses_p(const HopLaunch& h);
 // whether a launch of this shape takes canonical input (HopLaunch::cy, cz)
 bool hop_reads_canonical(const HopLaunch& h);
 hipError_t launch_hop_xr(const HopLaunch& h, hipStream_t st);
+// 32 workgroups of the small form that do nothing: the time they take is the time
+// such workgroups wait for a place
+hipError_t launch_hop_place(int prec, hipStream_t st);
 
 // Gauge import: canonical complex128 U -> internal links (any non-null
 // precision pointer is written); OPEN zeroes U_t(T-1).  two_row: store the

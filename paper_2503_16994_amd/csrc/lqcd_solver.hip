@@ -52,7 +52,17 @@ struct Ctl {
   int nrhs;
   double mu;         // twisted mass
   bool dag = false;  // launches of the adjoint operator g5 D(-mu) g5
+  bool shared = false;  // the GPU is busy with other work: general hop launches only
 };
+
+// Small hop launches have workgroups of eight waves, which find no place while the
+// launches of another stream keep the GPU full: 8^4 solves beside one of 12 rhs on
+// 24^3x48 took 52 ms (FP64, 1 rhs) and 46 (FP32, 12 rhs) with them, 13 and 15 with the
+// general form; alone 2.5 and 4.1, and 3.9 and 4.6.  So a small solve first looks how
+// long such workgroups wait for a place (launch_hop_place): 6 to 16 us on a GPU of
+// its own, beside that solve 100 to 600, beside one of 1 rhs, which leaves gaps, 7 to
+// 80 (where neither form is much better).  The form changes no result.
+constexpr float kSharedMs = 0.020f;
 
 // the same context for the adjoint operator (D(mu)^+ = g5 D(-mu) g5)
 Ctl dg(const Ctl& c) {
@@ -95,6 +105,7 @@ HopLaunch mk(const Ctl& c, int lprec, bool both = false) {
   h.tm_mu = c.dag ? -c.mu : c.mu;
   h.tm_post = c.mu != 0.0 ? 1 : 0;
   h.both = both;
+  h.general = c.shared;
   apply_tuning(h, tuning_of(c.w, lprec, c.nrhs, both));
   if (c.mu != 0.0) single_tile(h);  // twisted-mass kernels: one rhs per thread
   return h;
@@ -358,6 +369,20 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     const long nsite = g->V * 12;
     const bool sf = g->desc.bc == LQCD_BC_SF;
     const long nslice = g->V / g->desc.L[3] * 12;  // t = 0 is the first slice
+    // small hop launches: do their workgroups find a place (see kSharedMs)
+    const int place_prec = eo ? ip : P_F64;
+    const bool small = hop_nparts(mk(c, place_prec, !eo)) < 0;
+    hipEvent_t* const ev = w->probe;
+    if (small) {
+      if (!ev[1]) {
+        for (int i = 0; i < 2; ++i)
+          if (!ev[i]) LQCD_HIP(hipEventCreate(&ev[i]));
+        LQCD_HIP(launch_hop_place(place_prec, st));  // untimed: a process's first launch loads the kernel
+      }
+      LQCD_HIP(hipEventRecord(ev[0], st));
+      LQCD_HIP(launch_hop_place(place_prec, st));
+      LQCD_HIP(hipEventRecord(ev[1], st));
+    }
     auto norms = [&](const void* v, double* dst_all, double* dst_t0) -> hipError_t {
       hipError_t e = launch_norm2(v, P_F64, nsite, nsite, N, parts, st);
       if (e == hipSuccess) e = launch_reduce(parts, blas_nblocks(nsite), N, dst_all, st);
@@ -370,6 +395,11 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
     std::vector<double> tmp(6 * N, 0.0);
     LQCD_HIP(hipMemcpyAsync(tmp.data(), scal, sizeof(double) * 6 * N, hipMemcpyDeviceToHost, st));
     LQCD_HIP(hipStreamSynchronize(st));
+    if (small) {
+      float ms = 0.f;
+      LQCD_HIP(hipEventElapsedTime(&ms, ev[0], ev[1]));
+      c.shared = ms > kSharedMs;
+    }
     for (int r = 0; r < N; ++r) {
       h_eta2[r] = tmp[N + r];
       if (!isfinite(tmp[N + r])) return fail(LQCD_ENUMERIC, "lqcd_solve: source %d has NaN/Inf entries", r);
@@ -610,7 +640,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
       hipGraphExec_t exec = nullptr;
       for (auto& e : w->graphs)
         if (e.gauge_uid == u->uid && e.solver == prm->solver && e.inner_prec == key_prec && e.nrhs == N &&
-            e.chunk == len && e.mu == c.mu && same_tuning(e.tune_inner, tn) && same_tuning(e.tune_f64, t64) &&
+            e.chunk == len && e.mu == c.mu && e.shared == c.shared && same_tuning(e.tune_inner, tn) && same_tuning(e.tune_f64, t64) &&
             same_tuning(e.tune_f32, t32))
           exec = e.exec;
       if (!exec) {
@@ -629,7 +659,7 @@ extern "C" int lqcd_solve(const lqcd_gauge_t* u, const lqcd_solve_params* prm, c
           (void)hipGraphDestroy(gr);
           return hip_status(e3, "hipGraphInstantiate");
         }
-        w->graphs.push_back(GraphEntry{u->uid, prm->solver, key_prec, N, len, c.mu, tn, t64, t32, gr, exec});
+        w->graphs.push_back(GraphEntry{u->uid, prm->solver, key_prec, N, len, c.mu, c.shared, tn, t64, t32, gr, exec});
       }
       LQCD_HIP(hipGraphLaunch(exec, st));
       return LQCD_OK;

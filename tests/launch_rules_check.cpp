@@ -44,6 +44,9 @@ static void small_launches() {
           for (long V2 = 16; V2 * nrhs < 64 * 2 * line; V2 += 16) {
             const bool small = hop_nparts(hop(prec, V2, nrhs, both != 0, mu)) < 0;
             const long n = (both ? 2 : 1) * ((V2 + 63) / 64) * nrhs;
+            HopLaunch g = hop(prec, V2, nrhs, both != 0, mu);
+            g.general = true;  // asked for
+            CHECK(hop_nparts(g) > 0 && !hop_reads_canonical(g) && !hop_fuses_p(g), "prec %d V2 %ld: general form", prec, V2);
             CHECK(small == (n <= line), "prec %d nrhs %d both %d mu %g workgroups %ld", prec, nrhs, both, mu, n);
             if (failures > 10) return;
           }
