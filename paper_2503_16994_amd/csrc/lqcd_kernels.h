@@ -50,6 +50,7 @@ struct HopLaunch {
   // part of full vectors, parity 1 lies par_stride elements further and the
   // Cpre blocks of parity 1 cpre_par elements further.
   bool both;
+  bool general;  // not the small form, whatever the size (see hop_nparts)
   long par_stride;
   long cpre_par;
   // tuning: block order (0..6, see block_order in k_dslash.hip) and the
@@ -69,7 +70,6 @@ struct HopLaunch {
   double tm_mu;
   int tm_post;
   const void* Ctm;  // clover blocks A of the output parity (tm_post only)
-  bool general;      // not the small form, whatever the size (see hop_nparts)
   unsigned lds_cap;  // dynamic LDS bytes of the launch (set by the launcher)
   // filled in by the launcher
   int nbs;  // site blocks (both parities in `both` mode)
@@ -134,7 +134,7 @@ bool hop_fuses_p(const HopLaunch& h);
 // whether a launch of this shape takes canonical input (HopLaunch::cy, cz)
 bool hop_reads_canonical(const HopLaunch& h);
 hipError_t launch_hop_xr(const HopLaunch& h, hipStream_t st);
-// 32 workgroups of the small form that do nothing: the time they take is the time
+// 32 empty workgroups of the small form's registers and LDS: the time they take is the time
 // such workgroups wait for a place
 hipError_t launch_hop_place(int prec, hipStream_t st);
 
