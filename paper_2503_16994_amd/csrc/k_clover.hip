@@ -25,11 +25,11 @@
 // Bound: the links through L2 (twelve per plane and site), and their latency:
 // with W = 6 four of six waves end at the barrier while the last two hold the
 // workgroup's place, and only 1.5 waves per SIMD are resident on average.  W = 2
-// keeps every wave to the end: 24^3x48 (two rows, FP64 stored) 664 -> 538 us, and
-// with the tile order below and stores past L2 455.  W = 6 is the shorter chain
-// while the chip is not full: a changed operator and its Dw at 12x10x8x14 (210
-// workgroups) 53 us with W = 6, 58 with 2; 12^3x24 (648) 93 and 86; 32^3x64 2707
-// and 2172.  Two waves per SIMD: at three, 25 to 36 registers spill (W = 2: 598
+// keeps every wave to the end: 24^3x48 (two rows, three precisions stored) 664 ->
+// 538 us, and with the tile order below and stores past L2 433 to 455 (FP64 alone
+// 349).  W = 6 is the shorter chain while the chip is not full: a changed operator
+// and its Dw at 12x10x8x14 (210 workgroups) 53 us with W = 6, 58 with 2; 12^3x24
+// (648) 93 and 86; 32^3x64 2707 and 2172.  Two waves per SIMD: at three, 25 to 36 registers spill (W = 2: 598
 // against 495 us).
 #include "clover_inv.h"
 #include "lqcd_kernels.h"
